@@ -84,8 +84,8 @@ __device__ __forceinline__ void pb_load_rows(const void *src, uint64_t n_elems, 
             if (active && at < real) {
                 const uint32_t *in = reinterpret_cast<const uint32_t *>(src) + blk0 + at;
                 if (at + 8u <= real) {
-                    u = *reinterpret_cast<const uint4 *>(in);
-                    v = *reinterpret_cast<const uint4 *>(in + 4);
+                    u = ld_stream(reinterpret_cast<const uint4 *>(in));
+                    v = ld_stream(reinterpret_cast<const uint4 *>(in + 4));
                 } else {
                     uint32_t d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
@@ -102,7 +102,7 @@ __device__ __forceinline__ void pb_load_rows(const void *src, uint64_t n_elems, 
             if (active && at < real) {
                 const uint16_t *in = reinterpret_cast<const uint16_t *>(src) + blk0 + at;
                 if (at + 8u <= real) {
-                    r = *reinterpret_cast<const uint4 *>(in);
+                    r = ld_stream(reinterpret_cast<const uint4 *>(in));
                 } else {
                     uint32_t d[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -259,9 +259,9 @@ compress_per_block_kernel(const PbCompressArgs p)
                              byte_perm(v.y, v.x, 0x07060302u), byte_perm(v.w, v.z, 0x07060302u));
             // the lower halves leave at once (pads have zero lower halves; the region is padded to 16 bytes)
             if (active && at < real)
-                *reinterpret_cast<uint4 *>(it.out + it.tail_base + 2u * (blk0 + at)) =
-                    make_uint4(byte_perm(u.y, u.x, 0x05040100u), byte_perm(u.w, u.z, 0x05040100u),
-                               byte_perm(v.y, v.x, 0x05040100u), byte_perm(v.w, v.z, 0x05040100u));
+                st_stream(reinterpret_cast<uint4 *>(it.out + it.tail_base + 2u * (blk0 + at)),
+                          make_uint4(byte_perm(u.y, u.x, 0x05040100u), byte_perm(u.w, u.z, 0x05040100u),
+                                     byte_perm(v.y, v.x, 0x05040100u), byte_perm(v.w, v.z, 0x05040100u)));
         } else {
             r16 = raw[t];
         }
@@ -593,11 +593,11 @@ compress_per_block_kernel(const PbCompressArgs p)
             // pads have zero raw bytes already (their words were loaded as zero)
             const uint2 sm = t < PB_SM_REG_ROWS ? make_uint2(SM[t % PB_SM_REG_ROWS][0], SM[t % PB_SM_REG_ROWS][1])
                                                 : *reinterpret_cast<const uint2 *>(sm_park + (((uint32_t)(t - PB_SM_REG_ROWS) * blockDim.x + tid) << 3));
-            *reinterpret_cast<uint2 *>(dst + ((size_t)t << logC) + 8u * tid) = sm;
+            st_stream(reinterpret_cast<uint2 *>(dst + ((size_t)t << logC) + 8u * tid), sm);
         }
     }
     for (uint32_t v = tid; v < (mask_bytes >> 4); v += blockDim.x)
-        *reinterpret_cast<uint4 *>(dst + B + 16u * v) = *reinterpret_cast<const uint4 *>(img + 16u * v);
+        st_stream(reinterpret_cast<uint4 *>(dst + B + 16u * v), *reinterpret_cast<const uint4 *>(img + 16u * v));
     if (lm > 0) {
         uint8_t *dlow = dst + B + mask_bytes;
         const uint32_t T2 = (lm * B) >> 4;               // half of the plane's length
@@ -609,7 +609,7 @@ compress_per_block_kernel(const PbCompressArgs p)
             o.y = byte_perm(hi.x, lo.x, 0x07030602u);
             o.z = byte_perm(hi.y, lo.y, 0x05010400u);
             o.w = byte_perm(hi.y, lo.y, 0x07030602u);
-            *reinterpret_cast<uint4 *>(dlow + 16u * v) = o;
+            st_stream(reinterpret_cast<uint4 *>(dlow + 16u * v), o);
         }
     }
     if (a > 0) {
@@ -624,7 +624,7 @@ compress_per_block_kernel(const PbCompressArgs p)
                 if (at >= hbytes) w[i] = 0;
                 else if (at + 4u > hbytes) w[i] &= (1u << (8u * (hbytes - at))) - 1u;
             }
-            *reinterpret_cast<uint4 *>(dhigh + 16u * v) = make_uint4(w[0], w[1], w[2], w[3]);
+            st_stream(reinterpret_cast<uint4 *>(dhigh + 16u * v), make_uint4(w[0], w[1], w[2], w[3]));
         }
     }
     if (tid == 0) {
@@ -700,11 +700,11 @@ __global__ void __launch_bounds__(512) decompress_per_block_kernel(const PbDecom
     const uint8_t *src = it.in + it.payload_base + t0;
     const uint32_t nvec = ((uint32_t)sz - B) >> 4;
     for (uint32_t v = tid; v < nvec; v += blockDim.x)
-        *reinterpret_cast<uint4 *>(smem + 16u * v) = *reinterpret_cast<const uint4 *>(src + B + 16u * v);
+        *reinterpret_cast<uint4 *>(smem + 16u * v) = ld_stream(reinterpret_cast<const uint4 *>(src + B + 16u * v));
     uint2 smv[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t)
-        smv[t] = active ? *reinterpret_cast<const uint2 *>(src + ((size_t)t << logC) + 8u * tid) : make_uint2(0, 0);
+        smv[t] = active ? ld_stream(reinterpret_cast<const uint2 *>(src + ((size_t)t << logC) + 8u * tid)) : make_uint2(0, 0);
     __syncthreads();
     if (!active) return;
 
@@ -774,7 +774,7 @@ __global__ void __launch_bounds__(512) decompress_per_block_kernel(const PbDecom
         }
         if constexpr (DT == DT_FP32) {
             if (e0 < it.n_elems) {
-                const uint4 tl = *reinterpret_cast<const uint4 *>(it.in + it.tail_base + 2u * e0);   // region padded to 16 bytes
+                const uint4 tl = ld_stream(reinterpret_cast<const uint4 *>(it.in + it.tail_base + 2u * e0));   // region padded to 16 bytes
                 const uint32_t lo[4] = {tl.x, tl.y, tl.z, tl.w};
                 uint32_t w[8];
 #pragma unroll
@@ -784,8 +784,8 @@ __global__ void __launch_bounds__(512) decompress_per_block_kernel(const PbDecom
                 }
                 uint32_t *out32 = reinterpret_cast<uint32_t *>(it.out);
                 if (e0 + 8 <= it.n_elems) {
-                    *reinterpret_cast<uint4 *>(out32 + e0) = make_uint4(w[0], w[1], w[2], w[3]);
-                    *reinterpret_cast<uint4 *>(out32 + e0 + 4) = make_uint4(w[4], w[5], w[6], w[7]);
+                    st_stream(reinterpret_cast<uint4 *>(out32 + e0), make_uint4(w[0], w[1], w[2], w[3]));
+                    st_stream(reinterpret_cast<uint4 *>(out32 + e0 + 4), make_uint4(w[4], w[5], w[6], w[7]));
                 } else {
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
@@ -795,7 +795,7 @@ __global__ void __launch_bounds__(512) decompress_per_block_kernel(const PbDecom
         } else {
             uint16_t *out16 = reinterpret_cast<uint16_t *>(it.out);
             if (e0 + 8 <= it.n_elems) {
-                *reinterpret_cast<uint4 *>(out16 + e0) = make_uint4(o[0], o[1], o[2], o[3]);
+                st_stream(reinterpret_cast<uint4 *>(out16 + e0), make_uint4(o[0], o[1], o[2], o[3]));
             } else if (e0 < it.n_elems) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
