@@ -3,9 +3,10 @@
 libenec_test.so is the same library with ENEC_TEST_HOOKS defined for the host code: there the environment
 variable ENEC_SPIN_LIMIT lowers the bound of the scan's waits, which the tests of that bound need.
 
-The host code (csrc/enec_api.hip, csrc/enec_pipeline.hip), the kernels for streams with one tuple per data block
-(csrc/enec_per_block.hip) and the 18 kernel tables (csrc/enec_kernels.hip, once per element format, group
-length and direction) are compiled side by side into _build/*.o and linked into libenec.so.
+The host code (csrc/enec_api.hip, csrc/enec_pipeline.hip), the compression kernels for one tuple per data block
+(csrc/enec_per_block.hip), the decompression kernels (csrc/enec_decompress.hip) and the nine tables of compression
+kernels (csrc/enec_kernels.hip, once per element format and group length) are compiled side by side into
+_build/*.o and linked into libenec.so.
 """
 from __future__ import annotations
 
@@ -20,9 +21,10 @@ TEST_LIB = os.path.join(HERE, "libenec_test.so")      # the same library with EN
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 SOURCES = [os.path.join(CSRC, "enec_api.hip"), os.path.join(CSRC, "enec_kernels.hip"),
-           os.path.join(CSRC, "enec_per_block.hip"), os.path.join(CSRC, "enec_pipeline.hip")]
+           os.path.join(CSRC, "enec_per_block.hip"), os.path.join(CSRC, "enec_pipeline.hip"),
+           os.path.join(CSRC, "enec_decompress.hip")]
 HEADERS = [os.path.join(CSRC, "enec_device.hpp"), os.path.join(CSRC, "enec_kernels.hpp"),
-           os.path.join(CSRC, "enec_per_block.hpp"),
+           os.path.join(CSRC, "enec_per_block.hpp"), os.path.join(CSRC, "enec_decompress.hpp"),
            os.path.join(ROOT, "include", "enec.h")]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-ffp-contract=off",
@@ -31,12 +33,10 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950",
 
 def _units():
     units = [("enec_api.o", [SOURCES[0]]), ("enec_api_test.o", ["-DENEC_TEST_HOOKS", SOURCES[0]]),
-             ("enec_per_block.o", [SOURCES[2]]), ("enec_pipeline.o", [SOURCES[3]])]
+             ("enec_per_block.o", [SOURCES[2]]), ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]])]
     for lpg in (2, 1, 4):           # lanes per group: group lengths 16, 8, 32
         for dt in (0, 2, 1):
-            for direction in (0, 1):
-                units.append((f"enec_kernels_dt{dt}_lpg{lpg}_dir{direction}.o",
-                              [f"-DENEC_DT={dt}", f"-DENEC_LPG={lpg}", f"-DENEC_DIR={direction}", SOURCES[1]]))
+            units.append((f"enec_kernels_dt{dt}_lpg{lpg}.o", [f"-DENEC_DT={dt}", f"-DENEC_LPG={lpg}", SOURCES[1]]))
     return units
 
 

@@ -88,15 +88,6 @@ inline CompressFn pick_compress(int m, int a, int dtype, unsigned L)
     return ENEC_ROW(dt0);
 #undef ENEC_ROW
 }
-inline DecompressFn pick_decompress(int m, int a, int dtype, unsigned L)
-{
-#define ENEC_ROW(dt) (L == 8 ? pick_decompress_##dt##_lpg1(m, a) : L == 16 ? pick_decompress_##dt##_lpg2(m, a) : pick_decompress_##dt##_lpg4(m, a))
-    if (dtype == ENEC_FP16) return ENEC_ROW(dt1);
-    if (dtype == ENEC_FP32) return ENEC_ROW(dt2);
-    return ENEC_ROW(dt0);
-#undef ENEC_ROW
-}
-
 // A group length needs whole 16-byte vectors of mask per block (B >= 128 L) and at most 64 mask
 // words per block (the kernels scan them with one wave: B / L <= 2048).
 inline bool group_fits_block(unsigned L, uint32_t B) { return B >= 128u * L && B / L <= 2048u; }
@@ -776,82 +767,51 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
             return ENEC_E_FORMAT;
         }
     }
+    // Streams of one element format, group length and block size share a launch (up to MAX_BATCH each),
+    // whether they have one tuple or one tuple per block and whatever the tuples are.
     std::vector<char> done(n_items, 0);
-    {
-        for (size_t i = 0; i < n_items; ++i) {
-            if (done[i]) continue;
-            if (hdr[i].nb == 0) { done[i] = 1; continue; }
-            if (hdr[i].per_block) {
-                // streams with one tuple per block: those of one element format, group length and block size
-                // share a launch (up to MAX_BATCH each); their tuples are read from the streams
-                const Header &h0 = hdr[i];
-                PbDecompressArgs a;
-                a.n_items = 0;
-                a.n_blocks = 0;
-                a.B = h0.B; a.logB = ilog2(h0.B);
-                for (size_t j = i; j < n_items && a.n_items < (uint32_t)MAX_BATCH; ++j) {
-                    const Header &h = hdr[j];
-                    if (done[j] || h.nb == 0 || !h.per_block || h.B != h0.B || h.dtype != h0.dtype || h.prm.L != h0.prm.L ||
-                        (uint64_t)a.n_blocks + h.nb > 0xFFFFFFFFull)
-                        continue;
-                    PbDecompressItem &d = a.item[a.n_items++];
-                    d.in = static_cast<const uint8_t *>(items[j].in);
-                    d.out = items[j].out;
-                    d.n_elems = items[j].n_elems;
-                    d.tuples_at = table_end(d.n_elems, h.B);
-                    d.tail_base = d.tuples_at + tuple_table_bytes(d.n_elems, h.B);
-                    d.payload_base = payload_base(d.n_elems, h.B, h.dtype) + tuple_table_bytes(d.n_elems, h.B);
-                    d.payload_bytes = h.total - d.payload_base;
-                    d.nb = h.nb;
-                    d.first = a.n_blocks;
-                    d.status = items[j].status;
-                    std::memcpy(d.hdr, items[j].host_header, sizeof d.hdr);
-                    a.n_blocks += h.nb;
-                    done[j] = 1;
-                }
-                for (uint32_t j = a.n_items; j < (uint32_t)MAX_BATCH; ++j) a.item[j] = a.item[0];
-                PbDecompressFn fn = pick_decompress_per_block(h0.dtype, h0.prm.L);
-                if (!fn) return ENEC_E_FORMAT;
-                const unsigned threads = h0.B / 64 < 64 ? 64 : h0.B / 64;
-                const size_t lds = (size_t)h0.B / (8 * h0.prm.L) + h0.B + 16;     // the packed part of the widest block
-                hipLaunchKernelGGL(fn, dim3(a.n_blocks), dim3(threads), lds, s, a);
+    for (size_t i = 0; i < n_items; ++i) {
+        if (done[i]) continue;
+        if (hdr[i].nb == 0) { done[i] = 1; continue; }
+        const Header &h0 = hdr[i];
+        const unsigned threads = h0.B / 64 < 64 ? 64 : h0.B / 64;
+        DecompressArgs a;
+        a.B = h0.B;
+        a.logB = ilog2(h0.B);
+        uint32_t items_in = 0, widest = 0;
+        uint64_t blocks = 0;
+        for (size_t j = i; j < n_items && items_in < (uint32_t)MAX_BATCH; ++j) {
+            const Header &h = hdr[j];
+            if (done[j] || h.nb == 0 || h.B != h0.B || h.dtype != h0.dtype || h.prm.L != h0.prm.L ||
+                (blocks + h.nb) * threads > 0xFFFFFFFFull)            // a grid has fewer than 2^32 threads
                 continue;
-            }
-            DecompressArgs a;
-            a.B = hdr[i].B;
-            a.logB = ilog2(a.B);
-            a.n_items = 0;
-            a.total = 0;
-            for (size_t j = i; j < n_items && a.n_items < (uint32_t)MAX_BATCH; ++j) {
-                const Header &h = hdr[j];
-                if (done[j] || h.nb == 0 || h.per_block || h.B != a.B || h.prm.m != hdr[i].prm.m ||
-                    h.prm.n != hdr[i].prm.n || h.dtype != hdr[i].dtype || h.prm.L != hdr[i].prm.L)
-                    continue;
-                DecompressItem &c = a.item[a.n_items++];
-                c.in = static_cast<const uint8_t *>(items[j].in);
-                c.out = static_cast<uint16_t *>(items[j].out);
-                c.n_elems = items[j].n_elems;
-                c.payload_base = payload_base(items[j].n_elems, h.B, h.dtype);
-                c.payload_bytes = h.total - c.payload_base;
-                c.tail_base = table_end(items[j].n_elems, h.B);
-                c.nb = h.nb;
-                c.first = a.total;
-                c.b = h.prm.b;
-                c.mode = subtract_mode(h.prm.b, h.prm.n, h.dtype) == 0 ? 0u : 1u;
-                c.status = items[j].status;
-                std::memcpy(c.hdr, items[j].host_header, sizeof c.hdr);
-                a.total += c.nb;
-                done[j] = 1;
-            }
-            DecompressFn fn = pick_decompress(hdr[i].prm.m, hdr[i].prm.n - hdr[i].prm.m, hdr[i].dtype, hdr[i].prm.L);
-            if (!fn) return ENEC_E_FORMAT;
-            const unsigned threads = a.B / 64 < 64 ? 64 : a.B / 64;
-            const size_t plane_bits = hdr[i].prm.n + (hdr[i].dtype == ENEC_FP16 ? 3 : 0);
-            const size_t lds = 2 * ((size_t)a.B / (8 * hdr[i].prm.L) + plane_bits * a.B / 8);   // two images of the packed part
-            const unsigned resident = resident_workgroups((const void *)fn, threads, lds);
-            if (resident == 0) return ENEC_E_HIP;
-            hipLaunchKernelGGL(fn, dim3(persistent_grid(a.total, resident)), dim3(threads), lds, s, a);
+            const size_t tuples = h.per_block ? tuple_table_bytes(items[j].n_elems, h.B) : 0;
+            a.first[items_in] = (uint32_t)blocks;
+            DecompressItem &d = a.item[items_in++];
+            d.in = static_cast<const uint8_t *>(items[j].in);
+            d.out = items[j].out;
+            d.n_elems = items[j].n_elems;
+            d.tuples_at = h.per_block ? table_end(d.n_elems, h.B) : 24;
+            d.tuple_stride = h.per_block ? 4u : 0u;
+            d.tail_base = table_end(d.n_elems, h.B) + tuples;
+            d.payload_base = payload_base(d.n_elems, h.B, h.dtype) + tuples;
+            d.payload_bytes = h.total - d.payload_base;
+            d.status = items[j].status;
+            std::memcpy(d.hdr, items[j].host_header, sizeof d.hdr);
+            const uint32_t bits = h.per_block ? 8u : h.prm.n + (h.dtype == ENEC_FP16 ? 3u : 0u);
+            if (bits > widest) widest = bits;
+            blocks += h.nb;
+            done[j] = 1;
         }
+        for (uint32_t j = items_in; j < (uint32_t)MAX_BATCH; ++j) {
+            a.first[j] = 0xFFFFFFFFu;
+            a.item[j] = a.item[0];
+        }
+        DecompressFn fn = pick_decompress(h0.dtype, h0.prm.L);
+        if (!fn) return ENEC_E_FORMAT;
+        // the packed part of the widest block of the launch: mask | low plane | high records | padding
+        const size_t lds = (size_t)h0.B / (8 * h0.prm.L) + (size_t)widest * h0.B / 8 + 16;
+        hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(threads), lds, s, a);
     }
     return hipGetLastError() == hipSuccess ? ENEC_OK : ENEC_E_HIP;
 }

@@ -1,0 +1,220 @@
+// Decompression: offset lookup, mask prefix, unpack, inverse transform, recombine (Sec. V-A decompression
+// path; Alg. 1 decompression part), for streams with one tuple and with one tuple per data block.
+//
+// Bound: HBM.  One workgroup per data block, as many as the grid needs, none of them persistent: blocks are
+// independent, and a workgroup that starts when another ends keeps the accesses of the device in stream
+// order.  A kernel that only moves the bytes of a block (24.8 KB in, 32 KB out) reaches 5.9 TB/s that way
+// and 5.75 with a persistent grid and the next block prefetched, which this kernel replaced.  What a
+// block waits for (table entry, then its payload) is hidden by the other seven workgroups of the CU: 64
+// registers and at most B + B / (8 L) bytes of LDS let eight share it.
+//
+// The widths (m, n) are run-time values, uniform over the workgroup: the unpackers are reached through a
+// switch over eight low-plane widths and eight record widths.  So the streams of a call that differ only in
+// their tuples share a launch: the nine tensors of a decoder layer, whose norm vectors have a tuple of their
+// own, take one launch instead of two (138 + 6.3 us of kernels and the gap between them before).
+#pragma once
+#include "enec_kernels.hpp"
+
+namespace enec {
+
+// d3: plane values of the thread's 8 rows from the stream's low plane (already joined pairwise by
+// Alg. 2's last step: stream byte 2i = normalized byte i, 2i+1 = normalized byte i + T/2)
+template <int LM>
+__device__ __forceinline__ void unpack_low(const uint8_t *img_low, uint32_t B, uint32_t logC, uint32_t tid,
+                                           uint32_t (&LOW)[8][2])
+{
+    constexpr HHTable TL = HH<LM>::table;
+    uint32_t Pl[LM][2];
+    const uint32_t T2 = (LM * B) >> 4;
+#pragma unroll
+    for (int q = 0; q < LM; ++q) {
+        const uint32_t i = ((uint32_t)q << logC) + 8u * tid;
+        const bool even = i < T2;
+        const uint4 sp = *reinterpret_cast<const uint4 *>(img_low + 2u * (even ? i : i - T2));
+        const uint32_t sel = even ? 0x06040200u : 0x07050301u;
+        Pl[q][0] = byte_perm(sp.y, sp.x, sel);
+        Pl[q][1] = byte_perm(sp.w, sp.z, sel);
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) LOW[t][0] = LOW[t][1] = 0;
+#pragma unroll
+    for (int f = 0; f < TL.count; ++f) {
+        const uint32_t smask = (TL.shift[f] >= 0 ? (TL.dmask[f] >> TL.shift[f]) : (TL.dmask[f] << (-TL.shift[f]))) * 0x01010101u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) LOW[TL.row[f]][h] |= shl_or_shr(Pl[TL.plane[f]][h], -TL.shift[f]) & smask;
+    }
+}
+
+template <int A, int LPG>
+__device__ __forceinline__ void unpack_records(const uint8_t *img_high, uint32_t my_word, uint32_t my_excl,
+                                               uint32_t logC, uint32_t tid, uint32_t (&HI)[8][2])
+{
+#pragma unroll
+    for (int t = 0; t < 8; ++t) unpack_record_row<A, LPG>(img_high, my_word, my_excl, logC, tid, t, HI[t][0], HI[t][1]);
+}
+
+template <int DT, int LPG>
+__global__ void __launch_bounds__(512) decompress_kernel(const DecompressArgs p)
+{
+    constexpr uint32_t E = exponent_bits(DT);
+    constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
+    extern __shared__ __align__(16) uint8_t smem[];      // the packed part as it is in the stream
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t B = p.B, logC = p.logB - 3u;
+    const uint32_t nact = B >> 6, threads = nact < 64u ? 64u : nact;
+    const bool active = tid < nact;
+    const uint32_t mask_bytes = (B >> 6) >> LOG_LPG;                  // B / (8 L)
+    // the stream this block belongs to (the blocks of the launch's streams are numbered through; `first` of
+    // the entries that are not used is beyond every block)
+    uint32_t ti = 0;
+#pragma unroll
+    for (int i = 1; i < MAX_BATCH; ++i)
+        if (blockIdx.x >= p.first[i]) ti = i;
+    const DecompressItem &it = p.item[ti];
+    const uint32_t k = blockIdx.x - p.first[ti];
+
+    // d1: header as configured, tuple (in the tuple table, or in the header), offsets
+    const uint32_t *hd = reinterpret_cast<const uint32_t *>(it.in);
+    const uint64_t *table = reinterpret_cast<const uint64_t *>(it.in + 64);
+    const uint64_t t0 = table[k], t1 = table[k + 1];
+    const uint32_t tup = *reinterpret_cast<const uint32_t *>(it.in + it.tuples_at + (uint64_t)it.tuple_stride * k);
+    uint32_t differ = (hd[10] ^ it.hdr[10]) & (0u - (it.tuple_stride >> 2));     // byte 40 ff.: only with a tuple table
+#pragma unroll
+    for (int i = 0; i < 10; ++i) differ |= hd[i] ^ it.hdr[i];
+    const uint32_t b = tup & 0xFFu, n = (tup >> 8) & 0xFFu, m = (tup >> 16) & 0xFFu;
+    // a block that is skipped (damaged header, tuple or table entry) leaves its part of the output
+    // untouched: the caller is told through the status word
+    const uint32_t a = n - m, lm = m + (DT == DT_FP16 ? 3u : 0u);
+    const uint32_t fixed = B + mask_bytes + ((lm * B) >> 3);
+    const uint64_t sz = t1 - t0;
+    const uint64_t room = it.payload_bytes - t0;
+    if ((differ != 0) | (n < 1u) | (n > E) | (m > n) | (b >= (1u << E)) |
+        (sz < fixed) | (sz > fixed + (uint32_t)LPG * a * ((B >> 3) >> LOG_LPG) + 15u) | (((sz | t0) & 15u) != 0) |
+        (t0 > it.payload_bytes) | (sz > room)) {
+        if (tid == 0 && it.status) *it.status = 7u;
+        return;
+    }
+
+    // Everything the block needs is requested at once.  The packed part (mask | low plane | high records)
+    // goes from memory to LDS without passing through registers, 16 bytes per lane to the wave's base + 16
+    // lane; the sizes are whole 16-byte vectors.
+    const uint8_t *src = it.in + it.payload_base + t0;
+    const uint32_t nvec = ((uint32_t)sz - B) >> 4;
+    for (uint32_t v0 = __builtin_amdgcn_readfirstlane(tid & ~63u); v0 < nvec; v0 += threads)
+        if (v0 + lane < nvec) load_to_lds(src + B + 16u * (v0 + lane), smem + 16u * v0);
+    uint2 smv[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+        smv[t] = active ? ld_stream(reinterpret_cast<const uint2 *>(src + ((size_t)t << logC) + 8u * tid)) : make_uint2(0, 0);
+    // fp32: the lower halves of this thread's elements, straight from the stream (region padded to 16 bytes)
+    const uint64_t blk0 = (uint64_t)k << p.logB;
+    uint4 tl[DT == DT_FP32 ? 8 : 1];
+    if constexpr (DT == DT_FP32) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
+            tl[t] = active && e0 < it.n_elems ? ld_stream(reinterpret_cast<const uint4 *>(it.in + it.tail_base + 2u * e0))
+                                              : make_uint4(0, 0, 0, 0);
+        }
+    }
+    wait_loads();
+    __syncthreads();
+    if (!active) return;
+
+    // d2: mask words and their exclusive popcount prefix (a wave scan per wave)
+    const uint8_t *img_low = smem + mask_bytes;
+    const uint8_t *img_high = img_low + ((lm * B) >> 3);
+    const uint32_t nwords = (B >> 8) >> LOG_LPG;
+    const uint32_t my_word = lane < nwords ? reinterpret_cast<const uint32_t *>(smem)[lane] : 0u;
+    const uint32_t my_pc = __popc(my_word);
+    const uint32_t my_excl = wave_incl_scan(my_pc, lane) - my_pc;
+
+    // d3: low-plane values and high bits of the thread's 8 x 8 elements
+    uint32_t LOW[8][2], HI[8][2];
+    switch (lm) {
+    case 1: unpack_low<1>(img_low, B, logC, tid, LOW); break;
+    case 2: unpack_low<2>(img_low, B, logC, tid, LOW); break;
+    case 3: unpack_low<3>(img_low, B, logC, tid, LOW); break;
+    case 4: unpack_low<4>(img_low, B, logC, tid, LOW); break;
+    case 5: unpack_low<5>(img_low, B, logC, tid, LOW); break;
+    case 6: unpack_low<6>(img_low, B, logC, tid, LOW); break;
+    case 7: unpack_low<7>(img_low, B, logC, tid, LOW); break;
+    case 8: unpack_low<8>(img_low, B, logC, tid, LOW); break;
+    default:
+#pragma unroll
+        for (int t = 0; t < 8; ++t) LOW[t][0] = LOW[t][1] = 0;
+        break;
+    }
+    switch (a) {
+    case 1: unpack_records<1, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 2: unpack_records<2, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 3: unpack_records<3, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 4: unpack_records<4, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 5: unpack_records<5, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 6: unpack_records<6, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 7: unpack_records<7, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    case 8: unpack_records<8, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
+    default:
+#pragma unroll
+        for (int t = 0; t < 8; ++t) HI[t][0] = HI[t][1] = 0;
+        break;
+    }
+
+    const uint32_t crep = ((b + (1u << (n - 1))) & 0xFFu) * 0x01010101u;
+    const uint32_t srep = (1u << (n - 1)) * 0x01010101u;
+    const uint32_t lrep = ((1u << m) - 1u) * 0x01010101u;
+    const uint32_t erep = ((1u << E) - 1u) * 0x01010101u;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
+        uint32_t o[4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t Y = (LOW[t][h] & lrep) | (HI[t][h] << m);
+            // d4: x = b - sext_n(y) = (b + 2^(n-1)) - (y ^ 2^(n-1)), modulo the exponent field
+            const uint32_t Xv = bytesub_safe(crep, Y ^ srep) & erep;
+            const uint32_t sm = h ? smv[t].y : smv[t].x;
+            uint32_t Hi, Lo;
+            if constexpr (DT == DT_FP16) {
+                const uint32_t T3 = (LOW[t][h] >> m) & 0x07070707u;
+                Hi = (sm & 0x80808080u) | (Xv << 2) | ((sm >> 5) & 0x03030303u);
+                Lo = ((sm & 0x1F1F1F1Fu) << 3) | T3;
+            } else {
+                Hi = bfi(0x7F7F7F7Fu, Xv >> 1, sm);
+                Lo = bfi(0x7F7F7F7Fu, sm, Xv << 7);
+            }
+            o[2 * h] = byte_perm(Hi, Lo, 0x05010400u);
+            o[2 * h + 1] = byte_perm(Hi, Lo, 0x07030602u);
+        }
+        if constexpr (DT == DT_FP32) {
+            // element = lower half | bf16 word << 16
+            const uint32_t lo[4] = {tl[t].x, tl[t].y, tl[t].z, tl[t].w};
+            uint32_t w[8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                w[2 * i] = byte_perm(o[i], lo[i], 0x05040100u);
+                w[2 * i + 1] = byte_perm(o[i], lo[i], 0x07060302u);
+            }
+            uint32_t *out32 = reinterpret_cast<uint32_t *>(it.out);
+            if (e0 + 8 <= it.n_elems) {
+                st_stream(reinterpret_cast<uint4 *>(out32 + e0), make_uint4(w[0], w[1], w[2], w[3]));
+                st_stream(reinterpret_cast<uint4 *>(out32 + e0 + 4), make_uint4(w[4], w[5], w[6], w[7]));
+            } else if (e0 < it.n_elems) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (e0 + i < it.n_elems) out32[e0 + i] = w[i];
+            }
+        } else {
+            uint16_t *out16 = reinterpret_cast<uint16_t *>(it.out);
+            if (e0 + 8 <= it.n_elems) {
+                st_stream(reinterpret_cast<uint4 *>(out16 + e0), make_uint4(o[0], o[1], o[2], o[3]));
+            } else if (e0 < it.n_elems) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (e0 + i < it.n_elems) out16[e0 + i] = (uint16_t)(o[i >> 1] >> (16 * (i & 1)));
+            }
+        }
+    }
+}
+
+}  // namespace enec

@@ -136,6 +136,18 @@ __device__ __forceinline__ void st_stream(uint2 *p, uint2 v)
 {
     __builtin_nontemporal_store(vec2u{v.x, v.y}, reinterpret_cast<vec2u *>(p));
 }
+// 16 bytes per lane from memory to LDS without a register in between: lane i's bytes land at `lds` + 16 i
+// (`lds` is the same for the whole wave; lanes that are switched off move nothing).  Streaming, as above.
+__device__ __forceinline__ void load_to_lds(const uint8_t *p, uint8_t *lds)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)p,
+                                     (__attribute__((address_space(3))) void *)lds, 16, 0, 2 /* non-temporal */);
+}
+// all loads of this wave have arrived (in LDS too); a barrier after it makes them visible to the workgroup
+__device__ __forceinline__ void wait_loads()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
 
 __device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel)
 {
@@ -329,26 +341,6 @@ struct CompressArgs {
     uint32_t n_items;
     uint32_t spin_limit;    // polls of the scan state after which a workgroup gives up (status ENEC_E_HIP)
     CompressItem item[MAX_BATCH];
-};
-
-struct DecompressItem {
-    const uint8_t *in;
-    uint16_t *out;
-    uint64_t n_elems;
-    uint64_t payload_base;
-    uint64_t payload_bytes; // total_bytes - payload_base
-    uint64_t tail_base;     // fp32: where the lower halves of the elements are
-    uint32_t nb, first;
-    uint32_t b, mode;       // mode 0: plain byte subtract is exact; 1: borrow-safe subtract
-    uint32_t hdr[10];       // first 40 bytes of the expected header
-    uint32_t *status;       // device-accessible or null: set to 7 (format error) when a block is left undecoded
-};
-
-struct DecompressArgs {
-    uint32_t B, logB;
-    uint32_t total;
-    uint32_t n_items;
-    DecompressItem item[MAX_BATCH];
 };
 
 // ---------------------------------------------------------------------------------
@@ -1103,273 +1095,6 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
         }
         __syncthreads();
         store_block(p.item[pend_item], pend, pend_cnt, pend_S, smem + (slot ^ 1u) * img_bytes, pend_err);
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// decompression: offset lookup, mask prefix, unpack, inverse transform, recombine
-// (Sec. V-A decompression path; Alg. 1 decompression part)
-//
-// Persistent grid, block k handled by workgroup k mod gridDim (blocks are independent, so no
-// tickets are needed).  While block k is unpacked and stored, the payload of the workgroup's
-// next block is already travelling: its sign/mantissa bytes into registers, its packed part
-// (mask | low plane | high records, exactly as in the stream) into the other of two LDS images.
-// ---------------------------------------------------------------------------------
-template <int M, int A, int DT, int LPG>
-__global__ void __launch_bounds__(512) decompress_kernel(const DecompressArgs p)
-{
-    constexpr int N = M + A;
-    constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
-    constexpr uint32_t RB = A * LPG;                     // bytes of one high record: (n - m) L / 8
-    constexpr int LM = low_plane_bits(M, DT);            // width of the low plane
-    constexpr uint32_t SREP = (1u << (N - 1)) * 0x01010101u;
-    constexpr uint32_t LMASK = ((1u << M) - 1u) * 0x01010101u;
-    constexpr int MP = LM > 0 ? LM : 1;
-    constexpr int AP = A > 0 ? A : 1;
-    constexpr int VMAX = (LM + A) / 2 + 1;   // 16-byte vectors of packed payload per thread
-
-    extern __shared__ __align__(16) uint8_t smem[];
-
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const uint32_t B = p.B, logC = p.logB - 3u, C = 1u << logC;
-    const uint32_t nact = B >> 6;
-    const bool active = tid < nact;
-    const uint32_t mask_bytes = (B >> 6) >> LOG_LPG;                  // B / (8 L)
-    const uint32_t img_bytes = mask_bytes + (((uint32_t)(LM + A) * B) >> 3);
-    const uint32_t fixed = B + mask_bytes + ((LM * B) >> 3);
-
-    // tensor that global block kg belongs to, searching upwards from item c
-    auto item_of = [&](uint32_t kg, uint32_t c) -> uint32_t {
-        while (c + 1u < p.n_items && kg >= p.item[c + 1u].first) ++c;
-        return c;
-    };
-    // d1: the header in memory must be the one the launch was configured from (the host has
-    // checked that header and table lie inside the buffer); otherwise the tensor is not touched
-    uint32_t hdr_ok = 0, hdr_seen = 0;                       // one bit per item
-    auto header_matches = [&](uint32_t c) -> bool {
-        if (!((hdr_seen >> c) & 1u)) {
-            const uint32_t *h = reinterpret_cast<const uint32_t *>(p.item[c].in);
-            bool same = true;
-#pragma unroll
-            for (int i = 0; i < 10; ++i) same &= (h[i] == p.item[c].hdr[i]);
-            hdr_seen |= 1u << c;
-            if (same) hdr_ok |= 1u << c;
-        }
-        return (hdr_ok >> c) & 1u;
-    };
-    // d1: offset lookup, in two steps so that the loads can be issued well before they are used;
-    // a block whose table entries point outside the stream is skipped.  kg = global block index.
-    auto fetch = [&](uint32_t kg, uint32_t c, uint64_t &t0, uint64_t &t1) {
-        if (kg < p.total) {
-            const uint64_t *table = reinterpret_cast<const uint64_t *>(p.item[c].in + 64);
-            const uint32_t kb = kg - p.item[c].first;
-            t0 = table[kb];
-            t1 = table[kb + 1];
-        }
-    };
-    auto check = [&](uint32_t kg, uint32_t c, uint64_t t0, uint64_t t1, uint64_t &off, uint32_t &size) -> bool {
-        if (kg >= p.total) return false;
-        const uint64_t sz = t1 - t0;
-        off = t0;
-        size = (uint32_t)sz;
-        return header_matches(c) &&
-               !(sz < fixed || sz > fixed + RB * ((B >> 3) >> LOG_LPG) + 15u || (sz & 15u) || t0 > p.item[c].payload_bytes ||
-                 sz > p.item[c].payload_bytes - t0);
-    };
-    // issue the loads of one block: sign/mantissa rows and the packed part
-    auto issue = [&](uint32_t c, uint64_t off, uint32_t size, uint2 (&smv)[8], uint4 (&vec)[VMAX]) {
-        const uint8_t *src = p.item[c].in + p.item[c].payload_base + off;
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-            smv[t] = active ? ld_stream(reinterpret_cast<const uint2 *>(src + ((size_t)t << logC) + 8u * tid)) : make_uint2(0, 0);
-        const uint32_t nvec = (size - B) >> 4;
-#pragma unroll
-        for (int i = 0; i < VMAX; ++i) {
-            const uint32_t v = tid + (uint32_t)i * blockDim.x;
-            vec[i] = v < nvec ? ld_stream(reinterpret_cast<const uint4 *>(src + B + 16u * v)) : make_uint4(0, 0, 0, 0);
-        }
-    };
-    auto to_image = [&](uint8_t *img, const uint4 (&vec)[VMAX]) {
-#pragma unroll
-        for (int i = 0; i < VMAX; ++i) {
-            const uint32_t v = tid + (uint32_t)i * blockDim.x;
-            if (16u * v < img_bytes) *reinterpret_cast<uint4 *>(img + 16u * v) = vec[i];
-        }
-    };
-
-    uint32_t k = blockIdx.x;                                // global block index
-    if (k >= p.total) return;
-    // A block that fails these tests is skipped and its part of the output stays as it was.  For the
-    // tensors that come with a status word, the last workgroup looks at the header and at every table
-    // entry once more before its own work and tells the caller if any block will be skipped.  (Done
-    // here, outside the loop below: a store inside that loop cost 5 % of the kernel's time.)
-    if (blockIdx.x == gridDim.x - 1u) {
-        for (uint32_t c = 0; c < p.n_items; ++c) {
-            if (!p.item[c].status) continue;
-            const uint64_t *table = reinterpret_cast<const uint64_t *>(p.item[c].in + 64);
-            bool bad = !header_matches(c);
-            for (uint32_t e = tid; e < p.item[c].nb && !bad; e += blockDim.x) {
-                const uint64_t t0 = table[e], sz = table[e + 1] - t0;
-                bad = sz < fixed || sz > fixed + RB * ((B >> 3) >> LOG_LPG) + 15u || (sz & 15u) || t0 > p.item[c].payload_bytes ||
-                      sz > p.item[c].payload_bytes - t0;
-            }
-            if (bad) *p.item[c].status = 7u;
-        }
-    }
-    uint32_t ci = item_of(k, 0);
-    uint32_t cn = item_of(k + gridDim.x, ci);               // item of the next block (if there is one)
-    uint64_t off = 0, offn = 0;
-    uint32_t size = 0, sizen = 0;
-    uint64_t ta = 0, tb = 0, tc = 0, td = 0;
-    fetch(k, ci, ta, tb);
-    fetch(k + gridDim.x, cn, tc, td);                       // the table is read one block ahead
-    bool valid = check(k, ci, ta, tb, off, size);
-    bool validn = check(k + gridDim.x, cn, tc, td, offn, sizen);
-    uint2 smc[8], smn[8];
-    uint4 vec[VMAX];
-    if (valid) {
-        issue(ci, off, size, smc, vec);
-        to_image(smem, vec);
-    }
-    uint32_t slot = 0;
-    constexpr HHTable TL = HH<MP>::table;
-
-    while (k < p.total) {
-        __syncthreads();            // image[slot] is complete, image[slot ^ 1] is free
-        // the next block's loads start now and are consumed at the end of the iteration
-        const uint32_t kn = k + gridDim.x;
-        if (validn) issue(cn, offn, sizen, smn, vec);
-        const uint32_t c2 = item_of(kn + gridDim.x, cn);
-        fetch(kn + gridDim.x, c2, ta, tb);
-        const DecompressItem &it = p.item[ci];
-        const uint32_t crep = ((it.b + (1u << (N - 1))) & 0xFFu) * 0x01010101u;
-
-        if (valid && active) {
-            const uint8_t *img = smem + slot * img_bytes;
-            const uint8_t *img_low = img + mask_bytes;
-            const uint8_t *img_high = img_low + (((size_t)LM * B) >> 3);
-            const uint64_t blk0 = (uint64_t)(k - it.first) << p.logB;
-            // fp32: the lower halves of this thread's elements, straight from the stream
-            uint4 tl[DT == DT_FP32 ? 8 : 1];
-            if constexpr (DT == DT_FP32) {
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
-                    tl[t] = e0 < it.n_elems ? ld_stream(reinterpret_cast<const uint4 *>(it.in + it.tail_base + 2u * e0))
-                                            : make_uint4(0, 0, 0, 0);
-                }
-            }
-            // d2: mask words and their exclusive popcount prefix (a wave scan per wave)
-            const uint32_t nwords = (B >> 8) >> LOG_LPG;
-            const uint32_t my_word = lane < nwords ? reinterpret_cast<const uint32_t *>(img)[lane] : 0u;
-            const uint32_t my_pc = __popc(my_word);
-            const uint32_t my_excl = wave_incl_scan(my_pc, lane) - my_pc;
-
-            // low plane: the 8 normalized bytes of plane q for this thread's columns are every
-            // other byte of one 16-byte span of the stream (undoing the final join of Alg. 2)
-            uint32_t Pl[MP][2];
-#pragma unroll
-            for (int q = 0; q < MP; ++q) {
-                if (LM > 0) {
-                    const uint32_t T2 = (LM * B) >> 4;
-                    const uint32_t i = ((uint32_t)q << logC) + 8u * tid;
-                    const bool even = i < T2;
-                    const uint4 sp = *reinterpret_cast<const uint4 *>(img_low + 2u * (even ? i : i - T2));
-                    const uint32_t sel = even ? 0x06040200u : 0x07050301u;
-                    Pl[q][0] = byte_perm(sp.y, sp.x, sel);
-                    Pl[q][1] = byte_perm(sp.w, sp.z, sel);
-                } else {
-                    Pl[q][0] = Pl[q][1] = 0;
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                uint32_t Y[2] = {0u, 0u}, T3[2] = {0u, 0u};
-                // d3: low-plane values of the 8 columns of this row: the low m bits of y (fp16:
-                // with the last three mantissa bits on top)
-                if (LM > 0) {
-#pragma unroll
-                    for (int f = 0; f < TL.count; ++f)
-                        if (TL.row[f] == t) {
-                            const uint32_t smask = (TL.shift[f] >= 0 ? (TL.dmask[f] >> TL.shift[f])
-                                                                    : (TL.dmask[f] << (-TL.shift[f]))) * 0x01010101u;
-#pragma unroll
-                            for (int h = 0; h < 2; ++h)
-                                Y[h] |= shl_or_shr(Pl[TL.plane[f]][h], -TL.shift[f]) & smask;
-                        }
-                    if constexpr (DT == DT_FP16) {
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            T3[h] = (Y[h] >> M) & 0x07070707u;
-                            Y[h] &= LMASK;
-                        }
-                    }
-                }
-                // d2/d3: high bits of masked groups, found through the mask prefix
-                if constexpr (A > 0) {
-                    uint32_t h0, h1;
-                    unpack_record_row<A, LPG>(img_high, my_word, my_excl, logC, tid, t, h0, h1);
-                    Y[0] |= h0 << M;
-                    Y[1] |= h1 << M;
-                }
-                // d4: x = b - sext_n(y) = (b + 2^(n-1)) - (y ^ 2^(n-1)); recombine with sign/mantissa
-                uint32_t o[4];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t Z = Y[h] ^ SREP;
-                    const uint32_t X = it.mode == 0 ? crep - Z : bytesub_safe(crep, Z);
-                    const uint32_t sm = h ? smc[t].y : smc[t].x;
-                    uint32_t Hi, Lo;         // high / low bytes of four 16-bit words
-                    if constexpr (DT == DT_FP16) {
-                        Hi = (sm & 0x80808080u) | ((X & 0x1F1F1F1Fu) << 2) | ((sm >> 5) & 0x03030303u);
-                        Lo = ((sm & 0x1F1F1F1Fu) << 3) | T3[h];
-                    } else {
-                        Hi = bfi(0x7F7F7F7Fu, X >> 1, sm);
-                        Lo = bfi(0x7F7F7F7Fu, sm, X << 7);
-                    }
-                    o[2 * h] = byte_perm(Hi, Lo, 0x05010400u);
-                    o[2 * h + 1] = byte_perm(Hi, Lo, 0x07030602u);
-                }
-                const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
-                if constexpr (DT == DT_FP32) {
-                    // element = lower half | bf16 word << 16
-                    const uint32_t lo[4] = {tl[t].x, tl[t].y, tl[t].z, tl[t].w};
-                    uint32_t w[8];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        w[2 * i] = byte_perm(o[i], lo[i], 0x05040100u);
-                        w[2 * i + 1] = byte_perm(o[i], lo[i], 0x07060302u);
-                    }
-                    uint32_t *out32 = reinterpret_cast<uint32_t *>(it.out);
-                    if (e0 + 8 <= it.n_elems) {
-                        st_stream(reinterpret_cast<uint4 *>(out32 + e0), make_uint4(w[0], w[1], w[2], w[3]));
-                        st_stream(reinterpret_cast<uint4 *>(out32 + e0 + 4), make_uint4(w[4], w[5], w[6], w[7]));
-                    } else if (e0 < it.n_elems) {
-#pragma unroll
-                        for (int i = 0; i < 8; ++i)
-                            if (e0 + i < it.n_elems) out32[e0 + i] = w[i];
-                    }
-                } else if (e0 + 8 <= it.n_elems) {
-                    st_stream(reinterpret_cast<uint4 *>(it.out + e0), make_uint4(o[0], o[1], o[2], o[3]));
-                } else if (e0 < it.n_elems) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        if (e0 + i < it.n_elems) it.out[e0 + i] = (uint16_t)(o[i >> 1] >> (16 * (i & 1)));
-                }
-            }
-        }
-        // the next block's packed part goes to the other image
-        if (validn) {
-            to_image(smem + (slot ^ 1u) * img_bytes, vec);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) smc[t] = smn[t];
-        }
-        valid = validn;
-        validn = check(kn + gridDim.x, c2, ta, tb, offn, sizen);
-        k = kn;
-        ci = cn;
-        cn = c2;
-        slot ^= 1u;
     }
 }
 

@@ -1,30 +1,49 @@
-// Kernel tables of libenec: one function per element format, group length and direction that maps
-// a tuple (m, a = n - m) to the kernel instance built for it (nullptr if there is none).  Each of
-// the 18 tables is compiled as a translation unit of its own (enec_kernels.hip with
-// -DENEC_DT=<format 0|1|2> -DENEC_LPG=<lanes per group 1|2|4> -DENEC_DIR=<0 compress | 1 decompress>)
-// so that the build runs in parallel.
+// Kernel tables of libenec.  Compression with one tuple per tensor has one function per element format and
+// group length that maps a tuple (m, a = n - m) to the kernel instance built for it (nullptr if there is
+// none); each of the nine is compiled as a translation unit of its own (enec_kernels.hip with
+// -DENEC_DT=<format 0|1|2> -DENEC_LPG=<lanes per group 1|2|4>) so that the build runs in parallel.
+// The other kernels know the widths at run time only and exist once per element format and group length.
 #pragma once
 #include "enec_device.hpp"
 
 namespace enec {
 
 using CompressFn = void (*)(const CompressArgs);
-using DecompressFn = void (*)(const DecompressArgs);
 
 #define ENEC_TABLES(dt)                               \
     CompressFn pick_compress_##dt##_lpg1(int m, int a);   \
     CompressFn pick_compress_##dt##_lpg2(int m, int a);   \
-    CompressFn pick_compress_##dt##_lpg4(int m, int a);   \
-    DecompressFn pick_decompress_##dt##_lpg1(int m, int a); \
-    DecompressFn pick_decompress_##dt##_lpg2(int m, int a); \
-    DecompressFn pick_decompress_##dt##_lpg4(int m, int a);
+    CompressFn pick_compress_##dt##_lpg4(int m, int a);
 ENEC_TABLES(dt0)
 ENEC_TABLES(dt1)
 ENEC_TABLES(dt2)
 #undef ENEC_TABLES
 
-// Streams with one tuple per data block (enec_per_block.hpp, compiled in enec_per_block.hip): the
-// widths are run-time values there, one kernel per element format, group length and direction.
+// Decompression (enec_decompress.hpp, compiled in enec_decompress.hip).  One launch takes up to MAX_BATCH
+// streams of one element format, group length and block size, whatever their tuples.
+struct DecompressItem {
+    const uint8_t *in;
+    void *out;
+    uint64_t n_elems;
+    uint64_t tuples_at;         // byte offset in the stream of the first block's tuple: the tuple table, or header byte 24
+    uint64_t tail_base;         // fp32: where the lower halves of the elements are
+    uint64_t payload_base;
+    uint64_t payload_bytes;     // total_bytes - payload_base
+    uint32_t *status;           // device-accessible or null: set to 7 (format error) when a block is left undecoded
+    uint32_t tuple_stride;      // bytes from a block's tuple to the next one's: 4, or 0 if one tuple holds for all
+    uint32_t hdr[11];           // the header the launch was configured from
+};
+
+struct DecompressArgs {
+    uint32_t first[MAX_BATCH];  // number of each stream's first data block among the blocks of the launch
+    uint32_t B, logB;
+    DecompressItem item[MAX_BATCH];
+};
+
+using DecompressFn = void (*)(const DecompressArgs);
+DecompressFn pick_decompress(int dtype, unsigned L);
+
+// Compression with one tuple per data block (enec_per_block.hpp, compiled in enec_per_block.hip).
 // LDS copies of the block histogram in the compress kernel, and their distance in words
 constexpr uint32_t PB_HIST_COPIES = 16, PB_HIST_STRIDE = 257;   // words; 16 * 257 * 4 bytes of LDS
 
@@ -56,26 +75,7 @@ struct PbCompressArgs {
 };
 constexpr int PB_SM_REG_ROWS = 4;               // rows of a thread's raw bytes kept in registers; the other rows wait in LDS
 
-struct PbDecompressItem {       // one stream of a launch
-    const uint8_t *in;
-    void *out;
-    uint64_t n_elems;
-    uint64_t tuples_at, tail_base, payload_base, payload_bytes;
-    uint32_t nb;
-    uint32_t first;             // number of its first data block among the blocks of the launch
-    uint32_t *status;           // device-accessible or null: set to 7 (format error) when a block is left undecoded
-    uint32_t hdr[11];           // the header the launch was configured from
-};
-
-struct PbDecompressArgs {
-    PbDecompressItem item[MAX_BATCH];
-    uint32_t n_items, n_blocks;
-    uint32_t B, logB;
-};
-
 using PbCompressFn = void (*)(const PbCompressArgs);
-using PbDecompressFn = void (*)(const PbDecompressArgs);
 PbCompressFn pick_compress_per_block(int dtype, unsigned L);
-PbDecompressFn pick_decompress_per_block(int dtype, unsigned L);
 
 }  // namespace enec

@@ -20,45 +20,6 @@ constexpr uint64_t PB_GAVE_UP = 1ull << 61;    // somebody before (or this block
 constexpr uint64_t PB_VALUE = (1ull << 61) - 1;
 constexpr int PB_WINDOW = 256;                  // blocks one look-back step covers (4 words per lane)
 
-// the inverse: plane values of the thread's 8 rows from the stream's low plane (already joined
-// pairwise by Alg. 2's last step: stream byte 2i = normalized byte i, 2i+1 = normalized byte i + T/2)
-template <int LM>
-__device__ __forceinline__ void pb_unpack_low(const uint8_t *img_low, uint32_t B, uint32_t logC, uint32_t tid,
-                                              uint32_t (&LOW)[8][2])
-{
-    constexpr HHTable TL = HH<LM>::table;
-    uint32_t Pl[LM][2];
-    const uint32_t T2 = (LM * B) >> 4;
-#pragma unroll
-    for (int q = 0; q < LM; ++q) {
-        const uint32_t i = ((uint32_t)q << logC) + 8u * tid;
-        const bool even = i < T2;
-        const uint4 sp = *reinterpret_cast<const uint4 *>(img_low + 2u * (even ? i : i - T2));
-        const uint32_t sel = even ? 0x06040200u : 0x07050301u;
-        Pl[q][0] = byte_perm(sp.y, sp.x, sel);
-        Pl[q][1] = byte_perm(sp.w, sp.z, sel);
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) LOW[t][0] = LOW[t][1] = 0;
-#pragma unroll
-    for (int f = 0; f < TL.count; ++f) {
-        const uint32_t smask = (TL.shift[f] >= 0 ? (TL.dmask[f] >> TL.shift[f]) : (TL.dmask[f] << (-TL.shift[f]))) * 0x01010101u;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) LOW[TL.row[f]][h] |= shl_or_shr(Pl[TL.plane[f]][h], -TL.shift[f]) & smask;
-    }
-}
-
-// The records of the masked groups are packed and unpacked by pack_records / unpack_record_row of
-// enec_device.hpp, the functions the kernels for one tuple per tensor use.
-template <int A, int LPG>
-__device__ __forceinline__ void pb_unpack_records(const uint8_t *img_high, uint32_t my_word, uint32_t my_excl,
-                                                  uint32_t logC, uint32_t tid, uint32_t (&HI)[8][2])
-{
-#pragma unroll
-    for (int t = 0; t < 8; ++t) unpack_record_row<A, LPG>(img_high, my_word, my_excl, logC, tid, t, HI[t][0], HI[t][1]);
-}
-
-
 // Eq. 1: bits needed for the window [l, h] around b, capped by the exponent field
 __device__ __forceinline__ uint32_t pb_width_for(uint32_t b, uint32_t l, uint32_t h, uint32_t E)
 {
@@ -651,156 +612,6 @@ compress_per_block_kernel(const PbCompressArgs p)
 #pragma unroll
             for (int i = 11; i < 16; ++i) h[i] = 0;
             if (it.out_bytes) *it.out_bytes = total;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// decompression of such a stream: one workgroup per data block; tuple and offsets come from the
-// stream, every size is checked against the tuple before anything is read or written
-// ---------------------------------------------------------------------------------
-template <int DT, int LPG>
-__global__ void __launch_bounds__(512) decompress_per_block_kernel(const PbDecompressArgs p)
-{
-    constexpr uint32_t E = exponent_bits(DT);
-    constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
-    extern __shared__ __align__(16) uint8_t smem[];      // the packed part as it is in the stream
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const uint32_t B = p.B, logC = p.logB - 3u;
-    const uint32_t nact = B >> 6;
-    const bool active = tid < nact;
-    const uint32_t mask_bytes = (B >> 6) >> LOG_LPG;                  // B / (8 L)
-    // the stream this block belongs to (the blocks of the launch's streams are numbered through)
-    if (blockIdx.x >= p.n_blocks) return;
-    uint32_t ti = 0;
-    for (uint32_t i = 1; i < p.n_items; ++i)
-        if (blockIdx.x >= p.item[i].first) ti = i;
-    const PbDecompressItem &it = p.item[ti];
-    const uint32_t k = blockIdx.x - it.first;
-
-    // d1: header as configured, tuple, offsets
-    const uint32_t *hd = reinterpret_cast<const uint32_t *>(it.in);
-    bool same = true;
-#pragma unroll
-    for (int i = 0; i < 11; ++i) same &= (hd[i] == it.hdr[i]);
-    const uint32_t tup = *reinterpret_cast<const uint32_t *>(it.in + it.tuples_at + 4u * k);
-    const uint32_t b = tup & 0xFFu, n = (tup >> 8) & 0xFFu, m = (tup >> 16) & 0xFFu;
-    const uint64_t *table = reinterpret_cast<const uint64_t *>(it.in + 64);
-    const uint64_t t0 = table[k], t1 = table[k + 1];
-    // a block that is skipped (damaged header, tuple or table entry) leaves its part of the output
-    // untouched: the caller is told through the status word
-    const uint32_t a = n - m, lm = m + (DT == DT_FP16 ? 3u : 0u);
-    const uint32_t fixed = B + mask_bytes + ((lm * B) >> 3);
-    const uint64_t sz = t1 - t0;
-    if (!same || n < 1u || n > E || m > n || b >= (1u << E) ||
-        sz < fixed || sz > fixed + (uint32_t)LPG * a * ((B >> 3) >> LOG_LPG) + 15u || ((sz | t0) & 15u) || t0 > it.payload_bytes || sz > it.payload_bytes - t0) {
-        if (tid == 0 && it.status) *it.status = 7u;
-        return;
-    }
-    const uint8_t *src = it.in + it.payload_base + t0;
-    const uint32_t nvec = ((uint32_t)sz - B) >> 4;
-    for (uint32_t v = tid; v < nvec; v += blockDim.x)
-        *reinterpret_cast<uint4 *>(smem + 16u * v) = ld_stream(reinterpret_cast<const uint4 *>(src + B + 16u * v));
-    uint2 smv[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-        smv[t] = active ? ld_stream(reinterpret_cast<const uint2 *>(src + ((size_t)t << logC) + 8u * tid)) : make_uint2(0, 0);
-    __syncthreads();
-    if (!active) return;
-
-    const uint8_t *img_low = smem + mask_bytes;
-    const uint8_t *img_high = img_low + ((lm * B) >> 3);
-    const uint32_t nwords = (B >> 8) >> LOG_LPG;
-    const uint32_t my_word = lane < nwords ? reinterpret_cast<const uint32_t *>(smem)[lane] : 0u;
-    const uint32_t my_pc = __popc(my_word);
-    const uint32_t my_excl = wave_incl_scan(my_pc, lane) - my_pc;
-
-    uint32_t LOW[8][2], HI[8][2];
-    switch (lm) {
-    case 1: pb_unpack_low<1>(img_low, B, logC, tid, LOW); break;
-    case 2: pb_unpack_low<2>(img_low, B, logC, tid, LOW); break;
-    case 3: pb_unpack_low<3>(img_low, B, logC, tid, LOW); break;
-    case 4: pb_unpack_low<4>(img_low, B, logC, tid, LOW); break;
-    case 5: pb_unpack_low<5>(img_low, B, logC, tid, LOW); break;
-    case 6: pb_unpack_low<6>(img_low, B, logC, tid, LOW); break;
-    case 7: pb_unpack_low<7>(img_low, B, logC, tid, LOW); break;
-    case 8: pb_unpack_low<8>(img_low, B, logC, tid, LOW); break;
-    default:
-#pragma unroll
-        for (int t = 0; t < 8; ++t) LOW[t][0] = LOW[t][1] = 0;
-        break;
-    }
-    switch (a) {
-    case 1: pb_unpack_records<1, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 2: pb_unpack_records<2, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 3: pb_unpack_records<3, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 4: pb_unpack_records<4, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 5: pb_unpack_records<5, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 6: pb_unpack_records<6, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 7: pb_unpack_records<7, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    case 8: pb_unpack_records<8, LPG>(img_high, my_word, my_excl, logC, tid, HI); break;
-    default:
-#pragma unroll
-        for (int t = 0; t < 8; ++t) HI[t][0] = HI[t][1] = 0;
-        break;
-    }
-
-    const uint32_t crep = ((b + (1u << (n - 1))) & 0xFFu) * 0x01010101u;
-    const uint32_t srep = (1u << (n - 1)) * 0x01010101u;
-    const uint32_t lrep = ((1u << m) - 1u) * 0x01010101u;
-    const uint32_t erep = ((1u << E) - 1u) * 0x01010101u;
-    const uint64_t blk0 = (uint64_t)k << p.logB;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
-        uint32_t o[4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t Y = (LOW[t][h] & lrep) | (HI[t][h] << m);
-            // d4: x = b - sext_n(y) = (b + 2^(n-1)) - (y ^ 2^(n-1)), modulo the exponent field
-            const uint32_t Xv = bytesub_safe(crep, Y ^ srep) & erep;
-            const uint32_t sm = h ? smv[t].y : smv[t].x;
-            uint32_t Hi, Lo;
-            if constexpr (DT == DT_FP16) {
-                const uint32_t T3 = (LOW[t][h] >> m) & 0x07070707u;
-                Hi = (sm & 0x80808080u) | (Xv << 2) | ((sm >> 5) & 0x03030303u);
-                Lo = ((sm & 0x1F1F1F1Fu) << 3) | T3;
-            } else {
-                Hi = bfi(0x7F7F7F7Fu, Xv >> 1, sm);
-                Lo = bfi(0x7F7F7F7Fu, sm, Xv << 7);
-            }
-            o[2 * h] = byte_perm(Hi, Lo, 0x05010400u);
-            o[2 * h + 1] = byte_perm(Hi, Lo, 0x07030602u);
-        }
-        if constexpr (DT == DT_FP32) {
-            if (e0 < it.n_elems) {
-                const uint4 tl = ld_stream(reinterpret_cast<const uint4 *>(it.in + it.tail_base + 2u * e0));   // region padded to 16 bytes
-                const uint32_t lo[4] = {tl.x, tl.y, tl.z, tl.w};
-                uint32_t w[8];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    w[2 * i] = byte_perm(o[i], lo[i], 0x05040100u);
-                    w[2 * i + 1] = byte_perm(o[i], lo[i], 0x07060302u);
-                }
-                uint32_t *out32 = reinterpret_cast<uint32_t *>(it.out);
-                if (e0 + 8 <= it.n_elems) {
-                    st_stream(reinterpret_cast<uint4 *>(out32 + e0), make_uint4(w[0], w[1], w[2], w[3]));
-                    st_stream(reinterpret_cast<uint4 *>(out32 + e0 + 4), make_uint4(w[4], w[5], w[6], w[7]));
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        if (e0 + i < it.n_elems) out32[e0 + i] = w[i];
-                }
-            }
-        } else {
-            uint16_t *out16 = reinterpret_cast<uint16_t *>(it.out);
-            if (e0 + 8 <= it.n_elems) {
-                st_stream(reinterpret_cast<uint4 *>(out16 + e0), make_uint4(o[0], o[1], o[2], o[3]));
-            } else if (e0 < it.n_elems) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (e0 + i < it.n_elems) out16[e0 + i] = (uint16_t)(o[i >> 1] >> (16 * (i & 1)));
-            }
         }
     }
 }
