@@ -810,7 +810,9 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
         DecompressFn fn = pick_decompress(h0.dtype, h0.prm.L);
         if (!fn) return ENEC_E_FORMAT;
         // the packed part of the widest block of the launch: mask | low plane | high records | padding
-        const size_t lds = (size_t)h0.B / (8 * h0.prm.L) + (size_t)widest * h0.B / 8 + 16;
+        const size_t packed = (size_t)h0.B / (8 * h0.prm.L) + (size_t)widest * h0.B / 8 + 16;
+        const size_t lds = packed + (h0.dtype == ENEC_FP32 ? 16 * threads : 0);
+        a.turn_at = (uint32_t)packed;
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(threads), lds, s, a);
     }
     return hipGetLastError() == hipSuccess ? ENEC_OK : ENEC_E_HIP;

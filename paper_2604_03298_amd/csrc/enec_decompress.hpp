@@ -5,8 +5,10 @@
 // independent, and a workgroup that starts when another ends keeps the accesses of the device in stream
 // order.  A kernel that only moves the bytes of a block (24.8 KB in, 32 KB out) reaches 5.9 TB/s that way
 // and 5.75 with a persistent grid and the next block prefetched, which this kernel replaced.  What a
-// block waits for (table entry, then its payload) is hidden by the other seven workgroups of the CU: 64
-// registers and at most B + B / (8 L) bytes of LDS let eight share it.
+// block waits for (table entry, then its payload) is hidden by the other workgroups of the CU.  Four share
+// it: the registers and the LDS would let eight, but then more of the device's accesses are in flight than
+// its memory likes (405 MB layer: 124.7 us with eight, 123.2 with five, 120.0 with four, 121.2 with three;
+// 470 MB matrices 273.8, 270.1, 271.9, 268.5).
 //
 // The widths (m, n) are run-time values, uniform over the workgroup: the unpackers are reached through a
 // switch over eight low-plane widths and eight record widths.  So the streams of a call that differ only in
@@ -53,8 +55,12 @@ __device__ __forceinline__ void unpack_records(const uint8_t *img_high, uint32_t
     for (int t = 0; t < 8; ++t) unpack_record_row<A, LPG>(img_high, my_word, my_excl, logC, tid, t, HI[t][0], HI[t][1]);
 }
 
+// workgroups of four waves per CU: four, and three for fp32, whose blocks are 115 KB of traffic and need the
+// registers (45e6 elements: 66.8 us with four, four registers spilled; 61.1 with three; 66.6 with two)
+#define DEC_WAVES (DT == DT_FP32 ? 3 : 4)
+
 template <int DT, int LPG>
-__global__ void __launch_bounds__(512) decompress_kernel(const DecompressArgs p)
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WAVES, DEC_WAVES))) decompress_kernel(const DecompressArgs p)
 {
     constexpr uint32_t E = exponent_bits(DT);
     constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
@@ -106,20 +112,26 @@ __global__ void __launch_bounds__(512) decompress_kernel(const DecompressArgs p)
 #pragma unroll
     for (int t = 0; t < 8; ++t)
         smv[t] = active ? ld_stream(reinterpret_cast<const uint2 *>(src + ((size_t)t << logC) + 8u * tid)) : make_uint2(0, 0);
-    // fp32: the lower halves of this thread's elements, straight from the stream (region padded to 16 bytes)
+    // fp32: lower halves, straight from the stream (region padded to 16 bytes).  A wave's 512 elements of a row
+    // are 2 KB of output.  Stored by the threads that unpack them, 2 x 16 bytes per lane, every streaming store
+    // would write half of each 128-byte line it touches, which a plain copy shows at 3.4 instead of 6.0 TB/s.  So
+    // the upper halves change lanes through LDS, and lane i stores elements 4 i .. 4 i + 3 of the first, then of
+    // the second 256 elements; it loads the lower halves of those.
     const uint64_t blk0 = (uint64_t)k << p.logB;
-    uint4 tl[DT == DT_FP32 ? 8 : 1];
+    uint2 tl[DT == DT_FP32 ? 16 : 1];
+    const uint32_t col4 = 8u * (tid & ~63u) + 4u * lane;                  // its column in the first of the two
     if constexpr (DT == DT_FP32) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
-            tl[t] = active && e0 < it.n_elems ? ld_stream(reinterpret_cast<const uint4 *>(it.in + it.tail_base + 2u * e0))
-                                              : make_uint4(0, 0, 0, 0);
+        for (int t = 0; t < 16; ++t) {
+            const uint32_t c = col4 + 256u * (t & 1);
+            const uint64_t e = blk0 + ((uint64_t)(t >> 1) << logC) + c;
+            tl[t] = c < (1u << logC) && e < it.n_elems ? ld_stream(reinterpret_cast<const uint2 *>(it.in + it.tail_base + 2u * e))
+                                                       : make_uint2(0, 0);
         }
     }
     wait_loads();
     __syncthreads();
-    if (!active) return;
+    if (DT != DT_FP32 && !active) return;
 
     // d2: mask words and their exclusive popcount prefix (a wave scan per wave)
     const uint8_t *img_low = smem + mask_bytes;
@@ -187,23 +199,31 @@ __global__ void __launch_bounds__(512) decompress_kernel(const DecompressArgs p)
             o[2 * h + 1] = byte_perm(Hi, Lo, 0x07030602u);
         }
         if constexpr (DT == DT_FP32) {
-            // element = lower half | bf16 word << 16
-            const uint32_t lo[4] = {tl[t].x, tl[t].y, tl[t].z, tl[t].w};
-            uint32_t w[8];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                w[2 * i] = byte_perm(o[i], lo[i], 0x05040100u);
-                w[2 * i + 1] = byte_perm(o[i], lo[i], 0x07060302u);
-            }
+            // the wave's 1 KB of upper halves in element order (a wave's LDS accesses are executed in order, the
+            // kilobyte is its own)
+            uint8_t *turn = smem + p.turn_at + 16u * (tid & ~63u);
+            *reinterpret_cast<uint4 *>(turn + 16u * lane) = make_uint4(o[0], o[1], o[2], o[3]);
+            __builtin_amdgcn_wave_barrier();
             uint32_t *out32 = reinterpret_cast<uint32_t *>(it.out);
-            if (e0 + 8 <= it.n_elems) {
-                st_stream(reinterpret_cast<uint4 *>(out32 + e0), make_uint4(w[0], w[1], w[2], w[3]));
-                st_stream(reinterpret_cast<uint4 *>(out32 + e0 + 4), make_uint4(w[4], w[5], w[6], w[7]));
-            } else if (e0 < it.n_elems) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (e0 + i < it.n_elems) out32[e0 + i] = w[i];
+            for (int i = 0; i < 2; ++i) {
+                const uint2 up = *reinterpret_cast<const uint2 *>(turn + 512u * i + 8u * lane), lo = tl[2 * t + i];
+                const uint32_t c = col4 + 256u * i;
+                const uint64_t e = blk0 + ((uint64_t)t << logC) + c;
+                // element = lower half | bf16 word << 16
+                const uint32_t w[4] = {byte_perm(up.x, lo.x, 0x05040100u), byte_perm(up.x, lo.x, 0x07060302u),
+                                       byte_perm(up.y, lo.y, 0x05040100u), byte_perm(up.y, lo.y, 0x07060302u)};
+                if (c < (1u << logC)) {
+                    if (e + 4 <= it.n_elems) {
+                        st_stream(reinterpret_cast<uint4 *>(out32 + e), make_uint4(w[0], w[1], w[2], w[3]));
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (e + j < it.n_elems) out32[e + j] = w[j];
+                    }
+                }
             }
+            __builtin_amdgcn_wave_barrier();
         } else {
             uint16_t *out16 = reinterpret_cast<uint16_t *>(it.out);
             if (e0 + 8 <= it.n_elems) {

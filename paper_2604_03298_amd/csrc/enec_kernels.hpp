@@ -37,6 +37,7 @@ struct DecompressItem {
 struct DecompressArgs {
     uint32_t first[MAX_BATCH];  // number of each stream's first data block among the blocks of the launch
     uint32_t B, logB;
+    uint32_t turn_at;           // fp32: byte offset in the dynamic LDS where upper halves change lanes (behind the packed part)
     DecompressItem item[MAX_BATCH];
 };
 
