@@ -80,9 +80,9 @@ inline size_t tuple_table_bytes(size_t n, uint32_t B) { return align16(4 * num_b
 
 inline bool group_ok(unsigned L) { return L == 8 || L == 16 || L == 32; }
 
-inline CompressFn pick_compress(int m, int a, int dtype, unsigned L)
+inline CompressFn pick_compress(int m, int a, int dtype, unsigned L, uint32_t B)
 {
-#define ENEC_ROW(dt) (L == 8 ? pick_compress_##dt##_lpg1(m, a) : L == 16 ? pick_compress_##dt##_lpg2(m, a) : pick_compress_##dt##_lpg4(m, a))
+#define ENEC_ROW(dt) (L == 8 ? pick_compress_##dt##_lpg1(m, a, B == 1u << DEFAULT_LOGB) : L == 16 ? pick_compress_##dt##_lpg2(m, a, B == 1u << DEFAULT_LOGB) : pick_compress_##dt##_lpg4(m, a, B == 1u << DEFAULT_LOGB))
     if (dtype == ENEC_FP16) return ENEC_ROW(dt1);
     if (dtype == ENEC_FP32) return ENEC_ROW(dt2);
     return ENEC_ROW(dt0);
@@ -548,13 +548,12 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
             a.total += c.nb;
             done[j] = 1;
         }
-        CompressFn fn = pick_compress(prep[i].prm.m, prep[i].prm.n - prep[i].prm.m, dtype, prep[i].prm.L);
+        CompressFn fn = pick_compress(prep[i].prm.m, prep[i].prm.n - prep[i].prm.m, dtype, prep[i].prm.L, a.B);
         if (!fn) return ENEC_E_PARAMS;
         const unsigned threads = a.B / 64 < 64 ? 64 : a.B / 64;
         const size_t plane_bits = prep[i].prm.n + (dtype == ENEC_FP16 ? 3 : 0);
         // two images of the packed part, and the sign/mantissa bytes of the block that waits to be stored
-        const size_t lds = 2 * ((size_t)a.B / (8 * prep[i].prm.L) + plane_bits * a.B / 8) +
-                           (compress_sm_in_lds(dtype, prep[i].prm.L == 8 ? 1 : prep[i].prm.L == 16 ? 2 : 4) ? a.B : 0);
+        const size_t lds = 2 * ((size_t)a.B / (8 * prep[i].prm.L) + plane_bits * a.B / 8) + a.B;
         const unsigned resident = resident_workgroups((const void *)fn, threads, lds);
         if (resident == 0) return ENEC_E_HIP;
         const unsigned grid = persistent_grid(a.total, resident);

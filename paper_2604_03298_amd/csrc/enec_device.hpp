@@ -32,7 +32,7 @@
 // with L = 32: 0.207 -> 0.181 ms against two waves with the bytes in registers).  The fp32 instances
 // (twice the row registers) spill at that budget and run faster with two.
 #ifndef ENEC_COMPRESS_OCCUPANCY
-#define ENEC_COMPRESS_WAVES (compress_sm_in_lds(DT, LPG) ? 3 : 2)
+#define ENEC_COMPRESS_WAVES (DT != DT_FP32 ? 3 : 2)
 #define ENEC_COMPRESS_OCCUPANCY __attribute__((amdgpu_waves_per_eu(ENEC_COMPRESS_WAVES, ENEC_COMPRESS_WAVES)))
 #endif
 
@@ -41,9 +41,6 @@ namespace enec {
 constexpr int DT_BF16 = 0, DT_FP16 = 1, DT_FP32 = 2;
 constexpr int low_plane_bits(int m, int dt) { return m + (dt == DT_FP16 ? 3 : 0); }
 constexpr uint32_t exponent_bits(int dt) { return dt == DT_FP16 ? 5u : 8u; }
-// the compress instances that run three waves per SIMD (the 16-bit formats) and therefore park the
-// waiting block's sign/mantissa bytes in LDS; the others get two waves
-constexpr bool compress_sm_in_lds(int dt, int /*lpg*/) { return dt != DT_FP32; }
 
 // ---------------------------------------------------------------------------------
 // Compile-time bit map of Alg. 2 for one column (8 values of W bits -> W bytes).
@@ -642,8 +639,12 @@ __device__ __forceinline__ void load_block_rows(const CompressItem &p, uint32_t 
 // compression: split, transform, group test, packing, inter-block scan, store
 // (Sec. V-A compression path; Sec. V-B; Sec. V-C; Fig. 4)
 // ---------------------------------------------------------------------------------
-template <int M, int A, int DT, int LPG>
-__global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(const CompressArgs p)
+// LOGB: log2 of the block size where it is a constant, 0 = it is p.B.  The default block size has instances of its
+// own: with run-time sizes 50 scalar registers of shifts and offsets are spilled into vector lanes and read back in
+// every block; as constants they cost nothing (layer of 405 MB 151.2 -> 147.7 us, 470 MB matrices 312.7 -> 301.6,
+// fp16 107.0 -> 104.7, groups of eight 52.9 -> 51.5).
+template <int M, int A, int DT, int LPG, uint32_t LOGB>
+__global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_OCCUPANCY compress_kernel(const CompressArgs p)
 {
     constexpr int N = M + A;
     constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
@@ -667,10 +668,10 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
     __shared__ uint32_t s_err[2];              // range error in the block of image 0 / 1
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t B = p.B, logC = p.logB - 3u;
-    const uint32_t nact = B >> 6;
-    const bool active = tid < nact;
-    const uint32_t acc_tid = blockDim.x > 64u ? 64u : 0u;   // the lane that talks to the group accumulators
+    const uint32_t B = LOGB ? 1u << LOGB : p.B, logB = LOGB ? LOGB : p.logB, logC = logB - 3u;
+    const uint32_t nact = B >> 6, threads = nact < 64u ? 64u : nact;
+    const bool active = LOGB || tid < nact;                 // (a constant block has a whole number of waves)
+    const uint32_t acc_tid = threads > 64u ? 64u : 0u;      // the lane that talks to the group accumulators
     const uint32_t mask_bytes = (B >> 6) >> LOG_LPG;                  // B / (8 L)
     const uint32_t img_bytes = mask_bytes + (((uint32_t)(LM + A) * B) >> 3);
     const uint32_t fixed = B + mask_bytes + ((LM * B) >> 3);
@@ -707,7 +708,7 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
     const uint32_t guess = blockIdx.x;                       // the grid never exceeds the number of blocks
     uint32_t ci = item_of(guess, 0);
     uint4 raw[RW];
-    load_block_rows<DT>(p.item[ci], B, p.logB, guess - p.item[ci].first, tid, active, logC, raw);
+    load_block_rows<DT>(p.item[ci], B, logB, guess - p.item[ci].first, tid, active, logC, raw);
     if (tid == 0) {
         ticket_base = ctl[1];
         tag0 = *reinterpret_cast<const uint64_t *>(ctl + 2) + 1u;
@@ -723,7 +724,7 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
     uint32_t k = __builtin_amdgcn_readfirstlane(s_k[0]);     // global block index
     if (k != guess && k != NO_BLOCK) {                       // the guess was wrong: ask again
         ci = item_of(k, 0);
-        load_block_rows<DT>(p.item[ci], B, p.logB, k - p.item[ci].first, tid, active, logC, raw);
+        load_block_rows<DT>(p.item[ci], B, logB, k - p.item[ci].first, tid, active, logC, raw);
     }
     const uint64_t tag = (uint64_t)s_tag << 24;
     constexpr HHTable TL = HH<MP>::table;
@@ -773,60 +774,55 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
 
     // the block waiting to be stored
     uint32_t pend = NO_BLOCK, pend_item = 0, pend_cnt = 0, pend_S = 0, pend_err = 0;   // pend: index inside its tensor
-    // its sign/mantissa bytes wait in LDS behind the two images, every thread's own 64 bytes (in
-    // registers they were what the compiler spilled); the instances built for two waves per SIMD have
-    // the registers and keep them there
-    constexpr bool SM_IN_LDS = compress_sm_in_lds(DT, LPG);
+    // its sign/mantissa bytes wait in LDS behind the two images, in element order (in registers they were
+    // what the compiler spilled)
     uint8_t *sm_wait = smem + 2u * img_bytes;
-    uint32_t SMp[SM_IN_LDS ? 1 : 8][2];
 
     // stores block `kb` whose packed part sits in image `img` and whose sign/mantissa bytes sit in sm_wait
     auto store_block = [&](const CompressItem &it, uint32_t kb, uint32_t cnt, uint32_t S, const uint8_t *img,
                            uint32_t err_own) {
         const uint64_t off = s_off;
         uint8_t *dst = it.out + it.payload_base + off;
-        if constexpr (SM_IN_LDS) {
-            // the plane waits in LDS in element order and leaves as 128-bit vectors (four per thread
-            // instead of eight 64-bit stores of the thread's own bytes; measured neutral, within 1 %)
-            for (uint32_t v = tid; v < (B >> 4); v += blockDim.x)
-                st_stream(reinterpret_cast<uint4 *>(dst + 16u * v), *reinterpret_cast<const uint4 *>(sm_wait + 16u * v));
-        } else if (active) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                st_stream(reinterpret_cast<uint2 *>(dst + ((size_t)t << logC) + 8u * tid), make_uint2(SMp[t][0], SMp[t][1]));
-        }
-        for (uint32_t v = tid; v < (mask_bytes >> 4); v += blockDim.x)
-            st_stream(reinterpret_cast<uint4 *>(dst + B + 16u * v), *reinterpret_cast<const uint4 *>(img + 16u * v));
-        if (LM > 0) {
-            const uint8_t *ilow = img + mask_bytes;
-            uint8_t *dlow = dst + B + mask_bytes;
-            const uint32_t T2 = (LM * B) >> 4;                // half of the plane's length
-            for (uint32_t v = tid; v < (T2 >> 3); v += blockDim.x) {
-                const uint2 a = *reinterpret_cast<const uint2 *>(ilow + 8u * v);
-                const uint2 c = *reinterpret_cast<const uint2 *>(ilow + 8u * v + T2);
-                uint4 o;   // stream byte 2i = normalized byte i, stream byte 2i+1 = normalized byte i + T/2
+        // The payload leaves as one run of 16-byte vectors, sign/mantissa plane | mask | low plane | high
+        // records.  Payloads start at multiples of 16 bytes, lines are 128: the vectors are dealt to the lanes
+        // so that a wave's kilobyte begins at a line, because a streaming store of part of a line costs far
+        // more than its bytes (64-byte pieces: 3.7 instead of 6.0 TB/s in a plain copy).  (Against every region
+        // stored from its own start: layer 147.7 -> 146.6 us, 470 MB matrices
+        // 301.6 -> 299.7, groups of eight 51.5 -> 51.2, fp16 104.7 -> 105.1.)
+        const uint32_t shift = (uint32_t)((uintptr_t)dst >> 4) & 7u;     // vectors of the first line that are not ours
+        const uint32_t nsm = B >> 4, nmask = mask_bytes >> 4, nlow = (LM * B) >> 7;
+        const uint32_t hbytes = RB * cnt, nall = S >> 4;
+        int32_t v = (int32_t)tid - (int32_t)shift;
+        for (; v < (int32_t)nsm; v += (int32_t)threads)
+            if (v >= 0)
+                st_stream(reinterpret_cast<uint4 *>(dst) + v, reinterpret_cast<const uint4 *>(sm_wait)[v]);
+        for (; v < (int32_t)nall; v += (int32_t)threads) {
+            const uint32_t u = (uint32_t)v - nsm, j = u - nmask;         // vector of the packed part / of the low plane
+            uint4 o;
+            if (LM > 0 && j < nlow) {                                    // (j of a mask vector wraps to a huge number)
+                const uint32_t T2 = (LM * B) >> 4;                       // half of the plane's length
+                const uint8_t *ilow = img + mask_bytes + 8u * j;
+                const uint2 a = *reinterpret_cast<const uint2 *>(ilow);
+                const uint2 c = *reinterpret_cast<const uint2 *>(ilow + T2);
+                // stream byte 2i = normalized byte i, stream byte 2i+1 = normalized byte i + T/2
                 o.x = byte_perm(c.x, a.x, 0x05010400u);
                 o.y = byte_perm(c.x, a.x, 0x07030602u);
                 o.z = byte_perm(c.y, a.y, 0x05010400u);
                 o.w = byte_perm(c.y, a.y, 0x07030602u);
-                st_stream(reinterpret_cast<uint4 *>(dlow + 16u * v), o);
-            }
-        }
-        if (A > 0) {
-            const uint8_t *ihigh = img + mask_bytes + ((LM * B) >> 3);
-            uint8_t *dhigh = dst + fixed;
-            const uint32_t hbytes = RB * cnt;
-            for (uint32_t v = tid; 16u * v < hbytes; v += blockDim.x) {
-                uint4 o = *reinterpret_cast<const uint4 *>(ihigh + 16u * v);
-                uint32_t w[4] = {o.x, o.y, o.z, o.w};
+            } else {
+                o = *reinterpret_cast<const uint4 *>(img + 16u * u);
+                const uint32_t at = 16u * (j - nlow);                    // (huge for the mask)
+                if (A > 0 && u >= nmask && at + 16u > hbytes) {          // zero the padding behind the last record
+                    uint32_t w[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {                 // zero the padding behind the last record
-                    const uint32_t at = 16u * v + 4u * i;
-                    if (at >= hbytes) w[i] = 0;
-                    else if (at + 4u > hbytes) w[i] &= (1u << (8u * (hbytes - at))) - 1u;
+                    for (int i = 0; i < 4; ++i) {
+                        if (at + 4u * i >= hbytes) w[i] = 0;
+                        else if (at + 4u * i + 4u > hbytes) w[i] &= (1u << (8u * (hbytes - at - 4u * i))) - 1u;
+                    }
+                    o = make_uint4(w[0], w[1], w[2], w[3]);
                 }
-                st_stream(reinterpret_cast<uint4 *>(dhigh + 16u * v), make_uint4(w[0], w[1], w[2], w[3]));
             }
+            st_stream(reinterpret_cast<uint4 *>(dst) + v, o);
         }
         if (tid == 0) {
             uint64_t *table = reinterpret_cast<uint64_t *>(it.out + 64);
@@ -888,7 +884,7 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
 #pragma unroll
         for (int q = 0; q < MP; ++q) accP[q][0] = accP[q][1] = 0;
 
-        const uint64_t row0 = ((uint64_t)kl << p.logB) + 8u * tid;   // this thread's first element of row 0
+        const uint64_t row0 = ((uint64_t)kl << logB) + 8u * tid;   // this thread's first element of row 0
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             uint32_t gor = 0;
@@ -1052,7 +1048,7 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
         uint32_t cnext = ci;
         if (knext != NO_BLOCK) {
             cnext = item_of(knext, ci);
-            load_block_rows<DT>(p.item[cnext], B, p.logB, knext - p.item[cnext].first, tid, active, logC, raw);
+            load_block_rows<DT>(p.item[cnext], B, logB, knext - p.item[cnext].first, tid, active, logC, raw);
         }
 
         // ---- a7: stores of the previous block ----------------------------------------------
@@ -1063,13 +1059,8 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
         // this block becomes the pending one
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            if constexpr (SM_IN_LDS) {
-                if (active)
-                    *reinterpret_cast<uint2 *>(sm_wait + ((size_t)t << logC) + 8u * tid) = make_uint2(SMc[t][0], SMc[t][1]);
-            } else {
-                SMp[t][0] = SMc[t][0];
-                SMp[t][1] = SMc[t][1];
-            }
+            if (active)
+                *reinterpret_cast<uint2 *>(sm_wait + ((size_t)t << logC) + 8u * tid) = make_uint2(SMc[t][0], SMc[t][1]);
         }
         pend = kl; pend_item = ci; pend_cnt = cnt; pend_S = S; pend_err = own_err;
         slot ^= 1u;
@@ -1081,7 +1072,7 @@ __global__ void __launch_bounds__(512) ENEC_COMPRESS_OCCUPANCY compress_kernel(c
             k = __builtin_amdgcn_readfirstlane(s_k[slot]);
             if (k != NO_BLOCK) {
                 ci = item_of(k, ci);
-                load_block_rows<DT>(p.item[ci], B, p.logB, k - p.item[ci].first, tid, active, logC, raw);
+                load_block_rows<DT>(p.item[ci], B, logB, k - p.item[ci].first, tid, active, logC, raw);
             }
         }
     }

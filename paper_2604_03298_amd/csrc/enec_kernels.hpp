@@ -9,11 +9,12 @@
 namespace enec {
 
 using CompressFn = void (*)(const CompressArgs);
+constexpr uint32_t DEFAULT_LOGB = 14;       // log2 of the default data-block size, which has instances of its own
 
 #define ENEC_TABLES(dt)                               \
-    CompressFn pick_compress_##dt##_lpg1(int m, int a);   \
-    CompressFn pick_compress_##dt##_lpg2(int m, int a);   \
-    CompressFn pick_compress_##dt##_lpg4(int m, int a);
+    CompressFn pick_compress_##dt##_lpg1(int m, int a, bool default_block);   \
+    CompressFn pick_compress_##dt##_lpg2(int m, int a, bool default_block);   \
+    CompressFn pick_compress_##dt##_lpg4(int m, int a, bool default_block);
 ENEC_TABLES(dt0)
 ENEC_TABLES(dt1)
 ENEC_TABLES(dt2)
