@@ -1,13 +1,15 @@
 // ENEC streams with one (b, n, m) per data block: the search of Sec. V-E (Eq. 1-4) runs inside the
 // compress kernel on the exponents of each block's own elements, so a tensor whose blocks differ
 // (zeros, constants, weights of several scales, noise) is coded block by block with the tuple
-// that fits.  One workgroup per data block, one pass over the tensor:
+// that fits.  Compression only: enec_decompress.hpp reads these streams like any other.  One workgroup per data
+// block, one pass over the tensor:
 //   ticket -> rows -> split -> LDS histogram -> (b, n) by Eq. 1-3 -> m by Eq. 4 -> transform ->
 //   group test -> size (published) -> packing (Alg. 2, widths chosen at run time from the template
 //   instances) -> look-back over the earlier blocks' sizes -> stores.
-// The widths are run-time values here, so the packers are reached through a switch; the kernels
-// of enec_device.hpp, which know their widths at compile time, stay the fast path for one tuple
-// per tensor.
+// The widths are run-time values here, so the packers are reached through a switch; the kernel
+// of enec_device.hpp, which knows its widths at compile time, stays the fast path for one tuple
+// per tensor.  (What bounds this kernel is the in-order placement: with every block stored at a place of its own, for
+// timing only, the 405 MB layer takes 145 instead of 222 us.)
 #pragma once
 #include "enec_kernels.hpp"
 
