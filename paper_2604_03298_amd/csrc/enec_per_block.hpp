@@ -47,8 +47,8 @@ __device__ __forceinline__ void pb_load_rows(const void *src, uint64_t n_elems, 
             if (active && at < real) {
                 const uint32_t *in = reinterpret_cast<const uint32_t *>(src) + blk0 + at;
                 if (at + 8u <= real) {
-                    u = ld_stream(reinterpret_cast<const uint4 *>(in));
-                    v = ld_stream(reinterpret_cast<const uint4 *>(in + 4));
+                    u = *reinterpret_cast<const uint4 *>(in);               // plain: see load_block_rows
+                    v = *reinterpret_cast<const uint4 *>(in + 4);
                 } else {
                     uint32_t d[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
