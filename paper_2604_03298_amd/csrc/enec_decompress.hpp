@@ -55,6 +55,16 @@ __device__ __forceinline__ void unpack_records(const uint8_t *img_high, uint32_t
     for (int t = 0; t < 8; ++t) unpack_record_row<A, LPG>(img_high, my_word, my_excl, logC, tid, t, HI[t][0], HI[t][1]);
 }
 
+// Between LDS accesses of different lanes of one wave.  The wave barrier alone accesses no memory, so it would let the
+// optimiser move a lane's accesses across it wherever it can prove that this lane's own addresses differ; the
+// wavefront-scope fences forbid that and cost no instruction.
+__device__ __forceinline__ void exchange_in_wave()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // workgroups of four waves per CU: four, and three for fp32, whose blocks are 115 KB of traffic and need the
 // registers (45e6 elements: 66.8 us with four, four registers spilled; 61.1 with three; 66.6 with two)
 #define DEC_WAVES (DT == DT_FP32 ? 3 : 4)
@@ -200,10 +210,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
         }
         if constexpr (DT == DT_FP32) {
             // the wave's 1 KB of upper halves in element order (a wave's LDS accesses are executed in order, the
-            // kilobyte is its own)
+            // kilobyte is its own; exchange_in_wave keeps the compiler to that order)
             uint8_t *turn = smem + p.turn_at + 16u * (tid & ~63u);
             *reinterpret_cast<uint4 *>(turn + 16u * lane) = make_uint4(o[0], o[1], o[2], o[3]);
-            __builtin_amdgcn_wave_barrier();
+            exchange_in_wave();
             uint32_t *out32 = reinterpret_cast<uint32_t *>(it.out);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -223,7 +233,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
                     }
                 }
             }
-            __builtin_amdgcn_wave_barrier();
+            exchange_in_wave();                  // the next row is written over what other lanes have read
         } else {
             uint16_t *out16 = reinterpret_cast<uint16_t *>(it.out);
             if (e0 + 8 <= it.n_elems) {
