@@ -163,6 +163,19 @@ uint32_t spin_limit()
     return SPIN_LIMIT;
 }
 
+// Dynamic LDS of a decompression workgroup of a 16-bit format, so that a CU works on 65536 elements at a time (the
+// reason is in enec_decompress.hpp): too much for one workgroup more, little enough for these.  Blocks of 2048
+// elements need none, the CU's 32 waves are their limit.
+constexpr size_t LDS_PER_CU = 160 * 1024, LDS_UNIT = 1280;     // bytes, and the step in which they are handed out
+constexpr size_t decompress_lds_floor(uint32_t B) { return B <= 2048 ? 0 : LDS_PER_CU / (65536 / B + 1) + 256; }
+constexpr bool holds_65536_elements(uint32_t B)
+{
+    const size_t each = (decompress_lds_floor(B) + LDS_UNIT - 1) / LDS_UNIT * LDS_UNIT;
+    return LDS_PER_CU / each == 65536 / B && each <= 65536;    // (more than 64 KB would have to be asked for)
+}
+static_assert(holds_65536_elements(4096) && holds_65536_elements(8192) && holds_65536_elements(16384) &&
+                  holds_65536_elements(32768), "LDS of a decompression workgroup");
+
 unsigned bit_length(unsigned v) { unsigned r = 0; for (; v; v >>= 1) ++r; return r; }
 
 // ---- Sec. V-E phases 1-3 on a 256-bin exponent histogram -------------------------------------
@@ -811,7 +824,8 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
         if (!fn) return ENEC_E_FORMAT;
         // the packed part of the widest block of the launch: mask | low plane | high records | padding
         const size_t packed = (size_t)h0.B / (8 * h0.prm.L) + (size_t)widest * h0.B / 8 + 16;
-        const size_t lds = packed + (h0.dtype == ENEC_FP32 ? 16 * threads : 0);
+        size_t lds = packed + (h0.dtype == ENEC_FP32 ? 16 * threads : 0);
+        if (h0.dtype != ENEC_FP32 && lds < decompress_lds_floor(h0.B)) lds = decompress_lds_floor(h0.B);
         a.turn_at = (uint32_t)packed;
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(threads), lds, s, a);
     }

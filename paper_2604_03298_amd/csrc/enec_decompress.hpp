@@ -5,10 +5,14 @@
 // independent, and a workgroup that starts when another ends keeps the accesses of the device in stream
 // order.  A kernel that only moves the bytes of a block (24.8 KB in, 32 KB out) reaches 5.9 TB/s that way
 // and 5.75 with a persistent grid and the next block prefetched, which this kernel replaced.  What a
-// block waits for (table entry, then its payload) is hidden by the other workgroups of the CU.  Four share
-// it: the registers and the LDS would let eight, but then more of the device's accesses are in flight than
-// its memory likes (405 MB layer: 124.7 us with eight, 123.2 with five, 120.0 with four, 121.2 with three;
-// 470 MB matrices 273.8, 270.1, 271.9, 268.5).
+// block waits for (table entry, then its payload) is hidden by the other workgroups of the CU.  For the 16-bit
+// formats these are the workgroups of 65536 elements, four at the default block size: the registers and the LDS
+// would let twice as many, but then more of the device's accesses are in flight than its memory likes (405 MB
+// layer: 124.7 us with eight, 123.2 with five, 120.0 with four, 121.2 with three; 470 MB matrices 273.8, 270.1,
+// 271.9, 268.5).  The host holds the rest back with LDS that nobody uses (decompress_lds_floor), because a limit
+// on the waves per SIMD would count the idle lanes of blocks of 2048 elements, half of each wave, as well: with
+// four waves per SIMD 537 MB in such blocks take 174 us instead of 153, 268 MB with one tuple per block 87 instead
+// of 78 (83 with the kernel that came before).
 //
 // The widths (m, n) are run-time values, uniform over the workgroup: the unpackers are reached through a
 // switch over eight low-plane widths and eight record widths.  So the streams of a call that differ only in
@@ -65,12 +69,13 @@ __device__ __forceinline__ void exchange_in_wave()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// workgroups of four waves per CU: four, and three for fp32, whose blocks are 115 KB of traffic and need the
-// registers (45e6 elements: 66.8 us with four, four registers spilled; 61.1 with three; 66.6 with two)
-#define DEC_WAVES (DT == DT_FP32 ? 3 : 4)
+// fp32: three waves per SIMD, whose blocks are 115 KB of traffic and need the registers (45e6 elements: 66.8 us with
+// four, four registers spilled; 61.1 with three; 66.6 with two); the 16-bit formats: at least what their LDS allows
+#define DEC_WAVES_MIN (DT == DT_FP32 ? 3 : 4)
+#define DEC_WAVES_MAX (DT == DT_FP32 ? 3 : 8)
 
 template <int DT, int LPG>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WAVES, DEC_WAVES))) decompress_kernel(const DecompressArgs p)
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WAVES_MIN, DEC_WAVES_MAX))) decompress_kernel(const DecompressArgs p)
 {
     constexpr uint32_t E = exponent_bits(DT);
     constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
