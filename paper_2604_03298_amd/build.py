@@ -4,9 +4,9 @@ libenec_test.so is the same library with ENEC_TEST_HOOKS defined for the host co
 variable ENEC_SPIN_LIMIT lowers the bound of the scan's waits, which the tests of that bound need.
 
 The host code (csrc/enec_api.hip, csrc/enec_pipeline.hip), the compression kernels for one tuple per data block
-(csrc/enec_per_block.hip), the decompression kernels (csrc/enec_decompress.hip) and the nine tables of compression
-kernels (csrc/enec_kernels.hip, once per element format and group length) are compiled side by side into
-_build/*.o and linked into libenec.so.
+(csrc/enec_per_block.hip), the decompression kernels (csrc/enec_decompress.hip) and the eighteen tables of
+compression kernels (csrc/enec_kernels.hip, once per element format, group length and kind of block size) are compiled
+side by side into _build/*.o and linked into libenec.so.
 """
 from __future__ import annotations
 
@@ -36,7 +36,9 @@ def _units():
              ("enec_per_block.o", [SOURCES[2]]), ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]])]
     for lpg in (2, 1, 4):           # lanes per group: group lengths 16, 8, 32
         for dt in (0, 2, 1):
-            units.append((f"enec_kernels_dt{dt}_lpg{lpg}.o", [f"-DENEC_DT={dt}", f"-DENEC_LPG={lpg}", SOURCES[1]]))
+            for logb in (14, 0):    # block size: the default one as a constant, any as an argument
+                units.append((f"enec_kernels_dt{dt}_lpg{lpg}_b{logb}.o",
+                              [f"-DENEC_DT={dt}", f"-DENEC_LPG={lpg}", f"-DENEC_LOGB={logb}", SOURCES[1]]))
     return units
 
 

@@ -82,11 +82,14 @@ inline bool group_ok(unsigned L) { return L == 8 || L == 16 || L == 32; }
 
 inline CompressFn pick_compress(int m, int a, int dtype, unsigned L, uint32_t B)
 {
-#define ENEC_ROW(dt) (L == 8 ? pick_compress_##dt##_lpg1(m, a, B == 1u << DEFAULT_LOGB) : L == 16 ? pick_compress_##dt##_lpg2(m, a, B == 1u << DEFAULT_LOGB) : pick_compress_##dt##_lpg4(m, a, B == 1u << DEFAULT_LOGB))
+    const bool std_block = B == 1u << DEFAULT_LOGB;
+#define ENEC_PICK(dt, lpg) (std_block ? pick_compress_##dt##_##lpg##_b14(m, a) : pick_compress_##dt##_##lpg##_b0(m, a))
+#define ENEC_ROW(dt) (L == 8 ? ENEC_PICK(dt, lpg1) : L == 16 ? ENEC_PICK(dt, lpg2) : ENEC_PICK(dt, lpg4))
     if (dtype == ENEC_FP16) return ENEC_ROW(dt1);
     if (dtype == ENEC_FP32) return ENEC_ROW(dt2);
     return ENEC_ROW(dt0);
 #undef ENEC_ROW
+#undef ENEC_PICK
 }
 // A group length needs whole 16-byte vectors of mask per block (B >= 128 L) and at most 64 mask
 // words per block (the kernels scan them with one wave: B / L <= 2048).

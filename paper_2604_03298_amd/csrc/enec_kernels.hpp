@@ -1,7 +1,9 @@
-// Kernel tables of libenec.  Compression with one tuple per tensor has one function per element format and
-// group length that maps a tuple (m, a = n - m) to the kernel instance built for it (nullptr if there is
-// none); each of the nine is compiled as a translation unit of its own (enec_kernels.hip with
-// -DENEC_DT=<format 0|1|2> -DENEC_LPG=<lanes per group 1|2|4>) so that the build runs in parallel.
+// Kernel tables of libenec.  Compression with one tuple per tensor has one function per element format, group
+// length and kind of block size (the default one as a constant, or any as an argument) that maps a tuple
+// (m, a = n - m) to the kernel instance built for it (nullptr if there is none); each of the eighteen is compiled as
+// a translation unit of its own (enec_kernels.hip with -DENEC_DT=<format 0|1|2> -DENEC_LPG=<lanes per group 1|2|4>
+// -DENEC_LOGB=<14|0>), so that the build runs in parallel and a process loads what it uses: the runtime loads a
+// unit's code when the first of its kernels is asked for.
 // The other kernels know the widths at run time only and exist once per element format and group length.
 #pragma once
 #include "enec_device.hpp"
@@ -9,12 +11,12 @@
 namespace enec {
 
 using CompressFn = void (*)(const CompressArgs);
-constexpr uint32_t DEFAULT_LOGB = 14;       // log2 of the default data-block size, which has instances of its own
+constexpr uint32_t DEFAULT_LOGB = 14;       // log2 of the default data-block size, which has instances of its own (the _b14 tables)
 
-#define ENEC_TABLES(dt)                               \
-    CompressFn pick_compress_##dt##_lpg1(int m, int a, bool default_block);   \
-    CompressFn pick_compress_##dt##_lpg2(int m, int a, bool default_block);   \
-    CompressFn pick_compress_##dt##_lpg4(int m, int a, bool default_block);
+#define ENEC_TABLES(dt)                                                                             \
+    CompressFn pick_compress_##dt##_lpg1_b14(int m, int a), pick_compress_##dt##_lpg1_b0(int m, int a); \
+    CompressFn pick_compress_##dt##_lpg2_b14(int m, int a), pick_compress_##dt##_lpg2_b0(int m, int a); \
+    CompressFn pick_compress_##dt##_lpg4_b14(int m, int a), pick_compress_##dt##_lpg4_b0(int m, int a);
 ENEC_TABLES(dt0)
 ENEC_TABLES(dt1)
 ENEC_TABLES(dt2)

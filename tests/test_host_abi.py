@@ -178,3 +178,13 @@ def test_stream_info_reads_oracle_headers(oracle):
     bad = per[:64].copy()
     bad[40] = 2
     assert enec.stream_info(bad)["rc"] == enec.E_FORMAT
+
+
+def test_each_kind_of_block_size_has_a_unit_of_its_own():
+    """The first call of a process loads the code of the unit its kernel is in, so a unit holds the compression kernels of one
+    element format, one group length and one kind of block size (the default one as a constant, any as an argument)."""
+    from paper_2604_03298_amd import build
+    tables = [dict(a[2:].split("=") for a in args if a.startswith("-D")) for name, args in build._units()
+              if name.startswith("enec_kernels_")]
+    want = {(dt, lpg, logb) for dt in "012" for lpg in "124" for logb in ("0", "14")}
+    assert len(tables) == len(want) and {(t["ENEC_DT"], t["ENEC_LPG"], t["ENEC_LOGB"]) for t in tables} == want
