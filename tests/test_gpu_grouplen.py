@@ -29,9 +29,9 @@ def test_bf16_every_width_pair(gpu, oracle, L, n):
 def test_fp16_every_width_pair(gpu, oracle, L, n):
     rng = np.random.default_rng(4000 + 10 * L + n)
     for m in range(0, n + 1):
-        B, size = [(4096, 3 * 4096 + 517), (16384, 2 * 16384 + 4099)][(n + m) % 2]
-        w = in_window_words(rng, 14, n, size, FP16, m=m)
-        check_both_ways(gpu, oracle, w, (14, n, m, L), FP16, B, f"fp16 L={L} n={n} m={m} B={B}")
+        for B, size in [(4096, 3 * 4096 + 517), (16384, 2 * 16384 + 4099)]:
+            w = in_window_words(rng, 14, n, size, FP16, m=m)
+            check_both_ways(gpu, oracle, w, (14, n, m, L), FP16, B, f"fp16 L={L} n={n} m={m} B={B}")
 
 
 @pytest.mark.parametrize("L", [8, 32])
@@ -39,9 +39,9 @@ def test_fp16_every_width_pair(gpu, oracle, L, n):
 def test_fp32_every_width_pair(gpu, oracle, L, n):
     rng = np.random.default_rng(5000 + 10 * L + n)
     for m in range(0, n + 1):
-        B, size = [(4096, 3 * 4096 + 517), (16384, 2 * 16384 + 4099)][(n + m) % 2]
-        w = in_window_words(rng, 128, n, size, FP32, m=m)
-        check_both_ways(gpu, oracle, w, (128, n, m, L), FP32, B, f"fp32 L={L} n={n} m={m} B={B}")
+        for B, size in [(4096, 3 * 4096 + 517), (16384, 2 * 16384 + 4099)]:
+            w = in_window_words(rng, 128, n, size, FP32, m=m)
+            check_both_ways(gpu, oracle, w, (128, n, m, L), FP32, B, f"fp32 L={L} n={n} m={m} B={B}")
 
 
 @pytest.mark.parametrize("L,B", [(8, 2048), (8, 4096), (8, 8192), (8, 16384), (32, 4096), (32, 8192), (32, 16384), (32, 32768)])
