@@ -144,10 +144,10 @@ unsigned resident_workgroups(const void *fn, unsigned threads, size_t lds)
     return value;
 }
 
-// A persistent grid for `total` blocks on a device that holds `resident` workgroups.  (Shrinking the
-// grid until every round of blocks is full, e.g. 727 instead of 768 workgroups for 12352 blocks, was
-// measured and lost 1.5 % on compression and 4 % on decompression of the 7B layer: the last, nearly
-// empty round costs less than the parallelism given up in all the others.)
+// The persistent grid of a compression launch for `total` blocks on a device that holds `resident` workgroups.
+// (Shrinking the grid until every round of blocks is full, e.g. 727 instead of 768 workgroups for 12352 blocks, was
+// measured and lost 1.5 % on the 7B layer: the last, nearly empty round costs less than the parallelism given up
+// in all the others.)
 unsigned persistent_grid(unsigned total, unsigned resident)
 {
     return total < resident ? total : resident;

@@ -16,8 +16,15 @@
 //
 // The widths (m, n) are run-time values, uniform over the workgroup: the unpackers are reached through a
 // switch over eight low-plane widths and eight record widths.  So the streams of a call that differ only in
-// their tuples share a launch: the nine tensors of a decoder layer, whose norm vectors have a tuple of their
-// own, take one launch instead of two (138 + 6.3 us of kernels and the gap between them before).
+// their tuples share a launch (sixteen vectors of 100001 elements with tuples of their own: 7 instead of 16 us).
+// Block sizes don't mix: a decoder layer takes one launch for its matrices and one of 4 us for its norm vectors,
+// whose default block size is their length.
+//
+// The decoded elements leave as streaming stores, whatever their number.  Alone that is faster at every size; a reader
+// right behind finds less of them in the caches.  Decode and reader together, streaming / plain stores / the kernel
+// before (us, caches full of other data): 34 MB and a copy 36.6 / 29.5 / 33.9, and a product with 16 rows
+// 35.6 / 37.1 / 41.6; 90 MB and a copy 84.5 / 64.6 / 77.2, 16 rows 87.1 / 84.3 / 98.2, 256 rows 103.8 / 94.8 / 105.8;
+// 470 MB and a copy 336 / 339 / 361, 16 rows 283 / 261 / 287, 256 rows 501 / 505 / 519.
 #pragma once
 #include "enec_kernels.hpp"
 

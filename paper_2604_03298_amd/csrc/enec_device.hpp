@@ -117,6 +117,16 @@ __device__ __forceinline__ uint32_t shl_or_shr(uint32_t v, int s)
 // Tensors and payloads are read once and written once, so they pass the caches as streaming
 // (non-temporal) accesses.  It takes both sides: a copy of 896 MB with blocks of 32 KB runs at 5.4 TB/s
 // with plain accesses, at 5.5 / 5.6 with only the loads / only the stores streaming, at 6.2 with both.
+// Streaming loads leave nothing in the 256 MB Infinity Cache, so they don't push out what others have just written
+// there, and they gain nothing from what lies there.  A 134 MB bf16 tensor, us, streaming / plain loads / the
+// kernels before, which had plain accesses on both sides:
+//   caches full of another kernel's output   compress 55 / 74 / 76   decompress 44 / 63 / 63
+//   input written by the kernel before       compress 54 / 51 / 55   decompress 49 / 38 / 41
+//   input brought by a copy from the host                            decompress 45 / 64 / 64
+//   the same data again and again            compress 52 / 47 / 58   decompress 40 / 36 / 51
+// The last line is for two sets of 232 MB in turn.  Where both sets fit into the cache (67 MB tensors), streaming
+// loses to both others: compress 32 / 28 / 30, decompress 22 / 20 / 21, one tuple per block 22 / 19 / 19.  Weights lie in
+// memory until their layer comes up and arrive over the host link, which are the first and the third line.
 typedef uint32_t vec2u __attribute__((ext_vector_type(2)));
 typedef uint32_t vec4u __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 ld_stream(const uint4 *p)
@@ -793,10 +803,11 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         uint8_t *dst = it.out + it.payload_base + off;
         // The payload leaves as one run of 16-byte vectors, sign/mantissa plane | mask | low plane | high
         // records.  Payloads start at multiples of 16 bytes, lines are 128: the vectors are dealt to the lanes
-        // so that a wave's kilobyte begins at a line, because a streaming store of part of a line costs far
-        // more than its bytes (64-byte pieces: 3.7 instead of 6.0 TB/s in a plain copy).  (Against every region
-        // stored from its own start: layer 147.7 -> 146.6 us, 470 MB matrices
-        // 301.6 -> 299.7, groups of eight 51.5 -> 51.2, fp16 104.7 -> 105.1.)
+        // so that a wave's kilobyte begins at a line, because a streaming store of part of a line costs more
+        // than its bytes (64-byte pieces: 3.7 instead of 6.0 TB/s in a plain copy).  Against the same run dealt from
+        // the payload's start it writes 1.6 % less (470 MB matrices 343.2 against 349.0 MB per launch) and is worth
+        // 1 to 2 % in batches (16 x 34 MB 179.8 against 183.2 us, 7 x 34 MB 85.8 / 87.1) and 1 to 5 % for blocks of
+        // 2048; nothing on one large tensor (537 MB 174.5 / 174.6); one small tensor loses 2 % (34 MB 21.1 / 20.7).
         const uint32_t shift = (uint32_t)((uintptr_t)dst >> 4) & 7u;     // vectors of the first line that are not ours
         const uint32_t nsm = B >> 4, nmask = mask_bytes >> 4, nlow = (LM * B) >> 7;
         const uint32_t hbytes = RB * cnt, nall = S >> 4;

@@ -548,6 +548,10 @@ compress_per_block_kernel(const PbCompressArgs p)
     __syncthreads();
 
     // ---- a7: stores ----
+    // Streaming although each region starts at any 16 bytes, so that its ends are parts of lines: that writes 3.6 %
+    // more than plain stores do (layer 313 against 302 MB), which the caches join, and is faster all the same
+    // (67e6 elements of mixed blocks 81.8 against 82.5 us, 134e6 146.8 / 151.4, 34e6 53.0 / 54.4; blocks of 2048
+    // equal).  One run dealt along lines, as in the one-tuple kernel, was not tried here.
     const uint64_t off = s_off;
     uint8_t *dst = it.out + it.payload_base + off;
     if (active) {
