@@ -4,8 +4,8 @@
 Workload (default, `--workload config2`): the synthetic 7B-style decoder layer (nine bf16 tensors,
 404.8 MB), resident in HBM.  One step = compress every tensor of the workload, then decompress every
 tensor (every row of the hot path).  Throughput counts uncompressed bytes, as the paper does (Sec. VI-B).
-The tensors of a pass go to the library's batch entry points, one call per (n, m) tuple and per sixteen
-tensors, which is one kernel launch each.
+The tensors of a pass go to the library's batch entry points, at most sixteen per call and one kernel launch
+per call: compression by tuple and block size, decompression by block size.
 
 Other workloads: config1 (one 1024x4096 matrix), config3 (edge-case mix, one 64M-element tensor),
 config3b (the same blocks as four per-category tensors), config4 (32 tensors of 8192x28672, 15 GB, the
@@ -38,9 +38,9 @@ WORKLOADS = ["config1", "config2", "config3", "config3b", "config4", "config5"]
 # profiles/codec_kernels_config2_hbm_traffic.md.  A figure is reported only while the kernel sources still
 # hash to what they were when it was measured, and only for the workload it was measured on; else null.
 MEASURED_TRAFFIC = {
-    "kernel_sources_sha256": "2b9e048caf862dc139eed311f676362c928a25bdaf8f7238c6f8e1fa06dcd19b",
+    "kernel_sources_sha256": "4f134bd83b3efae217171738d8a45e7ae0be619a540fa59ec979a71e9275aea8",
     "bytes_per_launch": {
-        "config2": {"enec::compress_kernel<4,2>": 714768173, "enec::decompress_kernel<4,2>": 713773370},
+        "config2": {"enec::compress_kernel<4, 2, 0, 2, 14u>": 716516077, "enec::decompress_kernel<0, 2>": 716992670},
     },
 }
 
@@ -222,18 +222,22 @@ def main():
     backs = [torch.zeros_like(s) for s in srcs]
     sizes = torch.zeros(nt, dtype=torch.int64, device="cuda")
 
-    # tensors that share (n, m) go into one library call of at most sixteen tensors (= one kernel launch)
-    by_tuple = {}
-    for i in range(nt):
-        by_tuple.setdefault((params[i][1], params[i][2]), []).append(i)
-    groups = [g[c:c + 16] for g in by_tuple.values() for c in range(0, len(g), 16)]
-    ng = len(groups)
-    calls = groups
+    # one library call of at most sixteen tensors per kernel launch: tensors of one tuple and block size are compressed
+    # together, streams of one block size decompressed together, whatever their tuples
+    def calls_by(key):
+        found = {}
+        for i in range(nt):
+            found.setdefault(key(i), []).append(i)
+        return [g[c:c + 16] for g in found.values() for c in range(0, len(g), 16)]
+
+    blocks = [enec.default_block_size(n) for n in n_el]
+    ccalls = calls_by(lambda i: (params[i][1:], blocks[i]))
+    dcalls = calls_by(lambda i: (params[i][3], blocks[i]))
 
     def compress_all(ev=None):
         if ev:
             ev[0].record()
-        for gi, g in enumerate(calls):
+        for gi, g in enumerate(ccalls):
             rc = enec.compress_batch([srcs[i] for i in g], [params[i] for i in g], [outs[i] for i in g], ws,
                                      out_bytes=[sizes[i:i + 1] for i in g])
             assert rc == 0, enec.strerror(rc)
@@ -246,12 +250,12 @@ def main():
     assert all(v > 0 for v in stream_bytes)
     headers = [outs[i][:64].cpu().numpy().tobytes() for i in range(nt)]
     ditems = [enec.make_decompress_items([outs[i] for i in g], [headers[i] for i in g], [backs[i] for i in g])
-              for g in calls]
+              for g in dcalls]
 
     def decompress_all(ev=None):
         if ev:
             ev[0].record()
-        for gi, g in enumerate(calls):
+        for gi in range(len(dcalls)):
             rc = enec.decompress_batch(None, None, None, items=ditems[gi][0])
             assert rc == 0, enec.strerror(rc)
             if ev:
@@ -262,11 +266,11 @@ def main():
     for i in range(nt):
         assert torch.equal(backs[i], srcs[i]), f"round trip of {names[i]} is not bit-exact"
 
-    def new_events():
-        return [torch.cuda.Event(enable_timing=True) for _ in range(ng + 1)]
+    def new_events(calls):
+        return [torch.cuda.Event(enable_timing=True) for _ in range(len(calls) + 1)]
 
-    evc = [new_events() for _ in range(args.steps)]
-    evd = [new_events() for _ in range(args.steps)]
+    evc = [new_events(ccalls) for _ in range(args.steps)]
+    evd = [new_events(dcalls) for _ in range(args.steps)]
 
     for _ in range(args.warmup):
         compress_all()
@@ -282,11 +286,12 @@ def main():
     ms_per_step = (t1 - t0) * 1e3 / args.steps
     value = 2 * raw_bytes / (ms_per_step * 1e-3) / 1e9
 
-    # per-launch durations from the events recorded inside the timed region (one launch per group)
-    dur_c = np.array([[evc[k][gi].elapsed_time(evc[k][gi + 1]) for gi in range(ng)] for k in range(args.steps)])
-    dur_d = np.array([[evd[k][gi].elapsed_time(evd[k][gi + 1]) for gi in range(ng)] for k in range(args.steps)])
-    pass_c = np.array([evc[k][0].elapsed_time(evc[k][ng]) for k in range(args.steps)])
-    pass_d = np.array([evd[k][0].elapsed_time(evd[k][ng]) for k in range(args.steps)])
+    # per-launch durations from the events recorded inside the timed region (one launch per call)
+    def launch_ms(evs):
+        return np.array([[e[gi].elapsed_time(e[gi + 1]) for gi in range(len(e) - 1)] for e in evs])
+    dur_c, dur_d = launch_ms(evc), launch_ms(evd)
+    pass_c = np.array([e[0].elapsed_time(e[-1]) for e in evc])
+    pass_d = np.array([e[0].elapsed_time(e[-1]) for e in evd])
     comp_gbps = raw_bytes / (np.median(pass_c) * 1e-3) / 1e9
     decomp_gbps = raw_bytes / (np.median(pass_d) * 1e-3) / 1e9
 
@@ -294,14 +299,22 @@ def main():
     # algorithmic bytes of one launch = for each of its tensors the bf16 data (2 bytes/element) plus
     # the whole stream (sign/mantissa plane, mask, packed planes, offset table, header), each read
     # or written once
+    # compress_kernel<m, n - m, element format, lanes per group, log2 of a constant block size or 0>,
+    # decompress_kernel<element format, lanes per group>; launches of another block size than the default are kept apart
+    def compress_name(i):
+        _, n, m, L = params[i]
+        return f"enec::compress_kernel<{m}, {n - m}, {enec.BF16}, {L // 8}, {14 if blocks[i] == 16384 else 0}u>"
+
+    def decompress_name(i):
+        return f"enec::decompress_kernel<{enec.BF16}, {params[i][3] // 8}>"
+
     kern = {}
-    for gi, g in enumerate(groups):
-        m, a = params[g[0]][2], params[g[0]][1] - params[g[0]][2]
-        moved = sum(2 * n_el[i] + stream_bytes[i] for i in g)
-        for kind, dur in (("compress", dur_c), ("decompress", dur_d)):
-            e = kern.setdefault(f"enec::{kind}_kernel<{m},{a}>", dict(ms=0.0, bytes=0, launches=0, tensors=0))
+    for name, calls, dur in ((compress_name, ccalls, dur_c), (decompress_name, dcalls, dur_d)):
+        for gi, g in enumerate(calls):
+            label = name(g[0]) + ("" if blocks[g[0]] == 16384 else f" (blocks of {blocks[g[0]]})")
+            e = kern.setdefault(label, dict(ms=0.0, bytes=0, launches=0, tensors=0))
             e["ms"] += float(dur[:, gi].sum())
-            e["bytes"] += moved * args.steps
+            e["bytes"] += sum(2 * n_el[i] + stream_bytes[i] for i in g) * args.steps
             e["launches"] += args.steps
             e["tensors"] += len(g)
     dom = max(kern, key=lambda k: kern[k]["ms"])
@@ -381,7 +394,7 @@ def main():
     ratio = raw_bytes / sum(stream_bytes)
     cfg = {"workload": wl_name, "tensors": nt, "uncompressed_bytes": raw_bytes, "block_size": 16384,
            "params": sorted({tuple(p) for p in params}) if nt > 9 else {names[i]: list(params[i]) for i in range(nt)},
-           "launches_per_pass": ng}
+           "launches_per_pass": len(ccalls), "decompress_launches_per_pass": len(dcalls)}
     if host is not None:
         cfg["input_crc32"] = {names[i]: zlib.crc32(host[i].tobytes()) for i in range(nt)}
         # ties the timed streams to the oracle's: tests/test_gpu_parity.py compares these streams byte for byte
