@@ -613,17 +613,28 @@ __device__ __forceinline__ void load_block_rows(const CompressItem &p, uint32_t 
             }
             return;
         }
+        const uint32_t left = (uint32_t)(p.n_elems - blk0);       // the tensor's last block, shorter than B
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
-            uint32_t d[8] = {padw, padw, padw, padw, padw, padw, padw, padw};
-            if (active && e0 < p.n_elems) {
+            const uint32_t at = ((uint32_t)t << logC) + 8u * tid;
+            const uint4 *src = reinterpret_cast<const uint4 *>(in + blk0 + at);
+            const bool whole = active && at + 8u <= left;
+            raw[2 * t] = whole ? src[0] : make_uint4(padw, padw, padw, padw);
+            raw[2 * t + 1] = whole ? src[1] : make_uint4(padw, padw, padw, padw);
+        }
+        if (const uint32_t end = left & ~7u, rest = left & 7u; rest && active && (end & ((1u << logC) - 1u)) == 8u * tid) {
+            const uint32_t *src = in + blk0 + end;
+            uint32_t d[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (e0 + i < p.n_elems) d[i] = in[e0 + i];
-            }
-            raw[2 * t] = make_uint4(d[0], d[1], d[2], d[3]);
-            raw[2 * t + 1] = make_uint4(d[4], d[5], d[6], d[7]);
+            for (int i = 0; i < 8; ++i) d[i] = src[(uint32_t)i < rest ? i : 0];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) d[i] = (uint32_t)i < rest ? d[i] : padw;
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if ((uint32_t)t == end >> logC) {
+                    raw[2 * t] = make_uint4(d[0], d[1], d[2], d[3]);
+                    raw[2 * t + 1] = make_uint4(d[4], d[5], d[6], d[7]);
+                }
         }
     } else {
         if (blk0 + B <= p.n_elems) {               // whole block inside the tensor: no per-row tests
@@ -633,20 +644,27 @@ __device__ __forceinline__ void load_block_rows(const CompressItem &p, uint32_t 
                                 : make_uint4(padw, padw, padw, padw);
             return;
         }
+        // the tensor's last block, shorter than B: whole vectors as ever, and the lane in whose vector the tensor ends
+        // asks for those elements together.  (All elements of all eight rows one by one, each under a branch and waited
+        // for before the next, made every tensor wait for its last block: three of 8388609 elements 26.8 us, now 24.0.)
+        const uint32_t left = (uint32_t)(p.n_elems - blk0);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
-            uint32_t d[4] = {padw, padw, padw, padw};
-            if (active && e0 < p.n_elems) {
+            const uint32_t at = ((uint32_t)t << logC) + 8u * tid;
+            raw[t] = active && at + 8u <= left ? ld_stream(reinterpret_cast<const uint4 *>(p.in + blk0 + at))
+                                               : make_uint4(padw, padw, padw, padw);
+        }
+        if (const uint32_t end = left & ~7u, rest = left & 7u; rest && active && (end & ((1u << logC) - 1u)) == 8u * tid) {
+            const uint16_t *src = p.in + blk0 + end;
+            uint32_t d[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (e0 + i < p.n_elems) {
-                        const uint32_t v = p.in[e0 + i];
-                        d[i >> 1] = (i & 1) ? ((d[i >> 1] & 0x0000FFFFu) | (v << 16))
-                                            : ((d[i >> 1] & 0xFFFF0000u) | v);
-                    }
-            }
-            raw[t] = make_uint4(d[0], d[1], d[2], d[3]);
+            for (int i = 0; i < 8; ++i) d[i] = src[(uint32_t)i < rest ? i : 0];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) d[i] = (uint32_t)i < rest ? d[i] : padw & 0xFFFFu;
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if ((uint32_t)t == end >> logC)
+                    raw[t] = make_uint4(d[0] | (d[1] << 16), d[2] | (d[3] << 16), d[4] | (d[5] << 16), d[6] | (d[7] << 16));
         }
     }
 }
