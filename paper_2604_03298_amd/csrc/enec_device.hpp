@@ -25,6 +25,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 // Three waves per SIMD for the compression kernel: the register budget (168) that lets three
 // workgroups of 256 threads share a CU.  The 16-bit formats fit it once the waiting block's
@@ -691,6 +692,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     constexpr int MP = LM > 0 ? LM : 1;
     constexpr int AP = A > 0 ? A : 1;
     constexpr int RW = DT == DT_FP32 ? 16 : 8;           // 128-bit vectors of one block per thread
+    constexpr bool FULL = N == (int)exponent_bits(DT);   // the window is the whole exponent range (mode 1)
 
     // two LDS images of the packed part of a payload: mask | low plane (as normalized bytes,
     // interleaved on the way out) | high records
@@ -930,6 +932,11 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         for (int q = 0; q < MP; ++q) accP[q][0] = accP[q][1] = 0;
 
         const uint64_t row0 = ((uint64_t)kl << logB) + 8u * tid;   // this thread's first element of row 0
+        // WRAP: the bytes are subtracted without borrows between them, and where the window is not the whole exponent
+        // range every exponent is compared with it.  Two straight runs of code and one branch: a branch on the mode at
+        // each of the sixteen subtractions cut the transform into pieces that nothing was scheduled across.
+        auto transform = [&](auto wrap) {
+        constexpr bool WRAP = decltype(wrap)::value;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             uint32_t gor = 0;
@@ -965,12 +972,12 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
                 }
                 // a2 transform: z = (b + 2^(n-1) - x) mod 256 per byte, y = z with the sign bit flipped
                 uint32_t Z;
-                if (mode == 0) {
+                if constexpr (!WRAP) {
                     Z = crep - X;
-                    if (N < 8) err_acc |= Z;
+                    err_acc |= Z;
                 } else {
                     Z = bytesub_safe(crep, X);
-                    if (mode == 2) {
+                    if constexpr (!FULL) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const uint32_t xb = (X >> (8 * i)) & 0xFFu;
@@ -1003,7 +1010,15 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
             else if constexpr (LPG == 2) mw[t] = compact_even_bits(flagged);
             else mw[t] = compact_fourth_bits(flagged);
         }
-        if (N < 8 && mode == 0) bad = (err_acc & ~NMASK) != 0;
+        };
+        if constexpr (FULL) {
+            transform(std::true_type{});
+        } else if (DT == DT_FP16 || mode == 0) {
+            transform(std::false_type{});
+            bad = (err_acc & ~NMASK) != 0;
+        } else {
+            transform(std::true_type{});
+        }
         if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) atomicOr(&s_err[slot], 1u);
 
         // a wave holds 64 / LPG mask bits of every row (nact / LPG when the block has 2048 elements
