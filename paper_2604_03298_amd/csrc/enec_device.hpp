@@ -185,35 +185,51 @@ __device__ __forceinline__ uint32_t swap_pair(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, false);
 }
 
-// keep the even bits of x, packed into 32 bits (wave-uniform: runs on the scalar unit)
-__device__ __forceinline__ uint32_t compact_even_bits(uint64_t x)
-{
-    x &= 0x5555555555555555ull;
-    x = (x | (x >> 1)) & 0x3333333333333333ull;
-    x = (x | (x >> 2)) & 0x0F0F0F0F0F0F0F0Full;
-    x = (x | (x >> 4)) & 0x00FF00FF00FF00FFull;
-    x = (x | (x >> 8)) & 0x0000FFFF0000FFFFull;
-    x = (x | (x >> 16)) & 0x00000000FFFFFFFFull;
-    return (uint32_t)x;
-}
-
-// keep every fourth bit of x, packed into 16 bits
-__device__ __forceinline__ uint32_t compact_fourth_bits(uint64_t x)
-{
-    x &= 0x1111111111111111ull;
-    x = (x | (x >> 3)) & 0x0303030303030303ull;
-    x = (x | (x >> 6)) & 0x000F000F000F000Full;
-    x = (x | (x >> 12)) & 0x000000FF000000FFull;
-    x = (x | (x >> 24)) & 0x000000000000FFFFull;
-    return (uint32_t)x;
-}
-
 // OR over the four lanes of a quad, two DPP moves
 __device__ __forceinline__ uint32_t quad_or(uint32_t v)
 {
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1 /* quad_perm [1,0,3,2] */, 0xF, 0xF, false);
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E /* quad_perm [2,3,0,1] */, 0xF, 0xF, false);
     return v;
+}
+
+// v_writelane_b32 (this compiler has no builtin for it; the declaration names LLVM's intrinsic)
+extern "C" __device__ int enec_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
+// a3: the wave's mask bits of the eight rows go into the block's mask (one bit per group, group order = row-major).
+// flagged[t] = ballot of "this lane's group of row t needs a record"; the LPG lanes of a group agree, so every LPG-th bit
+// counts.  Lane 2t + h takes half h of row t's ballot, and the sixteen lanes squeeze their 32 bits to 32 / LPG and store
+// them with one instruction.  (The same on the scalar unit, row after row, was 130 dependent instructions.)
+template <int LPG>
+__device__ __forceinline__ void put_mask_bits(const uint64_t (&flagged)[8], uint8_t *mask, uint32_t logC, uint32_t wave, uint32_t lane)
+{
+    uint32_t x = 0;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        x = (uint32_t)enec_writelane((int)(uint32_t)flagged[t], 2 * t, (int)x);
+        x = (uint32_t)enec_writelane((int)(uint32_t)(flagged[t] >> 32), 2 * t + 1, (int)x);
+    }
+    const uint32_t t = lane >> 1, h = lane & 1u;
+    // a row's mask is 2^(logC - 3) / LPG bits; the wave's share starts 64 / LPG bits after the one before.  A block of
+    // 2048 elements (logC = 8) has half a wave per row: its upper half holds no group.
+    const bool mine = lane < 16u && (logC > 8u || h == 0);
+    const uint32_t bit = (t << (logC - 3u)) + 64u * wave + 32u * h;      // first lane of the half row, over all rows
+    if constexpr (LPG == 1) {
+        if (mine) *reinterpret_cast<uint32_t *>(mask + (bit >> 3)) = x;
+    } else if constexpr (LPG == 2) {
+        x &= 0x55555555u;
+        x = (x | (x >> 1)) & 0x33333333u;
+        x = (x | (x >> 2)) & 0x0F0F0F0Fu;
+        x = (x | (x >> 4)) & 0x00FF00FFu;
+        x = x | (x >> 8);
+        if (mine) *reinterpret_cast<uint16_t *>(mask + (bit >> 4)) = (uint16_t)x;
+    } else {
+        x &= 0x11111111u;
+        x = (x | (x >> 3)) & 0x03030303u;
+        x = (x | (x >> 6)) & 0x000F000Fu;
+        x = x | (x >> 12);
+        if (mine) mask[bit >> 5] = (uint8_t)x;
+    }
 }
 
 // inclusive prefix sum over the 64 lanes with data-parallel-primitive moves: four shifts inside
@@ -925,7 +941,8 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         const bool draw_now = tid == 0 && p.lookahead && drawing;
         if (draw_now) next_raw = atomicAdd(ctl + zero, 1u);
 
-        uint32_t SMc[8][2], HI[8][2], accP[MP][2], mw[8], mw_hi[LPG == 1 ? 8 : 1];
+        uint32_t SMc[8][2], HI[8][2], accP[MP][2];
+        uint64_t flagged[8];
         uint32_t err_acc = 0;
         bool bad = false;
 #pragma unroll
@@ -1005,10 +1022,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
             // a3: OR over the lanes that share a group, one mask bit per group
             if constexpr (LPG == 2) gor |= swap_pair(gor);
             if constexpr (LPG == 4) gor = quad_or(gor);
-            const uint64_t flagged = __builtin_amdgcn_ballot_w64(gor != 0);
-            if constexpr (LPG == 1) { mw[t] = (uint32_t)flagged; mw_hi[t] = (uint32_t)(flagged >> 32); }
-            else if constexpr (LPG == 2) mw[t] = compact_even_bits(flagged);
-            else mw[t] = compact_fourth_bits(flagged);
+            flagged[t] = __builtin_amdgcn_ballot_w64(gor != 0);
         }
         };
         if constexpr (FULL) {
@@ -1021,34 +1035,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         }
         if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) atomicOr(&s_err[slot], 1u);
 
-        // a wave holds 64 / LPG mask bits of every row (nact / LPG when the block has 2048 elements
-        // and the only wave is half empty); group order = row-major
-        if (lane == 0 && 64u * wave < nact) {
-            if constexpr (LPG == 1) {
-                if (logC >= 9) {
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        img_maskw[((uint32_t)t << (logC - 8)) + 2u * wave] = mw[t];
-                        img_maskw[((uint32_t)t << (logC - 8)) + 2u * wave + 1u] = mw_hi[t];
-                    }
-                } else {  // B = 2048: 32 groups per row
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) img_maskw[t] = mw[t];
-                }
-            } else if constexpr (LPG == 2) {
-                if (logC >= 9) {
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) img_maskw[((uint32_t)t << (logC - 9)) + wave] = mw[t];
-                } else {  // B = 2048: 16 groups per row, one wave
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) img_maskw[u] = mw[2 * u] | (mw[2 * u + 1] << 16);
-                }
-            } else {      // 16 bits per wave and row (B >= 4096)
-                uint16_t *img_mask16 = reinterpret_cast<uint16_t *>(img);
-#pragma unroll
-                for (int t = 0; t < 8; ++t) img_mask16[((uint32_t)t << (logC - 9)) + wave] = (uint16_t)mw[t];
-            }
-        }
+        if (64u * wave < nact) put_mask_bits<LPG>(flagged, img, logC, wave, lane);
         if (LM > 0 && active) {
 #pragma unroll
             for (int q = 0; q < LM; ++q)

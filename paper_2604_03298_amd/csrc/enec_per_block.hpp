@@ -407,7 +407,7 @@ compress_per_block_kernel(const PbCompressArgs p)
     const uint32_t nrep = ((1u << n) - 1u) * 0x01010101u;
     const uint32_t lrep = ((1u << m) - 1u) * 0x01010101u;
     const uint32_t arep = ((1u << a) - 1u) * 0x01010101u;
-    const bool mask_writer = lane == 0 && 64u * wave < nact;
+    uint64_t flagged[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
         uint32_t gor = 0;
@@ -425,31 +425,12 @@ compress_per_block_kernel(const PbCompressArgs p)
             if constexpr (DT == DT_FP16) X[t][h] = Y | (X[t][h] & 0xE0E0E0E0u);
             else X[t][h] = Y;
         }
-        // a3: OR over the lanes that share a group, one mask bit per group; a wave holds 64 / LPG mask
-        // bits of every row, group order = row-major
+        // a3: OR over the lanes that share a group, one mask bit per group
         if constexpr (LPG == 2) gor |= swap_pair(gor);
         if constexpr (LPG == 4) gor = quad_or(gor);
-        const uint64_t flagged = __builtin_amdgcn_ballot_w64(gor != 0);
-        if constexpr (LPG == 1) {
-            if (mask_writer) {
-                if (logC >= 9) {
-                    img_maskw[((uint32_t)t << (logC - 8)) + 2u * wave] = (uint32_t)flagged;
-                    img_maskw[((uint32_t)t << (logC - 8)) + 2u * wave + 1u] = (uint32_t)(flagged >> 32);
-                } else {      // B = 2048: 32 groups per row
-                    img_maskw[t] = (uint32_t)flagged;
-                }
-            }
-        } else if constexpr (LPG == 2) {
-            const uint32_t mw = compact_even_bits(flagged);
-            if (mask_writer) {
-                if (logC >= 9) img_maskw[((uint32_t)t << (logC - 9)) + wave] = mw;
-                else reinterpret_cast<uint16_t *>(img)[t] = (uint16_t)mw;      // B = 2048: 16 groups per row, one wave
-            }
-        } else {              // 16 bits per wave and row (B >= 4096)
-            const uint32_t mw = compact_fourth_bits(flagged);
-            if (mask_writer) reinterpret_cast<uint16_t *>(img)[((uint32_t)t << (logC - 9)) + wave] = (uint16_t)mw;
-        }
+        flagged[t] = __builtin_amdgcn_ballot_w64(gor != 0);
     }
+    if (64u * wave < nact) put_mask_bits<LPG>(flagged, img, logC, wave, lane);
     __syncthreads();
 
     // ---- a5 positions: exclusive popcount prefix over the mask words (a wave scan per wave) ----
