@@ -847,45 +847,66 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         const uint32_t shift = (uint32_t)((uintptr_t)dst >> 4) & 7u;     // vectors of the first line that are not ours
         const uint32_t nsm = B >> 4, nmask = mask_bytes >> 4, nlow = (LM * B) >> 7;
         const uint32_t hbytes = RB * cnt, nall = S >> 4;
+        // vector j of the low plane: stream byte 2i = normalized byte i, stream byte 2i+1 = normalized byte i + T/2
+        auto low_vector = [&](uint32_t j) -> uint4 {
+            const uint32_t T2 = (LM * B) >> 4;                           // half of the plane's length
+            const uint8_t *ilow = img + mask_bytes + 8u * j;
+            const uint2 a = *reinterpret_cast<const uint2 *>(ilow);
+            const uint2 c = *reinterpret_cast<const uint2 *>(ilow + T2);
+            return make_uint4(byte_perm(c.x, a.x, 0x05010400u), byte_perm(c.x, a.x, 0x07030602u),
+                              byte_perm(c.y, a.y, 0x05010400u), byte_perm(c.y, a.y, 0x07030602u));
+        };
+        // vector u of the packed part, behind the low plane: the padding behind the last record is zero
+        auto high_vector = [&](uint32_t u) -> uint4 {
+            const uint4 o = *reinterpret_cast<const uint4 *>(img + 16u * u);
+            const uint32_t at = 16u * (u - nmask - nlow);
+            if (at + 16u <= hbytes) return o;
+            uint32_t w[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (at + 4u * i >= hbytes) w[i] = 0;
+                else if (at + 4u * i + 4u > hbytes) w[i] &= (1u << (8u * (hbytes - at - 4u * i))) - 1u;
+            }
+            return make_uint4(w[0], w[1], w[2], w[3]);
+        };
+        auto packed_vector = [&](uint32_t u) -> uint4 {
+            if (LM > 0 && u - nmask < nlow) return low_vector(u - nmask);            // (wraps for a mask vector)
+            if (A == 0 || u < nmask) return *reinterpret_cast<const uint4 *>(img + 16u * u);
+            return high_vector(u);
+        };
         int32_t v = (int32_t)tid - (int32_t)shift;
-        if constexpr (!SM_IN_LDS) {
-            if (active) {
+        if constexpr (LOGB != 0) {
+            // Constant sizes: round i stores vectors i threads - 7 .. i threads + threads - 1, so all but the rounds in
+            // which one region ends and the next begins know at compile time what they store.
+            constexpr int T = (1 << LOGB) / 64, NSM = (1 << LOGB) / 16, NLO = NSM + (1 << LOGB) / (1024 * LPG), NHI = NLO + (LM << LOGB) / 128;
+            constexpr int ROUNDS = (NHI + 7 + T - 1) / T;                // rounds that reach below NHI
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    st_stream(reinterpret_cast<uint2 *>(dst + ((size_t)t << logC) + 8u * tid), make_uint2(SMp[t][0], SMp[t][1]));
+            for (int i = 0; i < ROUNDS; ++i) {
+                const int first = i * T - 7, last = i * T + T - 1;
+                const int32_t w = v + i * T;
+                if ((first < 0 && w < 0) || (last >= NHI && w >= (int32_t)nall)) continue;
+                uint4 o;
+                if (last < NSM || (first < NSM && w < NSM)) o = reinterpret_cast<const uint4 *>(sm_wait)[w];
+                else if (LM > 0 && first >= NLO && last < NHI) o = low_vector((uint32_t)w - NLO);
+                else o = packed_vector((uint32_t)w - NSM);
+                st_stream(reinterpret_cast<uint4 *>(dst) + w, o);
             }
-            while (v < (int32_t)nsm) v += (int32_t)threads;
-        }
-        for (; v < (int32_t)nsm; v += (int32_t)threads)
-            if (v >= 0)
-                st_stream(reinterpret_cast<uint4 *>(dst) + v, reinterpret_cast<const uint4 *>(sm_wait)[v]);
-        for (; v < (int32_t)nall; v += (int32_t)threads) {
-            const uint32_t u = (uint32_t)v - nsm, j = u - nmask;         // vector of the packed part / of the low plane
-            uint4 o;
-            if (LM > 0 && j < nlow) {                                    // (j of a mask vector wraps to a huge number)
-                const uint32_t T2 = (LM * B) >> 4;                       // half of the plane's length
-                const uint8_t *ilow = img + mask_bytes + 8u * j;
-                const uint2 a = *reinterpret_cast<const uint2 *>(ilow);
-                const uint2 c = *reinterpret_cast<const uint2 *>(ilow + T2);
-                // stream byte 2i = normalized byte i, stream byte 2i+1 = normalized byte i + T/2
-                o.x = byte_perm(c.x, a.x, 0x05010400u);
-                o.y = byte_perm(c.x, a.x, 0x07030602u);
-                o.z = byte_perm(c.y, a.y, 0x05010400u);
-                o.w = byte_perm(c.y, a.y, 0x07030602u);
-            } else {
-                o = *reinterpret_cast<const uint4 *>(img + 16u * u);
-                const uint32_t at = 16u * (j - nlow);                    // (huge for the mask)
-                if (A > 0 && u >= nmask && at + 16u > hbytes) {          // zero the padding behind the last record
-                    uint32_t w[4] = {o.x, o.y, o.z, o.w};
+            if constexpr (A > 0)
+                for (v += ROUNDS * T; v < (int32_t)nall; v += T) st_stream(reinterpret_cast<uint4 *>(dst) + v, high_vector((uint32_t)v - NSM));
+        } else {
+            if constexpr (!SM_IN_LDS) {
+                if (active) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (at + 4u * i >= hbytes) w[i] = 0;
-                        else if (at + 4u * i + 4u > hbytes) w[i] &= (1u << (8u * (hbytes - at - 4u * i))) - 1u;
-                    }
-                    o = make_uint4(w[0], w[1], w[2], w[3]);
+                    for (int t = 0; t < 8; ++t)
+                        st_stream(reinterpret_cast<uint2 *>(dst + ((size_t)t << logC) + 8u * tid), make_uint2(SMp[t][0], SMp[t][1]));
                 }
+                while (v < (int32_t)nsm) v += (int32_t)threads;
             }
-            st_stream(reinterpret_cast<uint4 *>(dst) + v, o);
+            for (; v < (int32_t)nsm; v += (int32_t)threads)
+                if (v >= 0)
+                    st_stream(reinterpret_cast<uint4 *>(dst) + v, reinterpret_cast<const uint4 *>(sm_wait)[v]);
+            for (; v < (int32_t)nall; v += (int32_t)threads)
+                st_stream(reinterpret_cast<uint4 *>(dst) + v, packed_vector((uint32_t)v - nsm));
         }
         if (tid == 0) {
             uint64_t *table = reinterpret_cast<uint64_t *>(it.out + 64);
