@@ -1,0 +1,59 @@
+"""The counting kernel at the edges of its loop (a workgroup's vectors in flight, whole chunks of a sample, elements behind the
+last vector), and calls that tune from several threads at once, more of them than pinned slots are kept."""
+import threading
+
+import numpy as np
+import pytest
+
+from test_gpu_dtypes import gpu, BF16, FP16, FP32, WORD  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+STEP = 512 * 8          # elements that one round of a workgroup's loads covers (16-bit formats)
+
+
+@pytest.mark.parametrize("every", [1, 2, 16])
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+def test_counts_at_the_edges_of_the_loop(gpu, oracle, dtype, every):
+    torch, enec = gpu.torch, gpu.enec
+    rng = np.random.default_rng(10 * dtype + every)
+    sizes = [1, 3, 8, 9, STEP - 1, STEP, STEP + 1, 4 * STEP + 5, 5 * STEP, 256 * STEP - 3, 256 * STEP * 4 + 4097, 256 * STEP * 5 + 2]
+    ws_tensors = [rng.integers(0, np.iinfo(WORD[dtype]).max, n, dtype=WORD[dtype], endpoint=True) for n in sizes]
+    dev = [torch.from_numpy(w.view(np.int32 if dtype == FP32 else np.int16)).cuda() for w in ws_tensors]
+    ws = enec.new_workspace(sum(sizes))
+    alone = [enec.tune_batch([d], ws, every=every, dtype=dtype, want_histograms=True) for d in dev]
+    together = enec.tune_batch(dev, ws, every=every, dtype=dtype, want_histograms=True)
+    for i, w in enumerate(ws_tensors):
+        part = w if every == 1 else oracle.sample(w, every, dtype)
+        want = oracle.histogram(part, dtype)
+        assert np.array_equal(alone[i][1][0], want), sizes[i]
+        assert np.array_equal(together[1][i], want), sizes[i]
+        E = 5 if dtype == FP16 else 8
+        assert tuple(alone[i][0][0])[:3] == tuple(oracle.tune_hist(want, E)[0])[:3] == tuple(together[0][i])[:3]
+
+
+def test_calls_from_many_threads(gpu, oracle):
+    torch, enec = gpu.torch, gpu.enec
+    rng = np.random.default_rng(5)
+    jobs = []
+    for i in range(7):
+        ws = [rng.integers(i << 10, (i << 10) + 3000, 50001 + 777 * i + j, dtype=np.uint16) for j in range(17 if i == 3 else 3)]
+        dev = [torch.from_numpy(w.view(np.int16)).cuda() for w in ws]
+        jobs.append((ws, dev, enec.new_workspace(sum(w.size for w in ws)), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    got = [[] for _ in jobs]
+
+    def work(i):
+        for _ in range(5):
+            got[i].append(enec.tune_batch(jobs[i][1], jobs[i][2], stream=jobs[i][3], want_histograms=True))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i, (ws, _, _, _) in enumerate(jobs):
+        want = np.stack([oracle.histogram(w) for w in ws])
+        assert len(got[i]) == 5
+        for _, hist in got[i]:
+            assert np.array_equal(hist, want), i
