@@ -44,6 +44,12 @@ __global__ void __launch_bounds__(256) copy_kernel(uint4 *__restrict__ dst, cons
     for (uint64_t v = (uint64_t)blockIdx.x * 256u + threadIdx.x; v < nvec; v += stride) dst[v] = src[v];
 }
 
+// the tuner's counts on their way to the host (pinned memory): one workgroup per histogram
+__global__ void __launch_bounds__(128) hand_over_counts_kernel(uint4 *host, const uint4 *hist)
+{
+    host[blockIdx.x * 128u + threadIdx.x] = hist[blockIdx.x * 128u + threadIdx.x];
+}
+
 }  // namespace enec
 
 namespace {
@@ -178,6 +184,47 @@ constexpr bool holds_65536_elements(uint32_t B)
 }
 static_assert(holds_65536_elements(4096) && holds_65536_elements(8192) && holds_65536_elements(16384) &&
                   holds_65536_elements(32768), "LDS of a decompression workgroup");
+
+// Pinned memory in which a call that tunes finds its counts: a kernel stores them there, which takes 2 us where a copy
+// to pageable memory takes 14.  A call takes a slot for as long as it runs; up to four are kept for later calls, for
+// all threads, streams and devices, more are given back when their call ends, and these when the process does.
+class CountSlots {
+public:
+    static constexpr size_t BYTES = WS_HIST_SLOTS * 256 * 8, KEPT = 4;
+    void *take()
+    {
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (!free_.empty()) {
+                void *p = free_.back();
+                free_.pop_back();
+                return p;
+            }
+        }
+        // (another thread may be capturing a graph, and an allocation would end its capture in any mode but this one)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, BYTES, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        return p;
+    }
+    void give(void *p)
+    {
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (free_.size() < KEPT) { free_.push_back(p); return; }
+        }
+        (void)hipHostFree(p);
+    }
+    CountSlots() { free_.reserve(KEPT); }
+    ~CountSlots() { for (void *p : free_) (void)hipHostFree(p); }
+private:
+    std::mutex mu_;
+    std::vector<void *> free_;
+};
+// made by the first call that tunes, after the runtime has started, so that it ends before the runtime does
+CountSlots &count_slots() { static CountSlots slots; return slots; }
 
 unsigned bit_length(unsigned v) { unsigned r = 0; for (; v; v >>= 1) ++r; return r; }
 
@@ -374,8 +421,10 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
         if ((!items[i].in && items[i].n_elems) || !aligned16(items[i].in) || items[i].n_elems > MAX_ELEMS) return ENEC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     auto *dhist = reinterpret_cast<unsigned long long *>(static_cast<uint8_t *>(workspace) + WS_HIST);
-    std::vector<uint64_t> host(WS_HIST_SLOTS * 256);
-    // sixteen tensors at a time: their histograms are counted into sixteen slots, copied back together,
+    if (n_items == 0) return ENEC_OK;
+    uint64_t *host = static_cast<uint64_t *>(count_slots().take());
+    if (!host) return ENEC_E_HIP;
+    // sixteen tensors at a time: their histograms are counted into sixteen slots, handed over together,
     // and the stream is waited for once
     for (size_t first = 0; first < n_items; first += WS_HIST_SLOTS) {
         const size_t count = n_items - first < WS_HIST_SLOTS ? n_items - first : WS_HIST_SLOTS;
@@ -409,17 +458,20 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
             else if (dtype == ENEC_FP16) histogram_kernel<DT_FP16><<<grid, HIST_THREADS, 0, s>>>(a);
             else histogram_kernel<DT_BF16><<<grid, HIST_THREADS, 0, s>>>(a);
         }
-        if (hipMemcpyAsync(host.data(), dhist, count * 256 * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        uint4 *to = reinterpret_cast<uint4 *>(host);
+        const uint4 *from = reinterpret_cast<const uint4 *>(dhist);
+        void *args[] = {&to, &from};
+        if (hipLaunchKernel((const void *)hand_over_counts_kernel, dim3((unsigned)count), dim3(128), args, 0, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess) {
             (void)hipGetLastError();
-            return ENEC_E_HIP;
+            return ENEC_E_HIP;                 // (the slot is not given back: a kernel may still be about to write there)
         }
         for (size_t j = 0; j < count; ++j) {
-            int rc = enec_tune_histogram(host.data() + 256 * j, dtype, &params[first + j]);
-            if (rc != ENEC_OK) return rc;
-            if (histograms) std::memcpy(histograms + 256 * (first + j), host.data() + 256 * j, 256 * 8);
+            enec_tune_histogram(host + 256 * j, dtype, &params[first + j]);          // (refuses nothing that can be here)
+            if (histograms) std::memcpy(histograms + 256 * (first + j), host + 256 * j, 256 * 8);
         }
     }
+    count_slots().give(host);
     return ENEC_OK;
 }
 
