@@ -136,6 +136,141 @@ __device__ __forceinline__ uint32_t wave_min32(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// Phases 2 and 3 of Sec. V-E for one block, from the counts of its exponents (s_hist) and the values that occur
+// (s_present): s_best = n << 8 | b, s_m = m, visible to all waves on return.  s_best must be all ones before.
+template <int DT, int LPG>
+__device__ __forceinline__ void pb_search(const uint32_t *s_hist, const unsigned long long *s_present, unsigned long long &s_best, uint32_t &s_m,
+                                          uint32_t real)
+{
+    constexpr uint32_t E = exponent_bits(DT);
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t xl = 255u, xh = 0u;
+#pragma unroll
+    for (int c = 3; c >= 0; --c) {
+        const uint64_t z = s_present[c];
+        if (z) xl = 64u * c + (uint32_t)__builtin_ctzll(z);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint64_t z = s_present[c];
+        if (z) xh = 64u * c + 63u - (uint32_t)__builtin_clzll(z);
+    }
+    xl = __builtin_amdgcn_readfirstlane(xl);
+    xh = __builtin_amdgcn_readfirstlane(xh);
+    // Eq. 4 for every m (lane m holds the count of elements whose y fits m bits) with the group length
+    // the block is coded with, 1/L + n + (m - n) p^L, in IEEE double, p^L by three to five squarings;
+    // the smallest value wins, ties go to the smaller m (one wave)
+    auto choose_m = [&](uint32_t cnt, uint32_t n) -> uint32_t {
+        // (a whole block has a power of two of elements, which needs no division)
+        const double q = (real & (real - 1u)) == 0 ? __builtin_ldexp((double)cnt, -(int)__builtin_ctz(real)) : (double)cnt / (double)real;
+        const double q2 = q * q, q4 = q2 * q2;
+        double qL = q4 * q4;                                   // p^8
+        if constexpr (LPG >= 2) qL = qL * qL;                  // p^16
+        if constexpr (LPG == 4) qL = qL * qL;                  // p^32
+        double least = (1.0 / (double)(8 * LPG) + (double)n) + ((double)lane - (double)n) * qL;
+        if (lane > n) least = __builtin_inf();
+        uint32_t at = lane;
+        // the first minimum of lanes 0 .. 15 travels to lane 15; of two equal ones the lower lane's stays
+        auto fold = [&](auto ctrl) {
+            constexpr int C = decltype(ctrl)::value;
+            const unsigned long long bits = (unsigned long long)__double_as_longlong(least);
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)bits, (int)bits, C, 0xF, 0xF, false);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(bits >> 32), (int)(bits >> 32), C, 0xF, 0xF, false);
+            const uint32_t from = (uint32_t)__builtin_amdgcn_update_dpp((int)at, (int)at, C, 0xF, 0xF, false);
+            const double other = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+            if (other <= least) { least = other; at = from; }
+        };
+        fold(std::integral_constant<int, 0x111 /* row_shr:1 */>{});
+        fold(std::integral_constant<int, 0x112 /* row_shr:2 */>{});
+        fold(std::integral_constant<int, 0x114 /* row_shr:4 */>{});
+        fold(std::integral_constant<int, 0x118 /* row_shr:8 */>{});
+        return (uint32_t)__builtin_amdgcn_readlane((int)at, 15);
+    };
+    if (xh - xl < 64u) {
+        // The usual case, at most 64 values between the lowest and the highest: wave 0 does the whole
+        // search in registers.  Lane j holds the count of value xl + j and is candidate b = xl + j.
+        if (wave == 0) {
+            const uint32_t R = xh - xl + 1u;
+            const bool valid = lane < R;
+            const uint32_t v = valid ? s_hist[xl + lane] : 0u;
+            // every b with Eq. 1's n and Eq. 3's cost; ties: smaller n, then smaller b
+            const uint32_t nb_ = pb_width_for(xl + lane, xl, xh, E);
+            // Eq. 1's n makes 2^n exceed every distance inside the window, so with P_j = the counts of values xl .. xl + j
+            //   D_j = sum_i v_i ((j - i) mod 2^n) = j N - sum_i i v_i + 2^n (N - P_j):
+            // a prefix sum and a sum in place of a pass over the values (23 bits, exact as before).
+            const uint32_t P = wave_incl_scan(v, lane);
+            const uint32_t D = lane * real + ((real - P) << nb_) - wave_sum32(lane * v);
+            const uint32_t Dmin = wave_min32(valid ? D : 0xFFFFFFFFu);
+            const uint32_t pick = wave_min32(valid && D == Dmin ? (nb_ << 8) | (xl + lane) : 0xFFFFFFFFu);
+            const uint32_t b = pick & 0xFFu, n = pick >> 8;
+            // phase 3: lane m counts the elements whose y fits m bits: those down to 2^m - 1 below b, and above b those
+            // from 2^n - 2^m + 1 on (there y = 2^n - (x - b))
+            const uint32_t pos = b - xl, p2 = 1u << (lane < n ? lane : n);
+            const uint32_t below = (uint32_t)__shfl((int)P, (int)(pos - p2), 64);
+            const uint32_t top = pos + (1u << n) - p2;
+            const uint32_t above = (uint32_t)__shfl((int)P, (int)(top < 63u ? top : 63u), 64);
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)P, (int)pos) - (pos >= p2 ? below : 0u) + (real - above);
+            const uint32_t best_m = choose_m(cnt, n);
+            if (lane == 0) {
+                s_best = ((unsigned long long)n << 8) | b;
+                s_m = best_m;
+            }
+        }
+        __syncthreads();
+    } else {
+        // A block whose exponents spread over more than 64 values.  Lane j of a wave holds the counts of
+        // the values j, 64 + j, 128 + j and 192 + j; wave w takes the candidates b = xl + 64 w + j (and
+        // further ones if the workgroup has fewer than four waves); the waves' best meet in s_best.
+        // Eq. 1 gives n = 7 or 8 for every b of such a block (the wider side of the window has at least
+        // 32 values).  With n fixed, Eq. 3's cost D_n(b) = sum_x count[x] ((b - x) mod 2^n) obeys
+        //   D_n(b + 1) - D_n(b) = N - 2^n H_n[(b + 1) mod 2^n],   H_n = the counts folded modulo 2^n,
+        // (every term grows by one, the ones that wrap fall by 2^n - 1), so the 64 costs of a wave come
+        // from D_n of its first candidate, a sum over the lanes, and a prefix sum of H_n over the lanes.
+        uint32_t hv[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) hv[c] = s_hist[64 * c + lane];
+        for (uint32_t b0 = xl + 64u * wave; b0 <= xh; b0 += blockDim.x) {
+            const uint32_t bb = b0 + lane;
+            const bool valid = bb <= xh;
+            const uint32_t nb_ = pb_width_for(bb, xl, xh, E);
+            const uint32_t h0 = s_hist[bb & 255u], h1 = s_hist[(bb + 128u) & 255u];
+            uint32_t D = 0xFFFFFFFFu;                         // costs are at most 2^15 elements * 255
+#pragma unroll
+            for (uint32_t nn = 7; nn <= 8; ++nn) {
+                const uint32_t mask = (1u << nn) - 1u;
+                uint32_t t = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) t += __umul24(hv[c], (b0 - (64u * c + lane)) & mask);
+                const uint32_t first = wave_sum32(t);                       // D_nn(b0)
+                const uint32_t g = nn == 8 ? h0 : h0 + h1;                  // H_nn[b mod 2^nn]
+                const uint32_t upto = wave_incl_scan(g, lane) - (uint32_t)__builtin_amdgcn_readlane((int)g, 0);
+                if (nb_ == nn) D = first + lane * real - (upto << nn);
+            }
+            const uint32_t Dmin = wave_min32(valid ? D : 0xFFFFFFFFu);
+            const uint32_t pick = wave_min32(valid && D == Dmin ? (nb_ << 8) | bb : 0xFFFFFFFFu);
+            if (lane == 0) atomicMin(&s_best, ((unsigned long long)Dmin << 16) | pick);   // ties: smaller n, then smaller b
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t b = (uint32_t)s_best & 0xFFu, n = ((uint32_t)s_best >> 8) & 0xFFu;
+            uint32_t ybits[4];                                     // y < 2^m  <=>  ybits <= m
+#pragma unroll
+            for (int c = 0; c < 4; ++c) ybits[c] = 32u - (uint32_t)__clz((b - (64u * c + lane)) & ((1u << n) - 1u));
+            uint32_t cnt = 0;
+            for (uint32_t j = 0; j <= n; ++j) {
+                uint32_t t = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) t += ybits[c] <= j ? hv[c] : 0u;
+                const uint32_t s = wave_sum32(t);
+                if (lane == j) cnt = s;
+            }
+            const uint32_t best_m = choose_m(cnt, n);
+            if (lane == 0) s_m = best_m;
+        }
+        __syncthreads();
+    }
+}
+
 // waves per SIMD the compress kernel is built for: six where the instance fits 80 registers without
 // spilling (fp16, and bf16 with groups of 16), five elsewhere: a spill here parks raw bytes in scratch
 // memory, and they are reloaded when the block is stored, after they have left the L2
@@ -273,123 +408,7 @@ compress_per_block_kernel(const PbCompressArgs p)
         if (lane == 0) s_present[x >> 6] = present;
     }
     __syncthreads();
-    uint32_t xl = 255u, xh = 0u;
-#pragma unroll
-    for (int c = 3; c >= 0; --c) {
-        const uint64_t z = s_present[c];
-        if (z) xl = 64u * c + (uint32_t)__builtin_ctzll(z);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const uint64_t z = s_present[c];
-        if (z) xh = 64u * c + 63u - (uint32_t)__builtin_clzll(z);
-    }
-    xl = __builtin_amdgcn_readfirstlane(xl);
-    xh = __builtin_amdgcn_readfirstlane(xh);
-    // Eq. 4 for every m (lane m holds the count of elements whose y fits m bits) with the group length
-    // the block is coded with, 1/L + n + (m - n) p^L, in IEEE double, p^L by three to five squarings;
-    // the smallest value wins, ties go to the smaller m (one wave)
-    auto choose_m = [&](uint32_t cnt, uint32_t n) -> uint32_t {
-        const double q = (double)cnt / (double)real;
-        const double q2 = q * q, q4 = q2 * q2;
-        double qL = q4 * q4;                                   // p^8
-        if constexpr (LPG >= 2) qL = qL * qL;                  // p^16
-        if constexpr (LPG == 4) qL = qL * qL;                  // p^32
-        const double bexp = (1.0 / (double)(8 * LPG) + (double)n) + ((double)lane - (double)n) * qL;
-        const unsigned long long bits = (unsigned long long)__double_as_longlong(bexp);
-        uint32_t best_m = 0;
-        double best = __longlong_as_double((long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(bits >> 32), 0) << 32) |
-                                                       (uint32_t)__builtin_amdgcn_readlane((int)bits, 0)));
-        for (uint32_t j = 1; j <= n; ++j) {
-            const double cand = __longlong_as_double((long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(bits >> 32), (int)j) << 32) |
-                                                                 (uint32_t)__builtin_amdgcn_readlane((int)bits, (int)j)));
-            if (cand < best) { best = cand; best_m = j; }                 // ties: smaller m
-        }
-        return best_m;
-    };
-    if (xh - xl < 64u) {
-        // The usual case, at most 64 values between the lowest and the highest: wave 0 does the whole
-        // search in registers.  Lane j holds the count of value xl + j and is candidate b = xl + j.
-        if (wave == 0) {
-            const uint32_t R = xh - xl + 1u;
-            const bool valid = lane < R;
-            const uint32_t v = valid ? s_hist[xl + lane] : 0u;
-            // every b with Eq. 1's n and Eq. 3's cost; ties: smaller n, then smaller b
-            const uint32_t nb_ = pb_width_for(xl + lane, xl, xh, E);
-            const uint32_t nmask_b = (1u << nb_) - 1u;
-            uint32_t D = 0;                                   // at most 2^15 elements * 255
-            for (uint32_t i = 0; i < R; ++i)
-                D += __umul24((uint32_t)__builtin_amdgcn_readlane((int)v, (int)i), (lane - i) & nmask_b);
-            const uint32_t Dmin = wave_min32(valid ? D : 0xFFFFFFFFu);
-            const uint32_t pick = wave_min32(valid && D == Dmin ? (nb_ << 8) | (xl + lane) : 0xFFFFFFFFu);
-            const uint32_t b = pick & 0xFFu, n = pick >> 8;
-            // phase 3: lane m counts the elements whose y fits m bits
-            const uint32_t y = (b - (xl + lane)) & ((1u << n) - 1u);
-            const uint32_t ybits = 32u - (uint32_t)__clz(y);           // y < 2^m  <=>  ybits <= m
-            uint32_t cnt = 0;
-            for (uint32_t j = 0; j <= n; ++j) {
-                const uint32_t s = wave_sum32(valid && ybits <= j ? v : 0u);
-                if (lane == j) cnt = s;
-            }
-            const uint32_t best_m = choose_m(cnt, n);
-            if (lane == 0) {
-                s_best = ((unsigned long long)n << 8) | b;
-                s_m = best_m;
-            }
-        }
-        __syncthreads();
-    } else {
-        // A block whose exponents spread over more than 64 values.  Lane j of a wave holds the counts of
-        // the values j, 64 + j, 128 + j and 192 + j; wave w takes the candidates b = xl + 64 w + j (and
-        // further ones if the workgroup has fewer than four waves); the waves' best meet in s_best.
-        // Eq. 1 gives n = 7 or 8 for every b of such a block (the wider side of the window has at least
-        // 32 values).  With n fixed, Eq. 3's cost D_n(b) = sum_x count[x] ((b - x) mod 2^n) obeys
-        //   D_n(b + 1) - D_n(b) = N - 2^n H_n[(b + 1) mod 2^n],   H_n = the counts folded modulo 2^n,
-        // (every term grows by one, the ones that wrap fall by 2^n - 1), so the 64 costs of a wave come
-        // from D_n of its first candidate, a sum over the lanes, and a prefix sum of H_n over the lanes.
-        uint32_t hv[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) hv[c] = s_hist[64 * c + lane];
-        for (uint32_t b0 = xl + 64u * wave; b0 <= xh; b0 += blockDim.x) {
-            const uint32_t bb = b0 + lane;
-            const bool valid = bb <= xh;
-            const uint32_t nb_ = pb_width_for(bb, xl, xh, E);
-            const uint32_t h0 = s_hist[bb & 255u], h1 = s_hist[(bb + 128u) & 255u];
-            uint32_t D = 0xFFFFFFFFu;                         // costs are at most 2^15 elements * 255
-#pragma unroll
-            for (uint32_t nn = 7; nn <= 8; ++nn) {
-                const uint32_t mask = (1u << nn) - 1u;
-                uint32_t t = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) t += __umul24(hv[c], (b0 - (64u * c + lane)) & mask);
-                const uint32_t first = wave_sum32(t);                       // D_nn(b0)
-                const uint32_t g = nn == 8 ? h0 : h0 + h1;                  // H_nn[b mod 2^nn]
-                const uint32_t upto = wave_incl_scan(g, lane) - (uint32_t)__builtin_amdgcn_readlane((int)g, 0);
-                if (nb_ == nn) D = first + lane * real - (upto << nn);
-            }
-            const uint32_t Dmin = wave_min32(valid ? D : 0xFFFFFFFFu);
-            const uint32_t pick = wave_min32(valid && D == Dmin ? (nb_ << 8) | bb : 0xFFFFFFFFu);
-            if (lane == 0) atomicMin(&s_best, ((unsigned long long)Dmin << 16) | pick);   // ties: smaller n, then smaller b
-        }
-        __syncthreads();
-        if (wave == 0) {
-            const uint32_t b = (uint32_t)s_best & 0xFFu, n = ((uint32_t)s_best >> 8) & 0xFFu;
-            uint32_t ybits[4];                                     // y < 2^m  <=>  ybits <= m
-#pragma unroll
-            for (int c = 0; c < 4; ++c) ybits[c] = 32u - (uint32_t)__clz((b - (64u * c + lane)) & ((1u << n) - 1u));
-            uint32_t cnt = 0;
-            for (uint32_t j = 0; j <= n; ++j) {
-                uint32_t t = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) t += ybits[c] <= j ? hv[c] : 0u;
-                const uint32_t s = wave_sum32(t);
-                if (lane == j) cnt = s;
-            }
-            const uint32_t best_m = choose_m(cnt, n);
-            if (lane == 0) s_m = best_m;
-        }
-        __syncthreads();
-    }
+    pb_search<DT, LPG>(s_hist, s_present, s_best, s_m, real);
     const uint32_t b = (uint32_t)s_best & 0xFFu, n = ((uint32_t)s_best >> 8) & 0xFFu;
     const uint32_t m = s_m, a = n - m;
     const uint32_t lm = m + (DT == DT_FP16 ? 3u : 0u);
@@ -602,5 +621,6 @@ compress_per_block_kernel(const PbCompressArgs p)
         }
     }
 }
+
 
 }  // namespace enec
