@@ -33,7 +33,9 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950",
 
 def _units():
     units = [("enec_api.o", [SOURCES[0]]), ("enec_api_test.o", ["-DENEC_TEST_HOOKS", SOURCES[0]]),
-             ("enec_per_block.o", [SOURCES[2]]), ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]])]
+             # (no constants kept in registers over a loop with sixteen packers: see enec_per_block.hpp)
+             ("enec_per_block.o", ["-mllvm", "-disable-machine-licm", SOURCES[2]]), 
+             ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]])]
     for lpg in (2, 1, 4):           # lanes per group: group lengths 16, 8, 32
         for dt in (0, 2, 1):
             for logb in (14, 0):    # block size: the default one as a constant, any as an argument

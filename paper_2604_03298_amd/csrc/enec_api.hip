@@ -3,6 +3,7 @@
 #include "enec.h"
 #include "enec_kernels.hpp"
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -170,6 +171,42 @@ uint32_t spin_limit()
     }
 #endif
     return SPIN_LIMIT;
+}
+
+// The next item of a launch of a kernel with deferred stores; a.B is set.  acc / word: the first accumulator and scan word
+// that are still free (tags make their reuse from one launch to the next safe).
+void fill_compress_item(CompressArgs &a, size_t &acc, size_t &word, void *workspace, const void *in, void *out, uint64_t *out_bytes,
+                        size_t n_elems, int dtype)
+{
+    CompressItem &c = a.item[a.n_items++];
+    uint64_t *state = reinterpret_cast<uint64_t *>(static_cast<uint8_t *>(workspace) + WS_STATE);
+    c.nb = (uint32_t)num_blocks(n_elems, a.B);
+    c.in = static_cast<const uint16_t *>(in);
+    c.out = static_cast<uint8_t *>(out);
+    c.out_bytes = out_bytes;
+    c.ws_acc = state + acc;
+    acc += ws_groups(c.nb);
+    c.ws_group = state + word;
+    word += ws_groups(c.nb);
+    c.ws_block = state + word;
+    word += c.nb;
+    c.n_elems = n_elems;
+    c.payload_base = payload_base(n_elems, a.B, dtype);
+    c.tail_base = table_end(n_elems, a.B);
+    c.first = a.total;
+    a.total += c.nb;
+}
+
+template <class Fn>
+void launch_compress(Fn fn, CompressArgs &a, unsigned resident, unsigned threads, size_t lds, hipStream_t s)
+{
+    const unsigned grid = persistent_grid(a.total, resident);
+    a.ncls = grid < 8 ? grid : 8;
+    // The next ticket is drawn while the current block is worked on only if there are blocks for
+    // two rounds: with fewer, an early workgroup would take the block of one that starts a moment later.
+    a.lookahead = a.total >= 2 * grid ? 1u : 0u;
+    a.spin_limit = spin_limit();
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), lds, s, a);
 }
 
 // Dynamic LDS of a decompression workgroup of a 16-bit format, so that a CU works on 65536 elements at a time (the
@@ -573,7 +610,6 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
     }
 
     // ---- one launch per group of tensors that share (m, n - m, L, block size) ----------------
-    uint8_t *ws = static_cast<uint8_t *>(workspace);
     std::vector<char> done(n_items, 0);
     for (size_t i = 0; i < n_items; ++i) {
         if (done[i]) continue;
@@ -585,7 +621,7 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
             continue;
         }
         CompressArgs a;
-        a.ws_ctl = reinterpret_cast<uint32_t *>(ws + WS_CTL);
+        a.ws_ctl = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_CTL);
         a.B = prep[i].B;
         a.logB = ilog2(a.B);
         a.n_items = 0;
@@ -595,24 +631,10 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
             if (done[j] || prep[j].nb == 0 || prep[j].B != a.B || prep[j].prm.m != prep[i].prm.m ||
                 prep[j].prm.n != prep[i].prm.n || prep[j].prm.L != prep[i].prm.L)
                 continue;
-            CompressItem &c = a.item[a.n_items++];
-            c.in = static_cast<const uint16_t *>(items[j].in);
-            c.out = static_cast<uint8_t *>(items[j].out);
-            c.out_bytes = items[j].out_bytes;
-            c.ws_acc = reinterpret_cast<uint64_t *>(ws + WS_STATE) + acc;
-            acc += ws_groups(prep[j].nb);
-            c.ws_group = reinterpret_cast<uint64_t *>(ws + WS_STATE) + word;
-            word += ws_groups(prep[j].nb);
-            c.ws_block = reinterpret_cast<uint64_t *>(ws + WS_STATE) + word;
-            word += prep[j].nb;
-            c.n_elems = items[j].n_elems;
-            c.payload_base = payload_base(items[j].n_elems, a.B, dtype);
-            c.tail_base = table_end(items[j].n_elems, a.B);
-            c.nb = prep[j].nb;
-            c.first = a.total;
+            fill_compress_item(a, acc, word, workspace, items[j].in, items[j].out, items[j].out_bytes, items[j].n_elems, dtype);
+            CompressItem &c = a.item[a.n_items - 1];
             c.b = prep[j].prm.b;
             c.mode = subtract_mode(prep[j].prm.b, prep[j].prm.n, dtype);
-            a.total += c.nb;
             done[j] = 1;
         }
         CompressFn fn = pick_compress(prep[i].prm.m, prep[i].prm.n - prep[i].prm.m, dtype, prep[i].prm.L, a.B);
@@ -624,13 +646,7 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
                            (compress_sm_in_lds(dtype, a.B == 1u << DEFAULT_LOGB) ? a.B : 0);
         const unsigned resident = resident_workgroups((const void *)fn, threads, lds);
         if (resident == 0) return ENEC_E_HIP;
-        const unsigned grid = persistent_grid(a.total, resident);
-        a.ncls = grid < 8 ? grid : 8;
-        // The next ticket is drawn while the current block is worked on only if there are blocks for
-        // two rounds: with fewer, an early workgroup would take the block of one that starts a moment later.
-        a.lookahead = a.total >= 2 * grid ? 1u : 0u;
-        a.spin_limit = spin_limit();
-        hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), lds, s, a);
+        launch_compress(fn, a, resident, threads, lds, s);
     }
     return hipGetLastError() == hipSuccess ? ENEC_OK : ENEC_E_HIP;
 }
@@ -714,7 +730,6 @@ int enec_compress_per_block_batch(const enec_per_block_item *items, size_t n_ite
     hipStream_t s = (hipStream_t)stream;
     // every argument is checked before anything is enqueued
     std::vector<uint32_t> Bs(n_items);
-    size_t need = PB_TICKET_CLASSES * PB_TICKET_STRIDE / 2;      // the ticket counters, in 8-byte words
     uint64_t blocks = 0;
     for (size_t i = 0; i < n_items; ++i) {
         const enec_per_block_item &it = items[i];
@@ -726,24 +741,73 @@ int enec_compress_per_block_batch(const enec_per_block_item *items, size_t n_ite
         if (it.out_capacity < enec_compress_bound_per_block(it.n_elems, dtype, B)) return ENEC_E_CAPACITY;
         if (it.out_bytes && !device_accessible(it.out_bytes)) return ENEC_E_ARG;
         Bs[i] = B;
-        const size_t nb = num_blocks(it.n_elems, B);
-        need += nb + (nb & 1);                                   // look-back words, an even number per tensor
-        blocks += nb;
+        blocks += num_blocks(it.n_elems, B);
     }
     if (blocks > 0xFFFFFFFFull) return ENEC_E_ARG;               // block numbers are 32 bits wide
-    // ticket counters and look-back words behind the accumulators, cleared for this call
-    size_t first = ws_acc_words(workspace_bytes);
-    first += first & 1;                                          // 16-byte aligned for the fill kernel
-    if (ws_state_words(workspace_bytes) < first + need) return ENEC_E_CAPACITY;
     PbCompressFn fn = pick_compress_per_block(dtype, L);
-    if (!fn) return ENEC_E_DTYPE;
+    CompressFn stream_fn = pick_compress_per_block_stream(dtype, L);
+    if (!fn || !stream_fn) return ENEC_E_DTYPE;
+
+    // Tensors of the default block size go through the kernel with deferred stores, up to MAX_BATCH to a launch, in the
+    // order given; its scan words are those of enec_compress, handed out anew by every launch.  The others take the
+    // kernel that places a block at once, whose ticket counters and look-back words (an even number per tensor, behind
+    // the accumulators) are cleared for the call.  So does everything where the workspace has room for these words only.
+    const size_t acc_words = ws_acc_words(workspace_bytes), state_words = ws_state_words(workspace_bytes);
+    auto streamed = [&](size_t i) { return Bs[i] == ENEC_DEFAULT_BLOCK && items[i].n_elems != 0; };
+    bool use_stream = true;
+    for (size_t i = 0, in_launch = 0, groups = 0, words = 0; i < n_items; ++i) {
+        if (!streamed(i)) continue;
+        if (in_launch == (size_t)MAX_BATCH) in_launch = groups = words = 0;
+        const size_t nb = num_blocks(items[i].n_elems, Bs[i]);
+        ++in_launch;
+        groups += ws_groups(nb);
+        words += ws_groups(nb) + nb;
+        if (groups > acc_words || acc_words + words > state_words) use_stream = false;
+    }
+    const size_t first = acc_words + (acc_words & 1);            // 16-byte aligned for the fill kernel
+    size_t need = PB_TICKET_CLASSES * PB_TICKET_STRIDE / 2, need_all = need;      // the ticket counters, in 8-byte words
+    for (size_t i = 0; i < n_items; ++i) {
+        const size_t nb = num_blocks(items[i].n_elems, Bs[i]), words = nb + (nb & 1);
+        need_all += words;
+        if (!(use_stream && streamed(i))) need += words;
+    }
+    if (state_words < first + need_all) return ENEC_E_CAPACITY;
+    std::vector<char> done(n_items, 0);
+    if (use_stream) {
+        CompressArgs a;
+        const size_t lds = 2 * (size_t)pb_image_bytes(L) + ENEC_DEFAULT_BLOCK;
+        for (size_t i = 0; i < n_items;) {
+            for (; i < n_items && !streamed(i); ++i) {}
+            if (i == n_items) break;
+            size_t word = acc_words, acc = 0;
+            a.ws_ctl = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_CTL);
+            a.B = ENEC_DEFAULT_BLOCK;
+            a.logB = DEFAULT_LOGB;
+            a.n_items = a.total = 0;
+            for (; i < n_items && a.n_items < (uint32_t)MAX_BATCH; ++i) {
+                if (!streamed(i)) continue;
+                fill_compress_item(a, acc, word, workspace, items[i].in, items[i].out, items[i].out_bytes, items[i].n_elems, dtype);
+                CompressItem &c = a.item[a.n_items - 1];
+                const size_t tuples = tuple_table_bytes(items[i].n_elems, a.B);
+                c.b = 0;                              // (pads are read as zero words)
+                c.mode = 0;
+                c.tail_base += tuples;
+                c.payload_base += tuples;
+                done[i] = 1;
+            }
+            const unsigned resident = resident_workgroups((const void *)stream_fn, ENEC_DEFAULT_BLOCK / 64, lds);
+            if (resident == 0) return ENEC_E_HIP;
+            launch_compress(stream_fn, a, resident, ENEC_DEFAULT_BLOCK / 64, lds, s);
+        }
+    }
+    if (std::find(done.begin(), done.end(), 0) == done.end()) return hipGetLastError() == hipSuccess ? ENEC_OK : ENEC_E_HIP;
+
     uint64_t *base = reinterpret_cast<uint64_t *>(static_cast<uint8_t *>(workspace) + WS_STATE) + first;
     const uint64_t nvec = need / 2;
     const unsigned fill_grid = (unsigned)((nvec + 255) / 256 < 1024 ? (nvec + 255) / 256 : 1024);
     fill_zero_kernel<<<fill_grid, 256, 0, s>>>(reinterpret_cast<uint4 *>(base), nvec);
     uint64_t *words = base + PB_TICKET_CLASSES * PB_TICKET_STRIDE / 2;
-    uint64_t next_block = 0;        // the data blocks of the call are numbered through, launch after launch
-    std::vector<char> done(n_items, 0);
+    uint64_t next_block = 0;        // their data blocks are numbered through, launch after launch
     for (size_t i0 = 0; i0 < n_items; ++i0) {
         if (done[i0]) continue;
         const enec_per_block_item &it0 = items[i0];

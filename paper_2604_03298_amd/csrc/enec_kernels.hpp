@@ -81,5 +81,8 @@ constexpr int PB_SM_REG_ROWS = 4;               // rows of a thread's raw bytes 
 
 using PbCompressFn = void (*)(const PbCompressArgs);
 PbCompressFn pick_compress_per_block(int dtype, unsigned L);
+// the same for blocks of the default size, with deferred stores (its arguments are those of the one-tuple kernels)
+constexpr uint32_t pb_image_bytes(uint32_t L) { return (1u << DEFAULT_LOGB) / (8u * L) + (1u << DEFAULT_LOGB); }
+CompressFn pick_compress_per_block_stream(int dtype, unsigned L);
 
 }  // namespace enec

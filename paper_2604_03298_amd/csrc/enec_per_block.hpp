@@ -1,15 +1,15 @@
 // ENEC streams with one (b, n, m) per data block: the search of Sec. V-E (Eq. 1-4) runs inside the
 // compress kernel on the exponents of each block's own elements, so a tensor whose blocks differ
 // (zeros, constants, weights of several scales, noise) is coded block by block with the tuple
-// that fits.  Compression only: enec_decompress.hpp reads these streams like any other.  One workgroup per data
-// block, one pass over the tensor:
+// that fits.  Compression only: enec_decompress.hpp reads these streams like any other.  One pass over the tensor:
 //   ticket -> rows -> split -> LDS histogram -> (b, n) by Eq. 1-3 -> m by Eq. 4 -> transform ->
 //   group test -> size (published) -> packing (Alg. 2, widths chosen at run time from the template
-//   instances) -> look-back over the earlier blocks' sizes -> stores.
+//   instances) -> sum of the earlier blocks' sizes -> stores.
 // The widths are run-time values here, so the packers are reached through a switch; the kernel
 // of enec_device.hpp, which knows its widths at compile time, stays the fast path for one tuple
-// per tensor.  (What bounds this kernel is the in-order placement: with every block stored at a place of its own, for
-// timing only, the 405 MB layer takes 145 instead of 222 us.)
+// per tensor.
+// Two kernels: compress_per_block_stream_kernel for the default block size (persistent grid, stores deferred by a block)
+// and compress_per_block_kernel for the others (one workgroup per block, which places its block at once).
 #pragma once
 #include "enec_kernels.hpp"
 
@@ -622,5 +622,421 @@ compress_per_block_kernel(const PbCompressArgs p)
     }
 }
 
+
+// ---------------------------------------------------------------------------------
+// The same streams for blocks of the default size, from a persistent grid with deferred stores: the tickets, scan words and
+// their rules are those of compress_kernel (see "Inter-block scan" in enec_device.hpp).
+//
+// Bound: the in-order placement, then the chain of steps of a block.  A workgroup that places its block at once waits 8 us
+// of 23 for the slowest of the blocks before it, 2 for its ticket and 3 for its rows.  Here the ticket and the rows of the
+// next block travel while a block is worked on, and a block is stored an iteration after its size was published.  Three
+// workgroups per CU (50 KB of LDS: two images of the worst case and the waiting block's raw bytes).  An iteration takes 12 us: rows
+// and split 0.6, counting 1.9, sums and search 1.4, transform 0.7, packing 1.6, start of the waiting block 1.8, loads
+// and stores 3.0, rest 0.9.  us, against one workgroup per block with the former search in brackets:
+// 67e6 elements of mixed blocks 60.3 (79.3), 34e6 Gaussian 34.8 (50.7), 134e6 119.8 (143.3), 405 MB layer 186 (216), fp16
+// 34e6 37.8 (52.5), fp32 56.8 (62.7), 1e6 10.5 (13.1).
+// Looking up the start during the search and storing then, by the other three waves, was slower than all of these (layer
+// 244, mixed blocks 76): the blocks before have not published by then, and the wait for them grows from 1.8 to 5 us.
+// The unit is compiled without the hoisting of constants out of loops: the sixteen packers' constants, kept in registers
+// over the whole loop, cost 4 to 12 spilled registers and 4 % (34e6 elements 40.0).  fp32 has twice the rows in flight
+// and runs two waves per SIMD.
+// ---------------------------------------------------------------------------------
+#define PB_STREAM_WAVES (DT == DT_FP32 ? 2 : 3)
+
+template <int DT, int LPG>
+__global__ void __launch_bounds__((1 << DEFAULT_LOGB) / 64) __attribute__((amdgpu_waves_per_eu(PB_STREAM_WAVES, PB_STREAM_WAVES)))
+compress_per_block_stream_kernel(const CompressArgs p)
+{
+    constexpr uint32_t E = exponent_bits(DT), logB = DEFAULT_LOGB, B = 1u << logB, logC = logB - 3u, T = B / 64u;
+    constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
+    constexpr int RW = DT == DT_FP32 ? 16 : 8;
+    constexpr uint32_t MASK_BYTES = (B >> 6) >> LOG_LPG, IMG = pb_image_bytes(8 * LPG);
+    static_assert(IMG >= PB_HIST_COPIES * PB_HIST_STRIDE * 4 && IMG % 16 == 0, "the histogram copies lie where the image will be");
+
+    // two images (mask | low plane as normalized bytes | high records), the waiting block's raw bytes in element order
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ uint32_t s_hist[256];
+    __shared__ unsigned long long s_present[4], s_best, s_tag, s_off;
+    __shared__ uint32_t s_k[2], s_m, s_status;
+    uint8_t *sm_wait = smem + 2u * IMG;
+
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+
+    const uint32_t home = blockIdx.x % p.ncls;
+    uint32_t *ctl = p.ws_ctl + WS_STRIDE * home;
+    const uint32_t class_blocks = home < p.total ? (p.total - home + p.ncls - 1u) / p.ncls : 0u;
+    const uint32_t class_wgs = (gridDim.x - home + p.ncls - 1u) / p.ncls;
+    uint32_t ticket_base = 0, zero = 0;
+    uint64_t tag0 = 0;
+    bool drawing = true;
+    auto decode_draw = [&](uint32_t raw) -> uint32_t {
+        const uint32_t t = raw - ticket_base;
+        if (t == class_blocks + class_wgs - 1u) {
+            ctl[1] = raw + 1u;
+            for (uint32_t c = home; c < WS_CLASSES; c += p.ncls)
+                *reinterpret_cast<uint64_t *>(p.ws_ctl + WS_STRIDE * c + 2) = tag0;
+        }
+        if (t >= class_blocks) { drawing = false; return NO_BLOCK; }
+        return t * p.ncls + home;
+    };
+    auto item_of = [&](uint32_t kg, uint32_t c) -> uint32_t {
+        while (c + 1u < p.n_items && kg >= p.item[c + 1u].first) ++c;
+        return c;
+    };
+    const uint32_t guess = blockIdx.x;
+    uint32_t ci = item_of(guess, 0);
+    uint4 raw[RW];
+    load_block_rows<DT>(p.item[ci], B, logB, guess - p.item[ci].first, tid, true, logC, raw);
+    auto clear_counts = [&](uint8_t *img) {
+        for (uint32_t i = tid; i < PB_HIST_COPIES * PB_HIST_STRIDE / 4u; i += T) reinterpret_cast<uint4 *>(img)[i] = make_uint4(0, 0, 0, 0);
+    };
+    clear_counts(smem);
+    if (tid == 0) {
+        ticket_base = ctl[1];
+        tag0 = *reinterpret_cast<const uint64_t *>(ctl + 2) + 1u;
+        // the record must have been read before this workgroup's first draw can be counted
+        zero = ticket_base ^ (uint32_t)tag0;
+        asm volatile("v_and_b32 %0, 0, %0" : "+v"(zero));
+        s_k[0] = decode_draw(atomicAdd(ctl + zero, 1u));
+        s_tag = tag0;
+        s_status = 0;
+    }
+    __syncthreads();
+    uint32_t k = __builtin_amdgcn_readfirstlane(s_k[0]);
+    if (k != guess && k != NO_BLOCK) {
+        ci = item_of(k, 0);
+        load_block_rows<DT>(p.item[ci], B, logB, k - p.item[ci].first, tid, true, logC, raw);
+    }
+    const uint64_t tag = (uint64_t)s_tag << 24;
+
+    // wave 1 carries the scan of one tensor
+    uint64_t groups_sum = 0;
+    uint32_t groups_summed = 0, scan_flags = 0, scan_item = NO_BLOCK;
+    auto sum_words = [&](const uint64_t *base, uint32_t count, bool have, uint64_t v, uint32_t &flags) -> uint64_t {
+        const bool need = lane < count;
+        bool ok = !need || (have && (v & ~0xFFFFFFull) == tag);
+        uint32_t spins = 0;
+        while (__builtin_amdgcn_ballot_w64(!ok) != 0) {
+            if (!ok) {
+                v = ld_state(base + lane);
+                ok = (v & ~0xFFFFFFull) == tag;
+            }
+            if (__builtin_amdgcn_ballot_w64(!ok) == 0) break;
+            if (++spins > p.spin_limit) {                                      // never hang
+                flags |= 4u;
+                v = 0;
+                if (lane == 0) st_state(reinterpret_cast<uint64_t *>(p.ws_ctl + 4), tag);
+                break;
+            }
+            spin_pause(spins);
+        }
+        return wave_sum32(need ? (uint32_t)(v & ST_VALUE) : 0u);
+    };
+    auto block_start = [&](const CompressItem &it, uint32_t kb, bool early, uint64_t early_g, uint64_t early_b) -> uint64_t {
+        const uint32_t g = kb >> GROUP_LOG;
+        while (groups_summed < g) {
+            const uint32_t c = g - groups_summed < 64u ? g - groups_summed : 64u;
+            groups_sum += sum_words(it.ws_group + groups_summed, c, early, early_g, scan_flags);
+            groups_summed += c;
+            early = false;
+        }
+        const uint64_t own_group = sum_words(it.ws_block + ((uint64_t)g << GROUP_LOG), kb & (GROUP - 1u), early_b != 0, early_b, scan_flags);
+        return (groups_sum + own_group) << 4;
+    };
+
+    uint32_t pend = NO_BLOCK, pend_item = 0, pend_cnt = 0, pend_S = 0, pend_tuple = 0;
+    auto store_block = [&](const CompressItem &it, uint32_t kb, const uint8_t *img) {
+        const uint32_t n = (pend_tuple >> 8) & 0xFFu, m = pend_tuple >> 16;
+        const uint32_t lm = m + (DT == DT_FP16 ? 3u : 0u);
+        const uint64_t off = s_off;
+        const uint64_t tuples = (64ull + 8ull * ((uint64_t)it.nb + 1u) + 15u) & ~15ull;
+        uint8_t *dst = it.out + it.payload_base + off;
+        const uint32_t shift = (uint32_t)((uintptr_t)dst >> 4) & 7u;     // vectors of the first line that are not ours
+        constexpr uint32_t NSM = B >> 4, NMASK = MASK_BYTES >> 4;
+        const uint32_t nlow = lm << (logB - 7u), hbytes = (uint32_t)LPG * (n - m) * pend_cnt, nall = pend_S >> 4;
+        const uint32_t T2 = lm << (logB - 4u);                           // half of the low plane's length
+        auto packed_vector = [&](uint32_t u) -> uint4 {
+            const uint32_t j = u - NMASK;                                // vector of the low plane (wraps for a mask vector)
+            if (j < nlow) {
+                const uint2 a = *reinterpret_cast<const uint2 *>(img + MASK_BYTES + 8u * j);
+                const uint2 c = *reinterpret_cast<const uint2 *>(img + MASK_BYTES + 8u * j + T2);
+                return make_uint4(byte_perm(c.x, a.x, 0x05010400u), byte_perm(c.x, a.x, 0x07030602u),
+                                  byte_perm(c.y, a.y, 0x05010400u), byte_perm(c.y, a.y, 0x07030602u));
+            }
+            const uint4 o = *reinterpret_cast<const uint4 *>(img + 16u * u);
+            const uint32_t at = 16u * (j - nlow);                        // (huge for the mask)
+            if (u < NMASK || at + 16u <= hbytes) return o;
+            uint32_t w[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                                // zero the padding behind the last record
+                if (at + 4u * i >= hbytes) w[i] = 0;
+                else if (at + 4u * i + 4u > hbytes) w[i] &= (1u << (8u * (hbytes - at - 4u * i))) - 1u;
+            }
+            return make_uint4(w[0], w[1], w[2], w[3]);
+        };
+        int32_t v = (int32_t)tid - (int32_t)shift;
+#pragma unroll
+        for (int i = 0; i < (int)(NSM / T); ++i)                         // ends at most at vector NSM - 1
+            if (i > 0 || v >= 0)
+                st_stream(reinterpret_cast<uint4 *>(dst) + v + i * (int)T, reinterpret_cast<const uint4 *>(sm_wait)[v + i * (int)T]);
+        v += (int32_t)NSM;
+        if (v < (int32_t)NSM) {                                          // the raw bytes' last vectors
+            st_stream(reinterpret_cast<uint4 *>(dst) + v, reinterpret_cast<const uint4 *>(sm_wait)[v]);
+            v += (int32_t)T;
+        }
+        for (; v < (int32_t)nall; v += (int32_t)T) st_stream(reinterpret_cast<uint4 *>(dst) + v, packed_vector((uint32_t)v - NSM));
+        if (tid == 0) {
+            uint64_t *table = reinterpret_cast<uint64_t *>(it.out + 64);
+            table[kb] = off;
+            *reinterpret_cast<uint32_t *>(it.out + tuples + 4ull * kb) = pend_tuple;
+            if (kb == it.nb - 1u) {
+                const uint64_t end = off + pend_S;
+                uint32_t fl = s_status;
+                if (ld_state(reinterpret_cast<const uint64_t *>(p.ws_ctl + 4)) == tag) fl |= 4u;   // somebody gave up
+                const uint32_t status = (fl & 4u) ? 8u : 0u;
+                const uint64_t total = status ? 0ull : it.payload_base + end;
+                table[it.nb] = end;
+                if (((uint64_t)(it.nb + 1u) & 1ull)) table[it.nb + 1u] = 0;          // pad up to the tuple table
+                for (uint32_t i = it.nb; i < ((it.nb + 3u) & ~3u); ++i)              // pad behind the tuple table
+                    *reinterpret_cast<uint32_t *>(it.out + tuples + 4u * i) = 0;
+                uint32_t *h = reinterpret_cast<uint32_t *>(it.out);
+                h[0] = 0x43454E45u;                                                // "ENEC"
+                h[1] = 1u | ((uint32_t)DT << 16) | ((8u * LPG) << 24);             // version, dtype, L
+                h[2] = (uint32_t)it.n_elems; h[3] = (uint32_t)(it.n_elems >> 32);
+                h[4] = B; h[5] = it.nb;
+                h[6] = E << 24;                                                    // (b, n, m) = 0: see the tuple table
+                h[7] = status;
+                h[8] = (uint32_t)total; h[9] = (uint32_t)(total >> 32);
+                h[10] = 1u;                                                        // one tuple per block
+#pragma unroll
+                for (int i = 11; i < 16; ++i) h[i] = 0;
+                if (it.out_bytes) *it.out_bytes = total;
+            }
+        }
+    };
+
+    uint32_t slot = 0;
+    while (k != NO_BLOCK) {
+        uint8_t *img = smem + slot * IMG;
+        const CompressItem &it = p.item[ci];
+        const uint32_t kl = k - it.first;
+
+        uint32_t next_raw = 0;
+        const bool draw_now = tid == 0 && p.lookahead && drawing;
+        if (draw_now) next_raw = atomicAdd(ctl + zero, 1u);
+
+        // ---- a1: split; fp16's three left-over mantissa bits travel in bits 5..7 of X's bytes ----
+        const uint64_t blk0 = (uint64_t)kl << logB;
+        const uint32_t real = it.n_elems - blk0 < B ? (uint32_t)(it.n_elems - blk0) : B;   // elements that are not pads
+        const bool full = real == B;
+        uint32_t X[8][2], SM[8][2];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            uint4 r16;
+            if constexpr (DT == DT_FP32) {
+                const uint4 u = raw[2 * t], v = raw[2 * t + 1];
+                const uint32_t at = ((uint32_t)t << logC) + 8u * tid;
+                r16 = make_uint4(byte_perm(u.y, u.x, 0x07060302u), byte_perm(u.w, u.z, 0x07060302u),
+                                 byte_perm(v.y, v.x, 0x07060302u), byte_perm(v.w, v.z, 0x07060302u));
+                if (at < real)
+                    st_stream(reinterpret_cast<uint4 *>(it.out + it.tail_base + 2u * (blk0 + at)),
+                              make_uint4(byte_perm(u.y, u.x, 0x05040100u), byte_perm(u.w, u.z, 0x05040100u),
+                                         byte_perm(v.y, v.x, 0x05040100u), byte_perm(v.w, v.z, 0x05040100u)));
+            } else {
+                r16 = raw[t];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t d0 = h ? r16.z : r16.x, d1 = h ? r16.w : r16.y;
+                const uint32_t Lb = byte_perm(d1, d0, 0x06040200u);
+                const uint32_t Hb = byte_perm(d1, d0, 0x07050301u);
+                if constexpr (DT == DT_FP16) {
+                    SM[t][h] = (Hb & 0x80808080u) | ((Hb & 0x03030303u) << 5) | ((Lb >> 3) & 0x1F1F1F1Fu);
+                    X[t][h] = ((Hb >> 2) & 0x1F1F1F1Fu) | ((Lb & 0x07070707u) << 5);
+                } else {
+                    SM[t][h] = bfi(0x7F7F7F7Fu, Lb, Hb);
+                    X[t][h] = bfi(0xFEFEFEFEu, Hb << 1, Lb >> 7);
+                }
+            }
+        }
+        if (tid == 0) s_best = ~0ull;
+        __syncthreads();                                                     // the copies are clear
+
+        // ---- Sec. V-E phase 1: exponent counts of the block's own elements ----
+        uint32_t *mine = reinterpret_cast<uint32_t *>(img) + (lane & (PB_HIST_COPIES - 1u)) * PB_HIST_STRIDE;
+        if (full) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) atomicAdd(&mine[(X[t][h] >> (8 * i)) & (DT == DT_FP16 ? 0x1Fu : 0xFFu)], 1u);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (((uint32_t)t << logC) + 8u * tid + i < real)
+                        atomicAdd(&mine[(X[t][i >> 2] >> (8 * (i & 3))) & (DT == DT_FP16 ? 0x1Fu : 0xFFu)], 1u);
+        }
+        __syncthreads();
+        {   // phase 2: the counts of the 256 exponent values, and which occur
+            uint32_t c = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < PB_HIST_COPIES; ++i) c += reinterpret_cast<const uint32_t *>(img)[i * PB_HIST_STRIDE + tid];
+            s_hist[tid] = c;
+            const uint64_t present = __builtin_amdgcn_ballot_w64(c != 0);
+            if (lane == 0) s_present[wave] = present;
+        }
+        __syncthreads();
+        pb_search<DT, LPG>(s_hist, s_present, s_best, s_m, real);
+        const uint32_t b = (uint32_t)s_best & 0xFFu, n = ((uint32_t)s_best >> 8) & 0xFFu;
+        const uint32_t m = s_m, a = n - m;
+        const uint32_t lm = m + (DT == DT_FP16 ? 3u : 0u);
+        uint32_t *img_maskw = reinterpret_cast<uint32_t *>(img);
+        uint8_t *img_low = img + MASK_BYTES;
+        uint8_t *img_high = img_low + (lm << (logB - 3u));
+        const uint32_t fixed = B + MASK_BYTES + (lm << (logB - 3u));
+
+        // ---- a2 transform (in place: X becomes y, fp16 keeps its three bits above), a3 group test ----
+        const uint32_t crep = ((b + (1u << (n - 1))) & 0xFFu) * 0x01010101u;
+        const uint32_t brep = b * 0x01010101u;
+        const uint32_t srep = (1u << (n - 1)) * 0x01010101u;
+        const uint32_t nrep = ((1u << n) - 1u) * 0x01010101u;
+        const uint32_t lrep = ((1u << m) - 1u) * 0x01010101u;
+        const uint32_t arep = ((1u << a) - 1u) * 0x01010101u;
+        if (!full) {                               // pads behave like exponent b: y = 0
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int32_t left = (int32_t)real - (int32_t)(((uint32_t)t << logC) + 8u * tid + 4u * h);
+                    const uint32_t padm = left <= 0 ? 0xFFFFFFFFu : (left >= 4 ? 0u : 0xFFFFFFFFu << (8 * left));
+                    X[t][h] = bfi(padm, brep, X[t][h]);
+                }
+        }
+        uint64_t flagged[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            uint32_t gor = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t x = X[t][h];
+                if constexpr (DT == DT_FP16) x &= 0x1F1F1F1Fu;
+                const uint32_t Y = (bytesub_safe(crep, x) ^ srep) & nrep;
+                gor |= (Y >> m) & arep;
+                if constexpr (DT == DT_FP16) X[t][h] = Y | (X[t][h] & 0xE0E0E0E0u);
+                else X[t][h] = Y;
+            }
+            if constexpr (LPG == 2) gor |= swap_pair(gor);
+            if constexpr (LPG == 4) gor = quad_or(gor);
+            flagged[t] = __builtin_amdgcn_ballot_w64(gor != 0);
+        }
+        put_mask_bits<LPG>(flagged, img, logC, wave, lane);
+        if (tid == 0) s_k[slot ^ 1u] = draw_now ? decode_draw(next_raw) : NO_BLOCK;
+        __syncthreads();
+
+        // wave 1 reads the scan state for the waiting block now and uses it after the packing
+        uint64_t early_g = 0, early_b = 0;
+        if (wave == 1 && pend != NO_BLOCK) {
+            if (scan_item != pend_item) { scan_item = pend_item; groups_sum = 0; groups_summed = 0; scan_flags = 0; }
+            const CompressItem &pit = p.item[pend_item];
+            const uint32_t pg = pend >> GROUP_LOG;
+            if (groups_summed + lane < pg) early_g = ld_state(pit.ws_group + groups_summed + lane);
+            if (lane < (pend & (GROUP - 1u))) early_b = ld_state(pit.ws_block + ((uint64_t)pg << GROUP_LOG) + lane);
+        }
+        // ---- a5 positions, a6: publish this block's size at once ----
+        constexpr uint32_t NWORDS = (B >> 8) >> LOG_LPG;          // 32-bit words of the mask (at most 64)
+        const uint32_t my_word = lane < NWORDS ? img_maskw[lane] : 0u;
+        const uint32_t my_pc = __popc(my_word);
+        const uint32_t my_incl = wave_incl_scan(my_pc, lane);
+        const uint32_t my_excl = my_incl - my_pc;
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_incl, 63);
+        const uint32_t S = (fixed + (uint32_t)LPG * a * cnt + 15u) & ~15u;
+        if (tid == 0) st_state(it.ws_block + kl, tag | (uint64_t)(S >> 4));
+        const uint32_t grp = kl >> GROUP_LOG;
+        const uint32_t members = it.nb - (grp << GROUP_LOG) < GROUP ? it.nb - (grp << GROUP_LOG) : GROUP;
+        uint64_t acc_old = 0;
+        if (tid == 64u && members > 1u)
+            acc_old = __hip_atomic_fetch_add(it.ws_acc + grp, (1ull << 48) | (uint64_t)(S >> 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+        // ---- a4 low plane, a5 one record per masked group ----
+        switch (lm) {
+        case 1: pb_pack_low_from_y<1, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 2: pb_pack_low_from_y<2, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 3: pb_pack_low_from_y<3, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 4: pb_pack_low_from_y<4, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 5: pb_pack_low_from_y<5, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 6: pb_pack_low_from_y<6, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 7: pb_pack_low_from_y<7, DT>(X, lrep, m, img_low, logC, tid); break;
+        case 8: pb_pack_low_from_y<8, DT>(X, lrep, m, img_low, logC, tid); break;
+        default: break;
+        }
+        switch (a) {
+        case 1: pb_pack_records_from_y<1, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 2: pb_pack_records_from_y<2, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 3: pb_pack_records_from_y<3, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 4: pb_pack_records_from_y<4, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 5: pb_pack_records_from_y<5, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 6: pb_pack_records_from_y<6, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 7: pb_pack_records_from_y<7, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        case 8: pb_pack_records_from_y<8, LPG>(X, m, arep, my_word, my_excl, img_high, logC, tid, true); break;
+        default: break;
+        }
+
+        // ---- a6: whoever completes a group publishes its word and clears the accumulator for the next call ----
+        if (tid == 64u && (uint32_t)(acc_old >> 48) == members - 1u) {
+            st_state(it.ws_group + grp, tag | ((acc_old & 0xFFFFFFFFull) + (S >> 4)));
+            if (members > 1u) st_state(it.ws_acc + grp, 0ull);
+        }
+        // ---- a6 (wave 1): the start of the waiting block ----
+        if (wave == 1 && pend != NO_BLOCK) {
+            const uint64_t off = block_start(p.item[pend_item], pend, true, early_g, early_b);
+            if (lane == 0) { s_off = off; s_status = scan_flags; }
+        }
+        __syncthreads();
+
+        // the following block's rows start to travel while the previous block is stored
+        const uint32_t knext = __builtin_amdgcn_readfirstlane(s_k[slot ^ 1u]);
+        uint32_t cnext = ci;
+        if (knext != NO_BLOCK) {
+            cnext = item_of(knext, ci);
+            load_block_rows<DT>(p.item[cnext], B, logB, knext - p.item[cnext].first, tid, true, logC, raw);
+        }
+        // ---- a7: stores of the previous block ----
+        if (pend != NO_BLOCK) store_block(p.item[pend_item], pend, smem + (slot ^ 1u) * IMG);
+        __syncthreads();                                                     // the other image and sm_wait are free
+
+        // this block becomes the waiting one
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            *reinterpret_cast<uint2 *>(sm_wait + ((size_t)t << logC) + 8u * tid) = make_uint2(SM[t][0], SM[t][1]);
+        clear_counts(smem + (slot ^ 1u) * IMG);
+        pend = kl; pend_item = ci; pend_cnt = cnt; pend_S = S; pend_tuple = b | (n << 8) | (m << 16);
+        slot ^= 1u;
+        k = knext;
+        ci = cnext;
+        if (k == NO_BLOCK && !p.lookahead) {           // without lookahead the next ticket is drawn only now
+            if (tid == 0) s_k[slot] = drawing ? decode_draw(atomicAdd(ctl + zero, 1u)) : NO_BLOCK;
+            __syncthreads();
+            k = __builtin_amdgcn_readfirstlane(s_k[slot]);
+            if (k != NO_BLOCK) {
+                ci = item_of(k, ci);
+                load_block_rows<DT>(p.item[ci], B, logB, k - p.item[ci].first, tid, true, logC, raw);
+            }
+        }
+    }
+
+    // ---- drain: the last block of this workgroup ----
+    if (pend != NO_BLOCK) {
+        if (wave == 1) {
+            if (scan_item != pend_item) { scan_item = pend_item; groups_sum = 0; groups_summed = 0; scan_flags = 0; }
+            const uint64_t off = block_start(p.item[pend_item], pend, false, 0, 0);
+            if (lane == 0) { s_off = off; s_status = scan_flags; }
+        }
+        __syncthreads();
+        store_block(p.item[pend_item], pend, smem + (slot ^ 1u) * IMG);
+    }
+}
 
 }  // namespace enec
