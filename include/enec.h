@@ -193,7 +193,7 @@ int enec_decompress_with_header(const void *in, size_t in_bytes, const void *hos
                                 size_t n_elems, uint32_t *status, void *stream);
 
 /* Decompress several streams with one launch per (dtype, group length, block size) and sixteen streams, whatever
- * their tuples; fields as the arguments of
+ * their tuples (streams of a few blocks join the launch of a larger block size); fields as the arguments of
  * enec_decompress_with_header.  Fully asynchronous. */
 typedef struct {
     const void *in;             /* DEVICE */

@@ -899,21 +899,30 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
         }
     }
     // Streams of one element format, group length and block size share a launch (up to MAX_BATCH each),
-    // whether they have one tuple or one tuple per block and whatever the tuples are.
+    // whether they have one tuple or one tuple per block and whatever the tuples are.  A stream of at most JOIN blocks
+    // joins a launch of larger blocks too: each of its blocks takes the place of a large one, 8 us of one of the device's
+    // 1024 places, where a launch of their own takes 4 us of all of them.  A decoder layer with its two norm vectors, us:
+    // hidden size 512 10.9 -> 7.2, 1024 12.5 -> 8.7, 2048 35.9 -> 31.8, 4096 120.9 -> 118.1.
+    constexpr uint32_t JOIN = 16;
     std::vector<char> done(n_items, 0);
     for (size_t i = 0; i < n_items; ++i) {
         if (done[i]) continue;
         if (hdr[i].nb == 0) { done[i] = 1; continue; }
         const Header &h0 = hdr[i];
-        const unsigned threads = h0.B / 64 < 64 ? 64 : h0.B / 64;
+        uint32_t B = h0.B;
+        for (size_t j = i; h0.nb <= JOIN && j < n_items; ++j)
+            if (!done[j] && hdr[j].nb != 0 && hdr[j].dtype == h0.dtype && hdr[j].prm.L == h0.prm.L && hdr[j].B > B) B = hdr[j].B;
+        const unsigned threads = B / 64 < 64 ? 64 : B / 64;
         DecompressArgs a;
-        a.B = h0.B;
-        a.logB = ilog2(h0.B);
-        uint32_t items_in = 0, widest = 0;
+        a.B = B;
+        a.logB = ilog2(B);
+        bool mixed = false;
+        uint32_t items_in = 0;
         uint64_t blocks = 0;
+        size_t packed = 0;       // the packed part of the widest block of the launch: mask | low plane | high records | padding
         for (size_t j = i; j < n_items && items_in < (uint32_t)MAX_BATCH; ++j) {
             const Header &h = hdr[j];
-            if (done[j] || h.nb == 0 || h.B != h0.B || h.dtype != h0.dtype || h.prm.L != h0.prm.L ||
+            if (done[j] || h.nb == 0 || h.dtype != h0.dtype || h.prm.L != h0.prm.L || (h.B != B && (h.B > B || h.nb > JOIN)) ||
                 (blocks + h.nb) * threads > 0xFFFFFFFFull)            // a grid has fewer than 2^32 threads
                 continue;
             const size_t tuples = h.per_block ? tuple_table_bytes(items[j].n_elems, h.B) : 0;
@@ -928,9 +937,11 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
             d.payload_base = payload_base(d.n_elems, h.B, h.dtype) + tuples;
             d.payload_bytes = h.total - d.payload_base;
             d.status = items[j].status;
+            d.logB = ilog2(h.B);
+            mixed |= h.B != B;
             std::memcpy(d.hdr, items[j].host_header, sizeof d.hdr);
             const uint32_t bits = h.per_block ? 8u : h.prm.n + (h.dtype == ENEC_FP16 ? 3u : 0u);
-            if (bits > widest) widest = bits;
+            packed = std::max(packed, (size_t)h.B / (8 * h.prm.L) + (size_t)bits * h.B / 8 + 16);
             blocks += h.nb;
             done[j] = 1;
         }
@@ -938,12 +949,10 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
             a.first[j] = 0xFFFFFFFFu;
             a.item[j] = a.item[0];
         }
-        DecompressFn fn = pick_decompress(h0.dtype, h0.prm.L);
+        DecompressFn fn = pick_decompress(h0.dtype, h0.prm.L, mixed);
         if (!fn) return ENEC_E_FORMAT;
-        // the packed part of the widest block of the launch: mask | low plane | high records | padding
-        const size_t packed = (size_t)h0.B / (8 * h0.prm.L) + (size_t)widest * h0.B / 8 + 16;
         size_t lds = packed + (h0.dtype == ENEC_FP32 ? 16 * threads : 0);
-        if (h0.dtype != ENEC_FP32 && lds < decompress_lds_floor(h0.B)) lds = decompress_lds_floor(h0.B);
+        if (h0.dtype != ENEC_FP32 && lds < decompress_lds_floor(B)) lds = decompress_lds_floor(B);
         a.turn_at = (uint32_t)packed;
         hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(threads), lds, s, a);
     }

@@ -17,8 +17,9 @@
 // The widths (m, n) are run-time values, uniform over the workgroup: the unpackers are reached through a
 // switch over eight low-plane widths and eight record widths.  So the streams of a call that differ only in
 // their tuples share a launch (sixteen vectors of 100001 elements with tuples of their own: 7 instead of 16 us).
-// Block sizes don't mix: a decoder layer takes one launch for its matrices and one of 4 us for its norm vectors,
-// whose default block size is their length.
+// A launch has the threads and the LDS of its largest block size; the blocks of streams with smaller ones join it as
+// long as they are few (enec_decompress_batch), for each takes the place of a large one while it runs.  So the norm
+// vectors of a decoder layer, whose default block size is their length, need no launch of 4 us of their own.
 //
 // The decoded elements leave as streaming stores, whatever their number.  Alone that is faster at every size; a reader
 // right behind finds less of them in the caches.  Decode and reader together, streaming / plain stores / the kernel
@@ -81,17 +82,15 @@ __device__ __forceinline__ void exchange_in_wave()
 #define DEC_WAVES_MIN (DT == DT_FP32 ? 3 : 4)
 #define DEC_WAVES_MAX (DT == DT_FP32 ? 3 : 8)
 
-template <int DT, int LPG>
+// MIXED: the streams' block sizes differ.  (In the instances for one block size it stays an argument: looked up with the
+// stream, it cost fp32 1 to 2 % and the 16-bit formats the eighth wave per SIMD, 12 % in blocks of 2048.)
+template <int DT, int LPG, bool MIXED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WAVES_MIN, DEC_WAVES_MAX))) decompress_kernel(const DecompressArgs p)
 {
     constexpr uint32_t E = exponent_bits(DT);
     constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
     extern __shared__ __align__(16) uint8_t smem[];      // the packed part as it is in the stream
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const uint32_t B = p.B, logC = p.logB - 3u;
-    const uint32_t nact = B >> 6, threads = nact < 64u ? 64u : nact;
-    const bool active = tid < nact;
-    const uint32_t mask_bytes = (B >> 6) >> LOG_LPG;                  // B / (8 L)
     // the stream this block belongs to (the blocks of the launch's streams are numbered through; `first` of
     // the entries that are not used is beyond every block)
     uint32_t ti = 0;
@@ -100,6 +99,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
         if (blockIdx.x >= p.first[i]) ti = i;
     const DecompressItem &it = p.item[ti];
     const uint32_t k = blockIdx.x - p.first[ti];
+    const uint32_t logB = MIXED ? it.logB : p.logB, B = MIXED ? 1u << logB : p.B, logC = logB - 3u;
+    const uint32_t nact = B >> 6, threads = MIXED ? blockDim.x : nact < 64u ? 64u : nact;     // those that unpack / that load
+    const bool active = tid < nact;
+    const uint32_t mask_bytes = (B >> 6) >> LOG_LPG;                  // B / (8 L)
 
     // d1: header as configured, tuple (in the tuple table, or in the header), offsets
     const uint32_t *hd = reinterpret_cast<const uint32_t *>(it.in);
@@ -139,7 +142,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
     // would write half of each 128-byte line it touches, which a plain copy shows at 3.4 instead of 6.0 TB/s.  So
     // the upper halves change lanes through LDS, and lane i stores elements 4 i .. 4 i + 3 of the first, then of
     // the second 256 elements; it loads the lower halves of those.
-    const uint64_t blk0 = (uint64_t)k << p.logB;
+    const uint64_t blk0 = (uint64_t)k << logB;
     uint2 tl[DT == DT_FP32 ? 16 : 1];
     const uint32_t col4 = 8u * (tid & ~63u) + 4u * lane;                  // its column in the first of the two
     if constexpr (DT == DT_FP32) {
@@ -153,7 +156,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
     }
     wait_loads();
     __syncthreads();
-    if (DT != DT_FP32 && !active) return;
+    // (a wave of fp32 stays whole, its lanes exchange what they have)
+    if (DT == DT_FP32 ? MIXED && (tid & ~63u) >= nact : !active) return;
 
     // d2: mask words and their exclusive popcount prefix (a wave scan per wave)
     const uint8_t *img_low = smem + mask_bytes;

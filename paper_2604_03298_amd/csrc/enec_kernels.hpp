@@ -23,7 +23,7 @@ ENEC_TABLES(dt2)
 #undef ENEC_TABLES
 
 // Decompression (enec_decompress.hpp, compiled in enec_decompress.hip).  One launch takes up to MAX_BATCH
-// streams of one element format, group length and block size, whatever their tuples.
+// streams of one element format and group length, whatever their tuples.
 struct DecompressItem {
     const uint8_t *in;
     void *out;
@@ -34,18 +34,19 @@ struct DecompressItem {
     uint64_t payload_bytes;     // total_bytes - payload_base
     uint32_t *status;           // device-accessible or null: set to 7 (format error) when a block is left undecoded
     uint32_t tuple_stride;      // bytes from a block's tuple to the next one's: 4, or 0 if one tuple holds for all
+    uint32_t logB;              // log2 of the data-block size
     uint32_t hdr[11];           // the header the launch was configured from
 };
 
 struct DecompressArgs {
     uint32_t first[MAX_BATCH];  // number of each stream's first data block among the blocks of the launch
-    uint32_t B, logB;
+    uint32_t B, logB;           // the block size if all streams have the same
     uint32_t turn_at;           // fp32: byte offset in the dynamic LDS where upper halves change lanes (behind the packed part)
     DecompressItem item[MAX_BATCH];
 };
 
 using DecompressFn = void (*)(const DecompressArgs);
-DecompressFn pick_decompress(int dtype, unsigned L);
+DecompressFn pick_decompress(int dtype, unsigned L, bool mixed_block_sizes);
 
 // Compression with one tuple per data block (enec_per_block.hpp, compiled in enec_per_block.hip).
 // LDS copies of the block histogram in the compress kernel, and their distance in words
