@@ -4,7 +4,7 @@ libenec_test.so is the same library with ENEC_TEST_HOOKS defined for the host co
 variable ENEC_SPIN_LIMIT lowers the bound of the scan's waits, which the tests of that bound need.
 
 The host code (csrc/enec_api.hip, csrc/enec_pipeline.hip), the compression kernels for one tuple per data block
-(csrc/enec_per_block.hip), the decompression kernels (csrc/enec_decompress.hip) and the eighteen tables of
+(csrc/enec_per_block.hip) and for tensors of one block (csrc/enec_single.hip), the decompression kernels (csrc/enec_decompress.hip) and the eighteen tables of
 compression kernels (csrc/enec_kernels.hip, once per element format, group length and kind of block size) are compiled
 side by side into _build/*.o and linked into libenec.so.
 """
@@ -22,9 +22,10 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 SOURCES = [os.path.join(CSRC, "enec_api.hip"), os.path.join(CSRC, "enec_kernels.hip"),
            os.path.join(CSRC, "enec_per_block.hip"), os.path.join(CSRC, "enec_pipeline.hip"),
-           os.path.join(CSRC, "enec_decompress.hip")]
+           os.path.join(CSRC, "enec_decompress.hip"), os.path.join(CSRC, "enec_single.hip")]
 HEADERS = [os.path.join(CSRC, "enec_device.hpp"), os.path.join(CSRC, "enec_kernels.hpp"),
            os.path.join(CSRC, "enec_per_block.hpp"), os.path.join(CSRC, "enec_decompress.hpp"),
+           os.path.join(CSRC, "enec_single.hpp"),
            os.path.join(ROOT, "include", "enec.h")]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-ffp-contract=off",
@@ -35,7 +36,8 @@ def _units():
     units = [("enec_api.o", [SOURCES[0]]), ("enec_api_test.o", ["-DENEC_TEST_HOOKS", SOURCES[0]]),
              # (no constants kept in registers over a loop with sixteen packers: see enec_per_block.hpp)
              ("enec_per_block.o", ["-mllvm", "-disable-machine-licm", SOURCES[2]]), 
-             ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]])]
+             ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]]),
+             ("enec_single.o", [SOURCES[5]])]
     for lpg in (2, 1, 4):           # lanes per group: group lengths 16, 8, 32
         for dt in (0, 2, 1):
             for logb in (14, 0):    # block size: the default one as a constant, any as an argument

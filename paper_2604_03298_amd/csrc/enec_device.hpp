@@ -609,8 +609,8 @@ __device__ __forceinline__ void unpack_record_row(const uint8_t *img_high, uint3
 
 // a1: 128-bit loads of the 8 rows of data block k (pad elements beyond the tensor's end); a
 // thread's 8 elements of a row are one vector (16-bit formats) or two (fp32)
-template <int DT>
-__device__ __forceinline__ void load_block_rows(const CompressItem &p, uint32_t B, uint32_t logB, uint32_t k,
+template <int DT, class Item>
+__device__ __forceinline__ void load_block_rows(const Item &p, uint32_t B, uint32_t logB, uint32_t k,
                                                 uint32_t tid, bool active, uint32_t logC,
                                                 uint4 (&raw)[DT == DT_FP32 ? 16 : 8])
 {

@@ -1,0 +1,84 @@
+"""Tensors of one data block: a launch takes them whatever their tuples and block sizes.  Edges of vectors, rows and blocks, windows
+at the ends of the exponent range, range errors of one tensor among others, more tensors than a launch takes, and tensors of one
+block beside larger ones that they share a kernel with; against the oracle, byte for byte."""
+import numpy as np
+import pytest
+
+from test_gpu_compress_edges import EXP, SHIFT, _tensor
+from test_gpu_dtypes import gpu, BF16, FP16, FP32, WORD  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(gpu, oracle, dtype, jobs):
+    """jobs: (tensor, params, block size); every stream against the oracle's."""
+    torch, enec = gpu.torch, gpu.enec
+    wide = np.int32 if dtype == FP32 else np.int16
+    srcs = [torch.from_numpy(np.ascontiguousarray(w).view(wide)).cuda() for w, _, _ in jobs]
+    caps = [enec.compress_bound(w.size, dtype, B) for w, _, B in jobs]
+    outs = [torch.full((c + 64,), 0xA5, dtype=torch.uint8, device="cuda") for c in caps]
+    sizes = torch.full((len(jobs),), -1, dtype=torch.int64, device="cuda")
+    ws = enec.new_workspace(sum(w.size for w, _, _ in jobs) + 32768 * len(jobs), 2048)
+    for _ in range(2):
+        assert enec.compress_batch(srcs, [p for _, p, _ in jobs], outs, ws, block_sizes=[B for _, _, B in jobs],
+                                   out_bytes=[sizes[i:i + 1] for i in range(len(jobs))], dtype=dtype) == enec.OK
+    torch.cuda.synchronize()
+    for (w, p, B), out, size, cap in zip(jobs, outs, sizes.tolist(), caps):
+        rc, want = oracle.compress(w, p, B, dtype=dtype)
+        got = out.cpu().numpy()
+        assert (got[cap:] == 0xA5).all()
+        if rc == enec.E_RANGE:
+            info = enec.stream_info(got[:64])
+            assert info["status"] == enec.E_RANGE and info["total_bytes"] == 0 and size == 0, (w.size, p, B)
+        else:
+            assert rc == 0 and size == want.size and np.array_equal(got[:size], want), (w.size, p, B)
+
+
+@pytest.mark.parametrize("L", [8, 16, 32])
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+def test_tensors_of_one_block(gpu, oracle, dtype, L):
+    rng = np.random.default_rng(10 * dtype + L)
+    full = 5 if dtype == FP16 else 8
+    windows = [(3, 10), (0, 6), (24, 31), (0, 31)] if dtype == FP16 else [(100, 118), (0, 11), (240, 255), (0, 255)]
+    jobs, i = [], 0
+    for B in (2048, 4096, 8192, 16384, 32768):
+        if not (128 * L <= B <= 2048 * L):
+            continue
+        for n in (1, 7, 8, B // 8 - 1, B // 8 + 3, 5 * (B // 8) + 17, B - 1, B):
+            lo, hi = windows[i % 4]
+            w = _tensor(rng, dtype, n, lo, hi, (0.0, 0.03, 0.5, 1.0)[(i // 4) % 4])
+            b, nw, m, _ = oracle.tune(w, dtype)
+            jobs.append((w, (b, full if i % 4 == 3 else nw, m, L), B))
+            if i % 4 == 1:                               # an exponent outside a window that is clear of the ends, or touches them
+                bad = w.copy()
+                keep = WORD[dtype](~(EXP[dtype] << SHIFT[dtype]) & np.iinfo(WORD[dtype]).max)
+                bad[n // 2] = (bad[n // 2] & keep) | (WORD[dtype](EXP[dtype]) << WORD[dtype](SHIFT[dtype]))
+                jobs.append((bad, (b, nw, m, L), B))
+            i += 1
+    assert len(jobs) > 32
+    _run(gpu, oracle, dtype, jobs)
+    for j in jobs[:6]:
+        _run(gpu, oracle, dtype, [j])
+
+
+@pytest.mark.parametrize("n", range(1, 9))
+def test_every_width_pair(gpu, oracle, n):
+    rng = np.random.default_rng(n)
+    for dtype in (BF16, FP16, FP32):
+        if n > (5 if dtype == FP16 else 8):
+            continue
+        b = 1 << (n - 1) if dtype == FP16 else 120
+        lo, hi = (0, EXP[dtype]) if n == (5 if dtype == FP16 else 8) else (max(0, b - (1 << (n - 1)) + 1), min(EXP[dtype], b + (1 << (n - 1))))
+        jobs = [(_tensor(rng, dtype, 3000 + 64 * m, lo, hi, 0.3), (b, n, m, L), 4096) for m in range(n + 1) for L in (8, 16, 32)]
+        _run(gpu, oracle, dtype, jobs)
+
+
+def test_beside_larger_tensors(gpu, oracle):
+    """One-block tensors that share (m, n, L, block size) with a tensor of more blocks go through its launch, the others don't."""
+    rng = np.random.default_rng(3)
+    jobs = []
+    for i in range(40):
+        B = (16384, 4096)[i % 2]
+        w = _tensor(rng, BF16, (B - 5, 3 * B + 1, 77, B, 9 * B)[i % 5], 100 + i % 3, 118, 0.02)
+        jobs.append((w, (115, 5, 2 + i % 3, 16), B))
+    _run(gpu, oracle, BF16, jobs)
