@@ -263,7 +263,7 @@ private:
 // made by the first call that tunes, after the runtime has started, so that it ends before the runtime does
 CountSlots &count_slots() { static CountSlots slots; return slots; }
 
-unsigned bit_length(unsigned v) { unsigned r = 0; for (; v; v >>= 1) ++r; return r; }
+unsigned bit_length(unsigned v) { return v ? 32u - (unsigned)__builtin_clz(v) : 0u; }
 
 // ---- Sec. V-E phases 1-3 on a 256-bin exponent histogram -------------------------------------
 struct Search {
@@ -278,6 +278,9 @@ struct Search {
 // priced by Eq. 3 in exact integers, sum of count * y with y from Eq. 2; the cheapest wins, then the
 // narrower, then the smaller centre.  Afterwards the elements are counted by the bit length of their y,
 // which is all phase 3 needs.  False for an empty histogram.
+// With the width fixed, the cost D(b) of the next centre follows from the one before: every y grows by one, and those of
+// the values congruent to b + 1 modulo 2^n fall from 2^n - 1 to 0, so D(b + 1) = D(b) + total - 2^n H[(b + 1) mod 2^n] with
+// the counts H folded modulo 2^n (unsigned arithmetic, exact).  Two or three widths occur among the centres.
 bool centre_and_width(const uint64_t *hist, unsigned nmax, Search &r)
 {
     r.lo = 256; r.hi = 0; r.total = 0;
@@ -288,19 +291,29 @@ bool centre_and_width(const uint64_t *hist, unsigned nmax, Search &r)
         r.total += hist[x];
     }
     if (r.total == 0) return false;
-    auto key_of = [&](unsigned b) {
+    auto width_of = [&](unsigned b) {
         const unsigned need_below = bit_length(b - r.lo);                       // y = b - x, largest for x = l
         const unsigned need_above = r.hi > b ? bit_length(r.hi - b - 1u) : 0u;  // y = 2^n - (x - b)
-        unsigned n = (need_below > need_above ? need_below : need_above) + 1u;
-        if (n > nmax) n = nmax;
-        uint64_t cost = 0;
-        for (unsigned x = r.lo; x <= r.hi; ++x) cost += hist[x] * (uint64_t)((b - x) & ((1u << n) - 1u));
-        return std::make_tuple(cost, n, b);
+        const unsigned n = (need_below > need_above ? need_below : need_above) + 1u;
+        return n < nmax ? n : nmax;
     };
-    auto best = key_of(r.lo);
-    for (unsigned b = r.lo + 1; b <= r.hi; ++b) {
-        const auto k = key_of(b);
-        if (k < best) best = k;                   // lexicographic: cost, then width, then centre
+    unsigned widths = 0;
+    for (unsigned b = r.lo; b <= r.hi; ++b) widths |= 1u << width_of(b);
+    auto best = std::make_tuple(~(uint64_t)0, 0u, 0u);
+    for (unsigned n = 1; n <= nmax; ++n) {
+        if (!(widths >> n & 1u)) continue;
+        const unsigned mask = (1u << n) - 1u;
+        uint64_t folded[256] = {}, cost = 0;
+        for (unsigned x = r.lo; x <= r.hi; ++x) {
+            folded[x & mask] += hist[x];
+            cost += hist[x] * (uint64_t)((r.lo - x) & mask);
+        }
+        for (unsigned b = r.lo; b <= r.hi; ++b) {
+            if (b != r.lo) cost += r.total - (folded[b & mask] << n);
+            if (width_of(b) != n) continue;
+            const auto k = std::make_tuple(cost, n, b);
+            if (k < best) best = k;               // lexicographic: cost, then width, then centre
+        }
     }
     r.n = std::get<1>(best);
     r.b = std::get<2>(best);

@@ -8,6 +8,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
+from array import array
 
 import numpy as np
 
@@ -62,6 +64,15 @@ class OffloadItem(C.Structure):
                 ("n_elems", C.c_size_t), ("status", C.c_void_p)]
 
 
+# Item arrays are packed in one go and handed over as bytes: filling a ctypes array costs 1.5 us per tensor, as much as the
+# whole call in the library.
+_COMPRESS_ITEM = struct.Struct("=QQI4xQQQQ")
+_PER_BLOCK_ITEM = struct.Struct("=QQI4xQQQ")
+_TUNE_ITEM = struct.Struct("=QQ")
+assert (_COMPRESS_ITEM.size, _PER_BLOCK_ITEM.size, _TUNE_ITEM.size) == (C.sizeof(CompressItem), C.sizeof(PerBlockItem), C.sizeof(TuneItem))
+_U32 = 0xFFFFFFFF
+
+
 class EnecError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -94,7 +105,7 @@ def lib():
         L.enec_workspace_init.restype = C.c_int
         L.enec_workspace_init.argtypes = [vp, sz, vp]
         L.enec_compress.restype = C.c_int
-        L.enec_compress.argtypes = [vp, sz, C.c_int, u32, C.POINTER(Params), vp, sz, vp, vp, sz, vp]
+        L.enec_compress.argtypes = [vp, sz, C.c_int, u32, vp, vp, sz, vp, vp, sz, vp]
         L.enec_compress_static.restype = C.c_int
         L.enec_compress_static.argtypes = [vp, sz, C.c_int, u32, C.POINTER(Params), vp, sz, vp, vp]
         L.enec_decompress.restype = C.c_int
@@ -108,9 +119,9 @@ def lib():
         L.enec_compress_per_block.restype = C.c_int
         L.enec_compress_per_block.argtypes = [vp, sz, C.c_int, C.c_uint32, C.c_uint32, vp, sz, vp, vp, sz, vp]
         L.enec_compress_per_block_batch.restype = C.c_int
-        L.enec_compress_per_block_batch.argtypes = [C.POINTER(PerBlockItem), sz, C.c_int, C.c_uint32, vp, sz, vp]
+        L.enec_compress_per_block_batch.argtypes = [vp, sz, C.c_int, C.c_uint32, vp, sz, vp]
         L.enec_tune_batch.restype = C.c_int
-        L.enec_tune_batch.argtypes = [C.POINTER(TuneItem), sz, C.c_int, C.c_uint32, C.POINTER(Params), u64p, vp, sz, vp]
+        L.enec_tune_batch.argtypes = [vp, sz, C.c_int, C.c_uint32, C.POINTER(Params), vp, vp, sz, vp]
         L.enec_tune_sampled.restype = C.c_int
         L.enec_tune_sampled.argtypes = [vp, sz, C.c_int, C.c_uint32, C.POINTER(Params), u64p, vp, sz, vp]
         L.enec_compress_sampled.restype = C.c_int
@@ -126,7 +137,7 @@ def lib():
         L.enec_copy.restype = C.c_int
         L.enec_copy.argtypes = [vp, vp, sz, vp]
         L.enec_compress_batch.restype = C.c_int
-        L.enec_compress_batch.argtypes = [C.POINTER(CompressItem), sz, C.c_int, vp, sz, vp]
+        L.enec_compress_batch.argtypes = [vp, sz, C.c_int, vp, sz, vp]
         L.enec_decompress_batch.restype = C.c_int
         L.enec_decompress_batch.argtypes = [C.POINTER(DecompressItem), sz, vp]
         L.enec_pipeline_create.restype = C.c_int
@@ -152,14 +163,33 @@ def _check(rc: int, where: str):
         raise EnecError(rc, where)
 
 
+_torch = None
+
+
 def _stream_handle(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    """The handle of a torch stream (None: the current one of the current device)."""
+    if stream is not None:
+        return stream.cuda_stream
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    raw = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None and _torch.cuda.is_initialized():
+        return raw(_torch._C._cuda_getDevice())          # without the stream object, which takes 3 us to make
+    return _torch.cuda.current_stream().cuda_stream
 
 
 def _params(p) -> Params:
     return p if isinstance(p, Params) else Params(*[int(v) for v in p])
+
+
+def _params_bytes(p) -> bytes:
+    """The four bytes of an enec_params."""
+    if type(p) is tuple and len(p) == 4:
+        b, n, m, L = p
+        return bytes((int(b) & 255, int(n) & 255, int(m) & 255, int(L) & 255))
+    return bytes(_params(p))
 
 
 def dtype_of(t, dtype=None) -> int:
@@ -249,12 +279,11 @@ def compress(src, params, out, workspace, block_size: int = 0, out_bytes=None, s
     n = src.numel() if n_elems is None else n_elems
     dt = dtype_of(src, dtype)
     assert src.element_size() == (4 if dt == FP32 else 2)
-    pp = C.byref(_params(params)) if params is not None else None
-    ob = C.c_void_p(out_bytes.data_ptr()) if out_bytes is not None else None
+    pp = _params_bytes(params) if params is not None else None
+    ob = out_bytes.data_ptr() if out_bytes is not None else None
     return int(lib().enec_compress(
-        C.c_void_p(src.data_ptr()), n, dt, block_size, pp, C.c_void_p(out.data_ptr()),
-        out.numel() * out.element_size(), ob, C.c_void_p(workspace.data_ptr()),
-        workspace.numel() * workspace.element_size(), _stream_handle(stream)))
+        src.data_ptr(), n, dt, block_size, pp, out.data_ptr(), out.numel() * out.element_size(), ob,
+        workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream_handle(stream)))
 
 
 STATIC_SCRATCH_BYTES = 1 << 20
@@ -283,11 +312,10 @@ def compress_per_block(src, out, workspace, block_size: int = 0, out_bytes=None,
     exponents.  out: device uint8 tensor of >= compress_bound_per_block bytes."""
     n = src.numel() if n_elems is None else n_elems
     dt = dtype_of(src, dtype)
-    ob = C.c_void_p(out_bytes.data_ptr()) if out_bytes is not None else None
+    ob = out_bytes.data_ptr() if out_bytes is not None else None
     return int(lib().enec_compress_per_block(
-        C.c_void_p(src.data_ptr()), n, dt, block_size, group_length, C.c_void_p(out.data_ptr()),
-        out.numel() * out.element_size(), ob, C.c_void_p(workspace.data_ptr()),
-        workspace.numel() * workspace.element_size(), _stream_handle(stream)))
+        src.data_ptr(), n, dt, block_size, group_length, out.data_ptr(), out.numel() * out.element_size(), ob,
+        workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream_handle(stream)))
 
 
 def compress_per_block_batch(srcs, outs, workspace, out_bytes=None, stream=None, dtype: int | None = None,
@@ -295,17 +323,14 @@ def compress_per_block_batch(srcs, outs, workspace, out_bytes=None, stream=None,
     """Enqueues enec_compress_per_block_batch: the tensors of one block size share a launch.  out_bytes: None or
     one device int64 tensor (or None) per tensor; block_sizes: None (defaults) or one block size per tensor."""
     n = len(srcs)
-    items = (PerBlockItem * max(n, 1))()
+    pack, packed = _PER_BLOCK_ITEM.pack, []
     for i in range(n):
-        items[i].src = srcs[i].data_ptr()
-        items[i].n_elems = srcs[i].numel()
-        items[i].block_size = block_sizes[i] if block_sizes is not None else 0
-        items[i].out = outs[i].data_ptr()
-        items[i].out_capacity = outs[i].numel() * outs[i].element_size()
+        src, out = srcs[i], outs[i]
         ob = out_bytes[i] if out_bytes is not None else None
-        items[i].out_bytes = ob.data_ptr() if ob is not None else None
+        packed.append(pack(src.data_ptr(), src.numel(), block_sizes[i] & _U32 if block_sizes is not None else 0, out.data_ptr(),
+                           out.numel() * out.element_size(), ob.data_ptr() if ob is not None else 0))
     dt = dtype_of(srcs[0], dtype) if n else (BF16 if dtype is None else dtype)
-    return int(lib().enec_compress_per_block_batch(items, n, dt, group_length, C.c_void_p(workspace.data_ptr()),
+    return int(lib().enec_compress_per_block_batch(b"".join(packed), n, dt, group_length, workspace.data_ptr(),
                                                    workspace.numel() * workspace.element_size(), _stream_handle(stream)))
 
 
@@ -320,11 +345,9 @@ def decompress_with_header(stream_buf, host_header, out, n_elems: int | None = N
     """status: None, or a device / pinned-host int32 tensor holding 0; the kernel stores E_FORMAT there if it
     leaves a data block undecoded."""
     n = out.numel() if n_elems is None else n_elems
-    hdr = np.frombuffer(bytes(host_header[:HEADER_BYTES]), dtype=np.uint8).copy()
     return int(lib().enec_decompress_with_header(
-        C.c_void_p(stream_buf.data_ptr()), stream_buf.numel() * stream_buf.element_size(),
-        hdr.ctypes.data, C.c_void_p(out.data_ptr()), n,
-        C.c_void_p(status.data_ptr()) if status is not None else None, _stream_handle(stream)))
+        stream_buf.data_ptr(), stream_buf.numel() * stream_buf.element_size(), bytes(host_header[:HEADER_BYTES]), out.data_ptr(), n,
+        status.data_ptr() if status is not None else None, _stream_handle(stream)))
 
 
 def compress_batch(srcs, params, outs, workspace, block_sizes=None, out_bytes=None, stream=None,
@@ -334,18 +357,14 @@ def compress_batch(srcs, params, outs, workspace, block_sizes=None, out_bytes=No
     of one-u64 device-accessible tensors."""
     n = len(srcs)
     dt = dtype_of(srcs[0], dtype) if n else BF16
-    keep = [_params(p) if p is not None else None for p in params]
-    items = (CompressItem * n)()
+    tuples = array("B", b"".join([_params_bytes(p) if p is not None else b"\0\0\0\0" for p in params]))
+    at = tuples.buffer_info()[0]
+    pack, packed = _COMPRESS_ITEM.pack, []
     for i in range(n):
-        items[i].src = srcs[i].data_ptr()
-        items[i].n_elems = srcs[i].numel()
-        items[i].block_size = block_sizes[i] if block_sizes else 0
-        items[i].params = C.pointer(keep[i]) if keep[i] is not None else None
-        items[i].out = outs[i].data_ptr()
-        items[i].out_capacity = outs[i].numel() * outs[i].element_size()
-        items[i].out_bytes = out_bytes[i].data_ptr() if out_bytes is not None else None
-    return int(lib().enec_compress_batch(items, n, dt, C.c_void_p(workspace.data_ptr()),
-                                         workspace.numel() * workspace.element_size(),
+        src, out = srcs[i], outs[i]
+        packed.append(pack(src.data_ptr(), src.numel(), block_sizes[i] & _U32 if block_sizes else 0, at + 4 * i if params[i] is not None else 0,
+                           out.data_ptr(), out.numel() * out.element_size(), out_bytes[i].data_ptr() if out_bytes is not None else 0))
+    return int(lib().enec_compress_batch(b"".join(packed), n, dt, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                          _stream_handle(stream)))
 
 
@@ -393,17 +412,14 @@ def tune(src, workspace, stream=None, want_histogram: bool = False, dtype: int |
 def tune_batch(srcs, workspace, every: int = 1, stream=None, dtype: int | None = None, want_histograms: bool = False):
     """[(b, n, m, 16), ...] for a list of device tensors of one element format; one wait per sixteen tensors."""
     n = len(srcs)
-    items = (TuneItem * n)()
-    for i, s in enumerate(srcs):
-        items[i].src = s.data_ptr()
-        items[i].n_elems = s.numel()
+    items = b"".join([_TUNE_ITEM.pack(s.data_ptr(), s.numel()) for s in srcs])
     out = (Params * n)()
     hist = np.zeros((n, 256), dtype=np.uint64)
     dt = dtype_of(srcs[0], dtype) if n else BF16
-    _check(lib().enec_tune_batch(items, n, dt, every, out, hist.ctypes.data_as(C.POINTER(C.c_uint64)),
-                                 C.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
-                                 _stream_handle(stream)), "enec_tune_batch")
-    prm = [out[i].astuple() for i in range(n)]
+    _check(lib().enec_tune_batch(items, n, dt, every, out, hist.ctypes.data, workspace.data_ptr(),
+                                 workspace.numel() * workspace.element_size(), _stream_handle(stream)), "enec_tune_batch")
+    raw = bytes(out)
+    prm = [tuple(raw[4 * i:4 * i + 4]) for i in range(n)]
     return (prm, hist) if want_histograms else prm
 
 
