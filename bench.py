@@ -38,9 +38,9 @@ WORKLOADS = ["config1", "config2", "config3", "config3b", "config4", "config5"]
 # profiles/codec_kernels_config2_hbm_traffic.md.  A figure is reported only while the kernel sources still
 # hash to what they were when it was measured, and only for the workload it was measured on; else null.
 MEASURED_TRAFFIC = {
-    "kernel_sources_sha256": "4f134bd83b3efae217171738d8a45e7ae0be619a540fa59ec979a71e9275aea8",
+    "kernel_sources_sha256": "b5436a196a25b8e1e2bc7e7edc7644b8a03e4ab19ef2d050f57bbf29e13e5a94",
     "bytes_per_launch": {
-        "config2": {"enec::compress_kernel<4, 2, 0, 2, 14u>": 716516077, "enec::decompress_kernel<0, 2>": 716992670},
+        "config2": {"enec::compress_kernel<4, 2, 0, 2, 14u>": 714534237, "enec::decompress_kernel<0, 2, true>": 716903771},
     },
 }
 
@@ -223,7 +223,8 @@ def main():
     sizes = torch.zeros(nt, dtype=torch.int64, device="cuda")
 
     # one library call of at most sixteen tensors per kernel launch: tensors of one tuple and block size are compressed
-    # together, streams of one block size decompressed together, whatever their tuples
+    # together, and those of one block that share neither with a longer tensor; streams of one block size are decompressed
+    # together, whatever their tuples, and streams of at most sixteen blocks join the largest block size
     def calls_by(key):
         found = {}
         for i in range(nt):
@@ -231,8 +232,11 @@ def main():
         return [g[c:c + 16] for g in found.values() for c in range(0, len(g), 16)]
 
     blocks = [enec.default_block_size(n) for n in n_el]
-    ccalls = calls_by(lambda i: (params[i][1:], blocks[i]))
-    dcalls = calls_by(lambda i: (params[i][3], blocks[i]))
+    nblocks = [-(-n // b) for n, b in zip(n_el, blocks)]
+    longer = {(params[i][1:], blocks[i]) for i in range(nt) if nblocks[i] > 1}
+    single = [(params[i][1:], blocks[i]) not in longer for i in range(nt)]
+    ccalls = calls_by(lambda i: (params[i][3],) if single[i] else (params[i][1:], blocks[i]))
+    dcalls = calls_by(lambda i: (params[i][3], max(blocks) if nblocks[i] <= 16 else blocks[i]))
 
     def compress_all(ev=None):
         if ev:
@@ -300,18 +304,24 @@ def main():
     # the whole stream (sign/mantissa plane, mask, packed planes, offset table, header), each read
     # or written once
     # compress_kernel<m, n - m, element format, lanes per group, log2 of a constant block size or 0>,
-    # decompress_kernel<element format, lanes per group>; launches of another block size than the default are kept apart
-    def compress_name(i):
+    # compress_single_kernel<element format, lanes per group>, decompress_kernel<element format, lanes per group, several block
+    # sizes>; launches without blocks of the default size are kept apart
+    def compress_name(g):
+        i = g[0]
         _, n, m, L = params[i]
+        if single[i]:
+            return f"enec::compress_single_kernel<{enec.BF16}, {L // 8}>"
         return f"enec::compress_kernel<{m}, {n - m}, {enec.BF16}, {L // 8}, {14 if blocks[i] == 16384 else 0}u>"
 
-    def decompress_name(i):
-        return f"enec::decompress_kernel<{enec.BF16}, {params[i][3] // 8}>"
+    def decompress_name(g):
+        mixed = "true" if len({blocks[i] for i in g}) > 1 else "false"
+        return f"enec::decompress_kernel<{enec.BF16}, {params[g[0]][3] // 8}, {mixed}>"
 
     kern = {}
     for name, calls, dur in ((compress_name, ccalls, dur_c), (decompress_name, dcalls, dur_d)):
         for gi, g in enumerate(calls):
-            label = name(g[0]) + ("" if blocks[g[0]] == 16384 else f" (blocks of {blocks[g[0]]})")
+            largest = max(blocks[i] for i in g)
+            label = name(g) + ("" if largest == 16384 else f" (blocks of {largest})")
             e = kern.setdefault(label, dict(ms=0.0, bytes=0, launches=0, tensors=0))
             e["ms"] += float(dur[:, gi].sum())
             e["bytes"] += sum(2 * n_el[i] + stream_bytes[i] for i in g) * args.steps
