@@ -633,7 +633,7 @@ compress_per_block_kernel(const PbCompressArgs p)
 // workgroups per CU (50 KB of LDS: two images of the worst case and the waiting block's raw bytes).  An iteration takes 12 us: rows
 // and split 0.6, counting 1.9, sums and search 1.4, transform 0.7, packing 1.6, start of the waiting block 1.8, loads
 // and stores 3.0, rest 0.9.  us, against one workgroup per block with the former search in brackets:
-// 67e6 elements of mixed blocks 60.3 (79.3), 34e6 Gaussian 34.8 (50.7), 134e6 119.8 (143.3), 405 MB layer 186 (216), fp16
+// (before the waves' priority) 67e6 elements of mixed blocks 60.3 (79.3), 34e6 Gaussian 34.8 (50.7), 134e6 119.8 (143.3), 405 MB layer 186 (216), fp16
 // 34e6 37.8 (52.5), fp32 56.8 (62.7), 1e6 10.5 (13.1).
 // Looking up the start during the search and storing then, by the other three waves, was slower than all of these (layer
 // 244, mixed blocks 76): the blocks before have not published by then, and the wait for them grows from 1.8 to 5 us.
@@ -935,6 +935,11 @@ compress_per_block_stream_kernel(const CompressArgs p)
         put_mask_bits<LPG>(flagged, img, logC, wave, lane);
         if (tid == 0) s_k[slot ^ 1u] = draw_now ? decode_draw(next_raw) : NO_BLOCK;
         __syncthreads();
+        // From here to the end of the stores a block has what others wait for (its size, its place) and what travels (rows,
+        // stores): these waves go before those of the CU's other workgroups, which count or search.  67e6 elements of mixed
+        // blocks 61.0 -> 57.6 us.  (In compress_kernel, whose waves spend their time alike, it gave 0.6 % of the layer and of
+        // 470 MB matrices and took 0.2 to 0.4 % from fp16 and groups of eight: left out.)
+        __builtin_amdgcn_s_setprio(2);
 
         // wave 1 reads the scan state for the waiting block now and uses it after the packing
         uint64_t early_g = 0, early_b = 0;
@@ -1012,6 +1017,7 @@ compress_per_block_stream_kernel(const CompressArgs p)
         for (int t = 0; t < 8; ++t)
             *reinterpret_cast<uint2 *>(sm_wait + ((size_t)t << logC) + 8u * tid) = make_uint2(SM[t][0], SM[t][1]);
         clear_counts(smem + (slot ^ 1u) * IMG);
+        __builtin_amdgcn_s_setprio(0);
         pend = kl; pend_item = ci; pend_cnt = cnt; pend_S = S; pend_tuple = b | (n << 8) | (m << 16);
         slot ^= 1u;
         k = knext;
