@@ -226,6 +226,12 @@ static_assert(holds_65536_elements(4096) && holds_65536_elements(8192) && holds_
 // to pageable memory takes 14.  A call takes a slot for as long as it runs; up to four are kept for later calls, for
 // all threads, streams and devices, more are given back when their call ends, and these when the process does.
 class CountSlots {
+    // Another thread may be capturing a graph: allocating or freeing would end its capture in any mode but this one.
+    struct SparesCaptures {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        ~SparesCaptures() { if (swapped) { hipStreamCaptureMode back = mode; (void)hipThreadExchangeStreamCaptureMode(&back); } }
+    };
 public:
     static constexpr size_t BYTES = WS_HIST_SLOTS * 256 * 8, KEPT = 4;
     void *take()
@@ -238,12 +244,9 @@ public:
                 return p;
             }
         }
-        // (another thread may be capturing a graph, and an allocation would end its capture in any mode but this one)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        const SparesCaptures guard;
         void *p = nullptr;
         if (hipHostMalloc(&p, BYTES, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
-        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
         return p;
     }
     void give(void *p)
@@ -252,7 +255,8 @@ public:
             std::lock_guard<std::mutex> lock(mu_);
             if (free_.size() < KEPT) { free_.push_back(p); return; }
         }
-        (void)hipHostFree(p);
+        const SparesCaptures guard;
+        if (hipHostFree(p) != hipSuccess) (void)hipGetLastError();        // (nobody's launch failed)
     }
     CountSlots() { free_.reserve(KEPT); }
     ~CountSlots() { for (void *p : free_) (void)hipHostFree(p); }
@@ -472,6 +476,12 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
     hipStream_t s = (hipStream_t)stream;
     auto *dhist = reinterpret_cast<unsigned long long *>(static_cast<uint8_t *>(workspace) + WS_HIST);
     if (n_items == 0) return ENEC_OK;
+    // a capture cannot be waited for: refused before anything is enqueued into it
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return ENEC_E_HIP;
+    }
     uint64_t *host = static_cast<uint64_t *>(count_slots().take());
     if (!host) return ENEC_E_HIP;
     // sixteen tensors at a time: their histograms are counted into sixteen slots, handed over together,
@@ -511,8 +521,12 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
         uint4 *to = reinterpret_cast<uint4 *>(host);
         const uint4 *from = reinterpret_cast<const uint4 *>(dhist);
         void *args[] = {&to, &from};
-        if (hipLaunchKernel((const void *)hand_over_counts_kernel, dim3((unsigned)count), dim3(128), args, 0, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess) {
+        if (hipLaunchKernel((const void *)hand_over_counts_kernel, dim3((unsigned)count), dim3(128), args, 0, s) != hipSuccess) {
+            (void)hipGetLastError();
+            count_slots().give(host);
+            return ENEC_E_HIP;
+        }
+        if (hipStreamSynchronize(s) != hipSuccess) {
             (void)hipGetLastError();
             return ENEC_E_HIP;                 // (the slot is not given back: a kernel may still be about to write there)
         }

@@ -1,0 +1,137 @@
+"""What the library's host code asks of the HIP runtime, watched on the CPU: a stand-in for the runtime's calls is loaded
+before libenec.so in a process of its own (device pointers are made-up numbers; nothing is launched)."""
+import ctypes
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from conftest import ROOT
+
+STAND_IN = r"""
+#include <pthread.h>
+#include <stdint.h>
+#include <stdlib.h>
+
+typedef struct { uint32_t x, y, z; } dim3_;
+static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
+static pthread_cond_t moved = PTHREAD_COND_INITIALIZER;
+int slots_held, slots_most, frees_unguarded, mallocs_unguarded, launches;
+int capturing, launch_fails, sync_fails, gather;     /* set by the test; gather: callers that meet in a wait */
+static int gathered;
+uint32_t grid[64], block[64], lds[64];
+static _Thread_local int mode;                       /* 0 = global, 2 = relaxed */
+static dim3_ pushed_grid, pushed_block;
+static uint64_t pushed_lds;
+
+int hipThreadExchangeStreamCaptureMode(int *m) { int old = mode; mode = *m; *m = old; return 0; }
+int hipStreamIsCapturing(void *s, int *status) { *status = capturing; return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned flags)
+{
+    pthread_mutex_lock(&mu);
+    if (mode != 2) ++mallocs_unguarded;
+    if (++slots_held > slots_most) slots_most = slots_held;
+    pthread_mutex_unlock(&mu);
+    *p = calloc(1, n);
+    return 0;
+}
+int hipHostFree(void *p)
+{
+    pthread_mutex_lock(&mu);
+    if (mode != 2) ++frees_unguarded;
+    --slots_held;
+    pthread_mutex_unlock(&mu);
+    free(p);
+    return 0;
+}
+int hipStreamSynchronize(void *s)
+{
+    pthread_mutex_lock(&mu);
+    if (gather) {
+        ++gathered;
+        pthread_cond_broadcast(&moved);
+        while (gathered < gather) pthread_cond_wait(&moved, &mu);
+    }
+    pthread_mutex_unlock(&mu);
+    return capturing ? 900 : sync_fails;
+}
+int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t shared, void *s)
+{
+    pthread_mutex_lock(&mu);
+    if (launches < 64) { grid[launches] = g.x; block[launches] = b.x; lds[launches] = (uint32_t)shared; }
+    ++launches;
+    pthread_mutex_unlock(&mu);
+    return launch_fails;
+}
+int hipGetLastError(void) { return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+"""
+
+PRELUDE = r"""
+import ctypes as C, json, struct, sys, threading
+rt = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)         # before the library: its calls end here
+L = C.CDLL(sys.argv[2])
+def word(name): return C.c_int.in_dll(rt, name)
+def launches(): return [(C.c_uint32 * 64).in_dll(rt, "grid")[i] for i in range(word("launches").value)], [(C.c_uint32 * 64).in_dll(rt, "block")[i] for i in range(word("launches").value)]
+FAKE = 1 << 20                                       # a "device" pointer, 16-byte aligned
+class P(C.Structure): _fields_ = [(f, C.c_uint8) for f in "bnmL"]
+def tune(stream=64):
+    prm = P()
+    return L.enec_tune(C.c_void_p(FAKE), C.c_size_t(100000), 0, C.byref(prm), None, C.c_void_p(FAKE), C.c_size_t(1 << 20), C.c_void_p(stream))
+def report(**kw): print(json.dumps(kw))
+"""
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    from paper_2604_03298_amd import enec
+    if not os.path.exists(enec.LIB_PATH):
+        from paper_2604_03298_amd import build
+        build.build()
+    where = tmp_path_factory.mktemp("stand_in")
+    src, so = where / "runtime.c", where / "runtime.so"
+    src.write_text(STAND_IN)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-pthread", "-o", str(so), str(src)], check=True)
+
+    def run(body):
+        script = where / "script.py"
+        script.write_text(PRELUDE + body)
+        res = subprocess.run([sys.executable, str(script), str(so), enec.LIB_PATH], capture_output=True, text=True, timeout=60, cwd=ROOT)
+        assert res.returncode == 0, res.stdout + res.stderr
+        return json.loads(res.stdout.splitlines()[-1])
+
+    return run
+
+
+def test_a_search_on_a_capturing_stream_is_refused_with_nothing_enqueued(stand_in):
+    got = stand_in("""
+word("capturing").value = 1
+rcs = {tune() for _ in range(50)}
+during = word("launches").value, word("slots_held").value
+word("capturing").value = 0
+report(rcs=list(rcs), during=during, after=tune(), held=word("slots_held").value)
+""")
+    assert got == dict(rcs=[8], during=[0, 0], after=0, held=1)
+
+
+def test_a_search_whose_launch_fails_gives_its_slot_back(stand_in):
+    got = stand_in("""
+word("launch_fails").value = 719
+rcs = {tune() for _ in range(50)}
+report(rcs=list(rcs), held=word("slots_held").value)
+""")
+    assert got == dict(rcs=[8], held=1)
+
+
+def test_slots_beyond_those_kept_are_freed_without_ending_a_capture_elsewhere(stand_in):
+    """Nine calls at once hold nine slots; five of them are freed afterwards, in the mode that spares other threads' captures."""
+    got = stand_in("""
+word("gather").value = 9
+threads = [threading.Thread(target=tune) for _ in range(9)]
+for t in threads: t.start()
+for t in threads: t.join()
+report(most=word("slots_most").value, held=word("slots_held").value, unguarded=[word("mallocs_unguarded").value, word("frees_unguarded").value])
+""")
+    assert got == dict(most=9, held=4, unguarded=[0, 0])
