@@ -965,15 +965,17 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
     // joins a launch of larger blocks too: each of its blocks takes the place of a large one, 8 us of one of the device's
     // 1024 places, where a launch of their own takes 4 us of all of them.  A decoder layer with its two norm vectors, us:
     // hidden size 512 10.9 -> 7.2, 1024 12.5 -> 8.7, 2048 35.9 -> 31.8, 4096 120.9 -> 118.1.
+    // The streams of the launch's block size are in it first: sixteen small ones ahead of a large one would else take all
+    // places of a launch with its threads and LDS, and leave it to a launch of its own.
     constexpr uint32_t JOIN = 16;
     std::vector<char> done(n_items, 0);
-    for (size_t i = 0; i < n_items; ++i) {
-        if (done[i]) continue;
-        if (hdr[i].nb == 0) { done[i] = 1; continue; }
+    for (size_t i = 0; i < n_items;) {
+        if (done[i] || hdr[i].nb == 0) { ++i; continue; }
         const Header &h0 = hdr[i];
+        auto alike = [&](size_t j) { return !done[j] && hdr[j].nb != 0 && hdr[j].dtype == h0.dtype && hdr[j].prm.L == h0.prm.L; };
         uint32_t B = h0.B;
         for (size_t j = i; h0.nb <= JOIN && j < n_items; ++j)
-            if (!done[j] && hdr[j].nb != 0 && hdr[j].dtype == h0.dtype && hdr[j].prm.L == h0.prm.L && hdr[j].B > B) B = hdr[j].B;
+            if (alike(j) && hdr[j].B > B) B = hdr[j].B;
         const unsigned threads = B / 64 < 64 ? 64 : B / 64;
         DecompressArgs a;
         a.B = B;
@@ -982,11 +984,9 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
         uint32_t items_in = 0;
         uint64_t blocks = 0;
         size_t packed = 0;       // the packed part of the widest block of the launch: mask | low plane | high records | padding
-        for (size_t j = i; j < n_items && items_in < (uint32_t)MAX_BATCH; ++j) {
+        auto take = [&](size_t j) {
             const Header &h = hdr[j];
-            if (done[j] || h.nb == 0 || h.dtype != h0.dtype || h.prm.L != h0.prm.L || (h.B != B && (h.B > B || h.nb > JOIN)) ||
-                (blocks + h.nb) * threads > 0xFFFFFFFFull)            // a grid has fewer than 2^32 threads
-                continue;
+            if (items_in == (uint32_t)MAX_BATCH || (blocks + h.nb) * threads > 0xFFFFFFFFull) return;   // a grid has fewer than 2^32 threads
             const size_t tuples = h.per_block ? tuple_table_bytes(items[j].n_elems, h.B) : 0;
             a.first[items_in] = (uint32_t)blocks;
             DecompressItem &d = a.item[items_in++];
@@ -1006,7 +1006,11 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
             packed = std::max(packed, (size_t)h.B / (8 * h.prm.L) + (size_t)bits * h.B / 8 + 16);
             blocks += h.nb;
             done[j] = 1;
-        }
+        };
+        for (size_t j = i; j < n_items; ++j)
+            if (alike(j) && hdr[j].B == B) take(j);
+        for (size_t j = i; j < n_items && items_in < (uint32_t)MAX_BATCH; ++j)
+            if (alike(j) && hdr[j].B < B && hdr[j].nb <= JOIN) take(j);
         for (uint32_t j = items_in; j < (uint32_t)MAX_BATCH; ++j) {
             a.first[j] = 0xFFFFFFFFu;
             a.item[j] = a.item[0];

@@ -54,3 +54,19 @@ def test_streams_of_all_block_sizes_in_one_call(gpu, oracle, dtype, L, order):
         else:
             assert np.array_equal(got[:w.size], w), f"blocks of {B}, {w.size} elements"
             assert int(st.item()) == 0
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+def test_more_small_streams_than_places_ahead_of_a_large_one(gpu, oracle, dtype):
+    """The large stream's launch is filled up with some of the small ones, the others follow in one of their own."""
+    torch, enec = gpu.torch, gpu.enec
+    words = [GEN[dtype](n, 0.02, 50 + i) for i, n in enumerate([4096 - i for i in range(9)] + [2048] * 10 + [20 * 16384 + 5])]
+    made = [oracle.compress(w, oracle.tune(w, dtype), oracle.default_block(w.size), dtype=dtype) for w in words]
+    assert all(rc == 0 for rc, _ in made)
+    bufs = [torch.from_numpy(s).cuda() for _, s in made]
+    wide = torch.int32 if dtype == FP32 else torch.int16
+    backs = [torch.zeros(w.size, dtype=wide, device="cuda") for w in words]
+    assert enec.decompress_batch(bufs, [s[:64].tobytes() for _, s in made], backs) == enec.OK
+    torch.cuda.synchronize()
+    for w, back in zip(words, backs):
+        assert np.array_equal(back.cpu().numpy().view(WORD[dtype]), w), w.size

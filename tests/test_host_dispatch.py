@@ -23,8 +23,9 @@ int capturing, launch_fails, sync_fails, gather;     /* set by the test; gather:
 static int gathered;
 uint32_t grid[64], block[64], lds[64];
 static _Thread_local int mode;                       /* 0 = global, 2 = relaxed */
-static dim3_ pushed_grid, pushed_block;
-static uint64_t pushed_lds;
+static _Thread_local dim3_ pushed_grid, pushed_block;
+static _Thread_local size_t pushed_lds;
+static _Thread_local void *pushed_stream;
 
 int hipThreadExchangeStreamCaptureMode(int *m) { int old = mode; mode = *m; *m = old; return 0; }
 int hipStreamIsCapturing(void *s, int *status) { *status = capturing; return 0; }
@@ -65,6 +66,9 @@ int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t shared,
     pthread_mutex_unlock(&mu);
     return launch_fails;
 }
+/* what a <<<>>> launch does before and inside the kernel's stub */
+int __hipPushCallConfiguration(dim3_ g, dim3_ b, size_t shared, void *s) { pushed_grid = g; pushed_block = b; pushed_lds = shared; pushed_stream = s; return 0; }
+int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *shared, void **s) { *g = pushed_grid; *b = pushed_block; *shared = pushed_lds; *s = pushed_stream; return 0; }
 int hipGetLastError(void) { return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 """
@@ -135,3 +139,37 @@ for t in threads: t.join()
 report(most=word("slots_most").value, held=word("slots_held").value, unguarded=[word("mallocs_unguarded").value, word("frees_unguarded").value])
 """)
     assert got == dict(most=9, held=4, unguarded=[0, 0])
+
+
+DECOMPRESS = """
+class Item(C.Structure): _fields_ = [("src", C.c_void_p), ("in_bytes", C.c_size_t), ("header", C.c_void_p), ("out", C.c_void_p), ("n", C.c_size_t), ("status", C.c_void_p)]
+def decompress(streams, dtype=0):
+    '''One call for streams of (elements, block size); the workgroups and the threads of its launches.'''
+    items, keep = (Item * len(streams))(), []
+    for it, (n, B) in zip(items, streams):
+        nb = -(-n // B)
+        h = struct.pack("<4sHBBQII4BIQ", b"ENEC", 1, dtype, 16, n, B, nb, 8, 5, 3, 5 if dtype == 1 else 8, 0, 1 << 40) + bytes(24)
+        keep.append(C.create_string_buffer(h, 64))
+        it.src, it.in_bytes, it.header, it.out, it.n = FAKE, 1 << 40, C.addressof(keep[-1]), FAKE, n
+    word("launches").value = 0
+    assert L.enec_decompress_batch(items, C.c_size_t(len(streams)), C.c_void_p(64)) == 0
+    return launches()
+"""
+
+
+@pytest.mark.parametrize("dtype", [0, 1, 2])
+def test_a_decompression_launch_has_the_threads_of_a_block_it_holds(stand_in, dtype):
+    """Sixteen streams to a launch: the streams of the largest block size are in it first, those of few blocks fill it up."""
+    got = stand_in(DECOMPRESS + f"""
+d = {dtype}
+norm, matrix, wide = (4096, 4096), (4 << 20, 16384), (17 << 15, 32768)
+report(before=decompress([norm] * 20 + [matrix], d), after=decompress([matrix] + [norm] * 20, d),
+       sixteen=decompress([norm] * 16 + [matrix], d), few=decompress([norm, matrix, norm], d), alone=decompress([norm] * 20, d),
+       many=decompress([norm] * 3 + [matrix] * 18, d), three=decompress([norm] * 15 + [matrix] * 15 + [wide] * 2, d),
+       long=decompress([(17 * 2048, 2048), (16 * 2048, 2048), matrix], d), empty=decompress([(0, 2048), norm, (0, 16384)], d))
+""")
+    joined = [[256 + 15, 5], [256, 64]]
+    assert got == dict(before=joined, after=joined, sixteen=[[256 + 15, 1], [256, 64]], few=[[258], [256]], alone=[[16, 4], [64, 64]],
+                       many=[[16 * 256, 2 * 256 + 3], [256, 256]],
+                       three=[[2 * 17 + 14, 15 * 256 + 1], [512, 256]],
+                       long=[[17 + 16, 256], [64, 256]], empty=[[1], [64]])
