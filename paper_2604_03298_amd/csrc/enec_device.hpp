@@ -608,8 +608,10 @@ __device__ __forceinline__ void unpack_record_row(const uint8_t *img_high, uint3
 }
 
 // a1: 128-bit loads of the 8 rows of data block k (pad elements beyond the tensor's end); a
-// thread's 8 elements of a row are one vector (16-bit formats) or two (fp32)
-template <int DT, class Item>
+// thread's 8 elements of a row are one vector (16-bit formats) or two (fp32).
+// WHOLE: the tensor's last block, shorter than B, is read with whole vectors; false: element by element (16-bit formats
+// only), for kernels that have no registers left for the former.
+template <int DT, bool WHOLE = true, class Item>
 __device__ __forceinline__ void load_block_rows(const Item &p, uint32_t B, uint32_t logB, uint32_t k,
                                                 uint32_t tid, bool active, uint32_t logC,
                                                 uint4 (&raw)[DT == DT_FP32 ? 16 : 8])
@@ -661,6 +663,24 @@ __device__ __forceinline__ void load_block_rows(const Item &p, uint32_t B, uint3
                                 : make_uint4(padw, padw, padw, padw);
             return;
         }
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const uint64_t e0 = blk0 + ((uint64_t)t << logC) + 8u * tid;
+                uint32_t d[4] = {padw, padw, padw, padw};
+                if (active && e0 < p.n_elems) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (e0 + i < p.n_elems) {
+                            const uint32_t v = p.in[e0 + i];
+                            d[i >> 1] = (i & 1) ? ((d[i >> 1] & 0x0000FFFFu) | (v << 16))
+                                                : ((d[i >> 1] & 0xFFFF0000u) | v);
+                        }
+                }
+                raw[t] = make_uint4(d[0], d[1], d[2], d[3]);
+            }
+            return;
+        }
         // the tensor's last block, shorter than B: whole vectors as ever, and the lane in whose vector the tensor ends
         // asks for those elements together.  (All elements of all eight rows one by one, each under a branch and waited
         // for before the next, made every tensor wait for its last block: three of 8388609 elements 26.8 us, now 24.0.)
@@ -709,6 +729,13 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     constexpr int AP = A > 0 ? A : 1;
     constexpr int RW = DT == DT_FP32 ? 16 : 8;           // 128-bit vectors of one block per thread
     constexpr bool FULL = N == (int)exponent_bits(DT);   // the window is the whole exponent range (mode 1)
+    // With a run-time block size the 16-bit formats have no registers left for two forms of the transform (bf16) and the
+    // ragged block in whole vectors: 22 to 34 were spilled, and 67e6 elements took, in blocks of 8192 and groups of 32,
+    // 76.4 us (bf16) and 72.5 (fp16) against 61.1 and 60.0 like this; groups of 16 59.9 and 64.7 against 55.2 and 58.1,
+    // groups of 8 60.4 and 64.5 against 54.9 and 58.1; three ragged tensors of 1e6 elements in blocks of 2048 15.6 and 15.5
+    // against 13.2 and 13.7.  fp32 (two waves per SIMD) and the constant block size have them.
+    constexpr bool WHOLE = LOGB != 0 || DT == DT_FP32;
+    constexpr bool MODE_PER_STEP = LOGB == 0 && DT == DT_BF16 && !FULL;
 
     // two LDS images of the packed part of a payload: mask | low plane (as normalized bytes,
     // interleaved on the way out) | high records
@@ -760,7 +787,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     const uint32_t guess = blockIdx.x;                       // the grid never exceeds the number of blocks
     uint32_t ci = item_of(guess, 0);
     uint4 raw[RW];
-    load_block_rows<DT>(p.item[ci], B, logB, guess - p.item[ci].first, tid, active, logC, raw);
+    load_block_rows<DT, WHOLE>(p.item[ci], B, logB, guess - p.item[ci].first, tid, active, logC, raw);
     if (tid == 0) {
         ticket_base = ctl[1];
         tag0 = *reinterpret_cast<const uint64_t *>(ctl + 2) + 1u;
@@ -776,7 +803,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     uint32_t k = __builtin_amdgcn_readfirstlane(s_k[0]);     // global block index
     if (k != guess && k != NO_BLOCK) {                       // the guess was wrong: ask again
         ci = item_of(k, 0);
-        load_block_rows<DT>(p.item[ci], B, logB, k - p.item[ci].first, tid, active, logC, raw);
+        load_block_rows<DT, WHOLE>(p.item[ci], B, logB, k - p.item[ci].first, tid, active, logC, raw);
     }
     const uint64_t tag = (uint64_t)s_tag << 24;
     constexpr HHTable TL = HH<MP>::table;
@@ -972,7 +999,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         const uint64_t row0 = ((uint64_t)kl << logB) + 8u * tid;   // this thread's first element of row 0
         // WRAP: the bytes are subtracted without borrows between them, and where the window is not the whole exponent
         // range every exponent is compared with it.  Two straight runs of code and one branch: a branch on the mode at
-        // each of the sixteen subtractions cut the transform into pieces that nothing was scheduled across.
+        // each of the sixteen subtractions (MODE_PER_STEP) cuts the transform into pieces that nothing is scheduled across.
         auto transform = [&](auto wrap) {
         constexpr bool WRAP = decltype(wrap)::value;
 #pragma unroll
@@ -1010,12 +1037,12 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
                 }
                 // a2 transform: z = (b + 2^(n-1) - x) mod 256 per byte, y = z with the sign bit flipped
                 uint32_t Z;
-                if constexpr (!WRAP) {
+                if (MODE_PER_STEP ? mode == 0 : !WRAP) {
                     Z = crep - X;
                     err_acc |= Z;
                 } else {
                     Z = bytesub_safe(crep, X);
-                    if constexpr (!FULL) {
+                    if (!FULL) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const uint32_t xb = (X >> (8 * i)) & 0xFFu;
@@ -1046,8 +1073,9 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
             flagged[t] = __builtin_amdgcn_ballot_w64(gor != 0);
         }
         };
-        if constexpr (FULL) {
+        if constexpr (FULL || MODE_PER_STEP) {
             transform(std::true_type{});
+            if (MODE_PER_STEP && mode == 0) bad = (err_acc & ~NMASK) != 0;
         } else if (DT == DT_FP16 || mode == 0) {
             transform(std::false_type{});
             bad = (err_acc & ~NMASK) != 0;
@@ -1116,7 +1144,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
         uint32_t cnext = ci;
         if (knext != NO_BLOCK) {
             cnext = item_of(knext, ci);
-            load_block_rows<DT>(p.item[cnext], B, logB, knext - p.item[cnext].first, tid, active, logC, raw);
+            load_block_rows<DT, WHOLE>(p.item[cnext], B, logB, knext - p.item[cnext].first, tid, active, logC, raw);
         }
 
         // ---- a7: stores of the previous block ----------------------------------------------
@@ -1145,7 +1173,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
             k = __builtin_amdgcn_readfirstlane(s_k[slot]);
             if (k != NO_BLOCK) {
                 ci = item_of(k, ci);
-                load_block_rows<DT>(p.item[ci], B, logB, k - p.item[ci].first, tid, active, logC, raw);
+                load_block_rows<DT, WHOLE>(p.item[ci], B, logB, k - p.item[ci].first, tid, active, logC, raw);
             }
         }
     }
