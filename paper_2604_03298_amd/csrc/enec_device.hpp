@@ -1037,12 +1037,24 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
                 }
                 // a2 transform: z = (b + 2^(n-1) - x) mod 256 per byte, y = z with the sign bit flipped
                 uint32_t Z;
-                if (MODE_PER_STEP ? mode == 0 : !WRAP) {
+                if constexpr (MODE_PER_STEP) {
+                    if (mode == 0) {
+                        Z = crep - X;
+                        err_acc |= Z;
+                    } else {
+                        Z = bytesub_safe(crep, X);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t xb = (X >> (8 * i)) & 0xFFu;
+                            bad |= (xb < xlo) | (xb > xhi);
+                        }
+                    }
+                } else if constexpr (!WRAP) {
                     Z = crep - X;
                     err_acc |= Z;
                 } else {
                     Z = bytesub_safe(crep, X);
-                    if (!FULL) {
+                    if constexpr (!FULL) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             const uint32_t xb = (X >> (8 * i)) & 0xFFu;
@@ -1073,9 +1085,11 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
             flagged[t] = __builtin_amdgcn_ballot_w64(gor != 0);
         }
         };
-        if constexpr (FULL || MODE_PER_STEP) {
+        if constexpr (FULL) {
             transform(std::true_type{});
-            if (MODE_PER_STEP && mode == 0) bad = (err_acc & ~NMASK) != 0;
+        } else if constexpr (MODE_PER_STEP) {
+            transform(std::true_type{});
+            if (mode == 0) bad = (err_acc & ~NMASK) != 0;
         } else if (DT == DT_FP16 || mode == 0) {
             transform(std::false_type{});
             bad = (err_acc & ~NMASK) != 0;
