@@ -159,17 +159,19 @@ def decompress(streams, dtype=0):
 
 @pytest.mark.parametrize("dtype", [0, 1, 2])
 def test_a_decompression_launch_has_the_threads_of_a_block_it_holds(stand_in, dtype):
-    """Sixteen streams to a launch: the streams of the largest block size are in it first, those of few blocks fill it up."""
+    """Sixteen streams to a launch: the streams of the largest block size are in it first; of a smaller size as many join as make one
+    launch less for that size, and only if they have few blocks."""
     got = stand_in(DECOMPRESS + f"""
 d = {dtype}
 norm, matrix, wide = (4096, 4096), (4 << 20, 16384), (17 << 15, 32768)
 report(before=decompress([norm] * 20 + [matrix], d), after=decompress([matrix] + [norm] * 20, d),
        sixteen=decompress([norm] * 16 + [matrix], d), few=decompress([norm, matrix, norm], d), alone=decompress([norm] * 20, d),
        many=decompress([norm] * 3 + [matrix] * 18, d), three=decompress([norm] * 15 + [matrix] * 15 + [wide] * 2, d),
-       long=decompress([(17 * 2048, 2048), (16 * 2048, 2048), matrix], d), empty=decompress([(0, 2048), norm, (0, 16384)], d))
+       long=decompress([(17 * 2048, 2048), (16 * 2048, 2048), matrix], d), rest=decompress([(17 * 2048, 2048)] + [(2048, 2048)] * 17 + [matrix], d),
+       sizes=decompress([(2048, 2048), (4096, 4096), (8192, 8192)] * 13 + [(2048, 2048)], d), empty=decompress([(0, 2048), norm, (0, 16384)], d))
 """)
-    joined = [[256 + 15, 5], [256, 64]]
-    assert got == dict(before=joined, after=joined, sixteen=[[256 + 15, 1], [256, 64]], few=[[258], [256]], alone=[[16, 4], [64, 64]],
+    joined = [256 + 4, 16]
+    assert got == dict(before=[joined, [256, 64]], after=[joined, [256, 64]], sixteen=[[256, 16], [256, 64]], few=[[258], [256]], alone=[[16, 4], [64, 64]],
                        many=[[16 * 256, 2 * 256 + 3], [256, 256]],
-                       three=[[2 * 17 + 14, 15 * 256 + 1], [512, 256]],
-                       long=[[17 + 16, 256], [64, 256]], empty=[[1], [64]])
+                       three=[[2 * 17, 15 * 256, 15], [512, 256, 64]],
+                       long=[[17 + 16, 256], [64, 256]], rest=[[17 + 15, 256 + 2], [64, 256]], sizes=[[13, 13, 14], [128, 64, 64]], empty=[[1], [64]])
