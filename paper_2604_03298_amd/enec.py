@@ -10,6 +10,7 @@ import ctypes as C
 import os
 import struct
 from array import array
+from operator import index
 
 import numpy as np
 
@@ -327,7 +328,7 @@ def compress_per_block_batch(srcs, outs, workspace, out_bytes=None, stream=None,
     for i in range(n):
         src, out = srcs[i], outs[i]
         ob = out_bytes[i] if out_bytes is not None else None
-        packed.append(pack(src.data_ptr(), src.numel(), block_sizes[i] & _U32 if block_sizes is not None else 0, out.data_ptr(),
+        packed.append(pack(src.data_ptr(), src.numel(), index(block_sizes[i]) & _U32 if block_sizes is not None else 0, out.data_ptr(),
                            out.numel() * out.element_size(), ob.data_ptr() if ob is not None else 0))
     dt = dtype_of(srcs[0], dtype) if n else (BF16 if dtype is None else dtype)
     return int(lib().enec_compress_per_block_batch(b"".join(packed), n, dt, group_length, workspace.data_ptr(),
@@ -362,7 +363,7 @@ def compress_batch(srcs, params, outs, workspace, block_sizes=None, out_bytes=No
     pack, packed = _COMPRESS_ITEM.pack, []
     for i in range(n):
         src, out = srcs[i], outs[i]
-        packed.append(pack(src.data_ptr(), src.numel(), block_sizes[i] & _U32 if block_sizes else 0, at + 4 * i if params[i] is not None else 0,
+        packed.append(pack(src.data_ptr(), src.numel(), index(block_sizes[i]) & _U32 if block_sizes else 0, at + 4 * i if params[i] is not None else 0,
                            out.data_ptr(), out.numel() * out.element_size(), out_bytes[i].data_ptr() if out_bytes is not None else 0))
     return int(lib().enec_compress_batch(b"".join(packed), n, dt, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                          _stream_handle(stream)))
