@@ -358,6 +358,7 @@ def compress_batch(srcs, params, outs, workspace, block_sizes=None, out_bytes=No
     of one-u64 device-accessible tensors."""
     n = len(srcs)
     dt = dtype_of(srcs[0], dtype) if n else BF16
+    params = list(params)
     tuples = array("B", b"".join([_params_bytes(p) if p is not None else b"\0\0\0\0" for p in params]))
     at = tuples.buffer_info()[0]
     pack, packed = _COMPRESS_ITEM.pack, []

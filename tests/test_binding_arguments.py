@@ -65,3 +65,10 @@ def test_block_sizes_may_be_integers_of_any_kind(enec, monkeypatch, kind):
     items = [struct.unpack_from("<QQI4xQQQQ", packed, 56 * i) for i in range(2)]
     assert [it[:3] + it[4:] for it in items] == [(1 << 20, 5000, 2048, 3 << 20, 10000, 0), (2 << 20, 70000, 32768, 4 << 20, 300000, 0)]
     assert items[0][3] != 0 and items[1][3] == 0
+
+
+def test_tuples_may_come_from_an_iterator(enec, monkeypatch):
+    calls = _record(monkeypatch, enec, "enec_compress_batch")
+    assert enec.compress_batch(SRCS, (p for p in [(122, 6, 3, 16), None]), OUTS, WS, dtype=0) == 0
+    items = [struct.unpack_from("<QQI4xQQQQ", _bytes(calls[0][0], 112), 56 * i) for i in range(2)]
+    assert items[0][3] != 0 and items[1][3] == 0
