@@ -11,6 +11,7 @@ import os
 import struct
 from array import array
 from operator import index
+from types import SimpleNamespace
 
 import numpy as np
 
@@ -65,8 +66,8 @@ class OffloadItem(C.Structure):
                 ("n_elems", C.c_size_t), ("status", C.c_void_p)]
 
 
-# Item arrays are packed in one go and handed over as bytes: filling a ctypes array costs 1.5 us per tensor, as much as the
-# whole call in the library.
+# Item arrays are packed in one go and handed over as bytes (lib().raw): filling a ctypes array costs 1.5 us per tensor, as
+# much as the whole call in the library.
 _COMPRESS_ITEM = struct.Struct("=QQI4xQQQQ")
 _PER_BLOCK_ITEM = struct.Struct("=QQI4xQQQ")
 _TUNE_ITEM = struct.Struct("=QQ")
@@ -106,7 +107,7 @@ def lib():
         L.enec_workspace_init.restype = C.c_int
         L.enec_workspace_init.argtypes = [vp, sz, vp]
         L.enec_compress.restype = C.c_int
-        L.enec_compress.argtypes = [vp, sz, C.c_int, u32, vp, vp, sz, vp, vp, sz, vp]
+        L.enec_compress.argtypes = [vp, sz, C.c_int, u32, C.POINTER(Params), vp, sz, vp, vp, sz, vp]
         L.enec_compress_static.restype = C.c_int
         L.enec_compress_static.argtypes = [vp, sz, C.c_int, u32, C.POINTER(Params), vp, sz, vp, vp]
         L.enec_decompress.restype = C.c_int
@@ -120,9 +121,9 @@ def lib():
         L.enec_compress_per_block.restype = C.c_int
         L.enec_compress_per_block.argtypes = [vp, sz, C.c_int, C.c_uint32, C.c_uint32, vp, sz, vp, vp, sz, vp]
         L.enec_compress_per_block_batch.restype = C.c_int
-        L.enec_compress_per_block_batch.argtypes = [vp, sz, C.c_int, C.c_uint32, vp, sz, vp]
+        L.enec_compress_per_block_batch.argtypes = [C.POINTER(PerBlockItem), sz, C.c_int, C.c_uint32, vp, sz, vp]
         L.enec_tune_batch.restype = C.c_int
-        L.enec_tune_batch.argtypes = [vp, sz, C.c_int, C.c_uint32, C.POINTER(Params), vp, vp, sz, vp]
+        L.enec_tune_batch.argtypes = [C.POINTER(TuneItem), sz, C.c_int, C.c_uint32, C.POINTER(Params), u64p, vp, sz, vp]
         L.enec_tune_sampled.restype = C.c_int
         L.enec_tune_sampled.argtypes = [vp, sz, C.c_int, C.c_uint32, C.POINTER(Params), u64p, vp, sz, vp]
         L.enec_compress_sampled.restype = C.c_int
@@ -138,7 +139,7 @@ def lib():
         L.enec_copy.restype = C.c_int
         L.enec_copy.argtypes = [vp, vp, sz, vp]
         L.enec_compress_batch.restype = C.c_int
-        L.enec_compress_batch.argtypes = [vp, sz, C.c_int, vp, sz, vp]
+        L.enec_compress_batch.argtypes = [C.POINTER(CompressItem), sz, C.c_int, vp, sz, vp]
         L.enec_decompress_batch.restype = C.c_int
         L.enec_decompress_batch.argtypes = [C.POINTER(DecompressItem), sz, vp]
         L.enec_pipeline_create.restype = C.c_int
@@ -155,6 +156,13 @@ def lib():
         L.enec_pipeline_release.argtypes = [vp, u32, vp]
         L.enec_pipeline_trace.restype = C.c_int
         L.enec_pipeline_trace.argtypes = [vp, C.POINTER(C.c_float), sz, C.POINTER(sz)]
+        # the same entry points for this module's own calls, which pass packed bytes in the place of structures
+        L.raw = SimpleNamespace()
+        for name in ("enec_compress", "enec_compress_batch", "enec_compress_per_block_batch", "enec_tune_batch"):
+            typed, plain = getattr(L, name), L[name]         # (indexing makes another function object)
+            plain.restype = C.c_int
+            plain.argtypes = [vp if issubclass(t, C._Pointer) else t for t in typed.argtypes]
+            setattr(L.raw, name, plain)
         _lib = L
     return _lib
 
@@ -282,7 +290,7 @@ def compress(src, params, out, workspace, block_size: int = 0, out_bytes=None, s
     assert src.element_size() == (4 if dt == FP32 else 2)
     pp = _params_bytes(params) if params is not None else None
     ob = out_bytes.data_ptr() if out_bytes is not None else None
-    return int(lib().enec_compress(
+    return int(lib().raw.enec_compress(
         src.data_ptr(), n, dt, block_size, pp, out.data_ptr(), out.numel() * out.element_size(), ob,
         workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream_handle(stream)))
 
@@ -331,7 +339,7 @@ def compress_per_block_batch(srcs, outs, workspace, out_bytes=None, stream=None,
         packed.append(pack(src.data_ptr(), src.numel(), index(block_sizes[i]) & _U32 if block_sizes is not None else 0, out.data_ptr(),
                            out.numel() * out.element_size(), ob.data_ptr() if ob is not None else 0))
     dt = dtype_of(srcs[0], dtype) if n else (BF16 if dtype is None else dtype)
-    return int(lib().enec_compress_per_block_batch(b"".join(packed), n, dt, group_length, workspace.data_ptr(),
+    return int(lib().raw.enec_compress_per_block_batch(b"".join(packed), n, dt, group_length, workspace.data_ptr(),
                                                    workspace.numel() * workspace.element_size(), _stream_handle(stream)))
 
 
@@ -366,7 +374,7 @@ def compress_batch(srcs, params, outs, workspace, block_sizes=None, out_bytes=No
         src, out = srcs[i], outs[i]
         packed.append(pack(src.data_ptr(), src.numel(), index(block_sizes[i]) & _U32 if block_sizes else 0, at + 4 * i if params[i] is not None else 0,
                            out.data_ptr(), out.numel() * out.element_size(), out_bytes[i].data_ptr() if out_bytes is not None else 0))
-    return int(lib().enec_compress_batch(b"".join(packed), n, dt, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+    return int(lib().raw.enec_compress_batch(b"".join(packed), n, dt, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                          _stream_handle(stream)))
 
 
@@ -418,7 +426,7 @@ def tune_batch(srcs, workspace, every: int = 1, stream=None, dtype: int | None =
     out = (Params * n)()
     hist = np.zeros((n, 256), dtype=np.uint64)
     dt = dtype_of(srcs[0], dtype) if n else BF16
-    _check(lib().enec_tune_batch(items, n, dt, every, out, hist.ctypes.data, workspace.data_ptr(),
+    _check(lib().raw.enec_tune_batch(items, n, dt, every, out, hist.ctypes.data, workspace.data_ptr(),
                                  workspace.numel() * workspace.element_size(), _stream_handle(stream)), "enec_tune_batch")
     raw = bytes(out)
     prm = [tuple(raw[4 * i:4 * i + 4]) for i in range(n)]

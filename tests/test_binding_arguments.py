@@ -34,12 +34,8 @@ def enec(monkeypatch):
 
 def _record(monkeypatch, enec, name):
     calls = []
-    monkeypatch.setattr(_where(enec), name, lambda *a: calls.append(a) or 0)
+    monkeypatch.setattr(enec.lib().raw, name, lambda *a: calls.append(a) or 0)
     return calls
-
-
-def _where(enec):
-    return getattr(enec.lib(), "raw", enec.lib())
 
 
 def _bytes(pointer, n):
@@ -72,3 +68,22 @@ def test_tuples_may_come_from_an_iterator(enec, monkeypatch):
     assert enec.compress_batch(SRCS, (p for p in [(122, 6, 3, 16), None]), OUTS, WS, dtype=0) == 0
     items = [struct.unpack_from("<QQI4xQQQQ", _bytes(calls[0][0], 112), 56 * i) for i in range(2)]
     assert items[0][3] != 0 and items[1][3] == 0
+
+
+def test_the_prototypes_of_lib_tell_their_structures_apart(enec):
+    """lib() hands out the entry points with the structures they take; the binding's own calls, which pass packed bytes, don't
+    loosen them.  Every accepted call fails in the library's first check (dtype 7)."""
+    from paper_2604_03298_amd.enec import CompressItem, DecompressItem, Params, PerBlockItem, TuneItem
+    L, at = enec.lib(), 1 << 20
+    prm = Params(122, 6, 3, 16)
+    for given in (prm, C.byref(prm), C.pointer(prm), None):
+        assert L.enec_compress(at, 10, 7, 0, given, at, 1 << 20, None, at, 1 << 20, None) == enec.E_DTYPE
+    assert L.enec_compress_batch((CompressItem * 1)(), 1, 7, at, 1 << 20, None) == enec.E_DTYPE
+    assert L.enec_compress_per_block_batch((PerBlockItem * 1)(), 1, 7, 16, at, 1 << 20, None) == enec.E_DTYPE
+    hist = (C.c_uint64 * 256)()
+    assert L.enec_tune_batch((TuneItem * 1)(), 1, 7, 1, C.byref(prm), hist, at, 1 << 20, None) == enec.E_DTYPE
+    for name, before, after in (("enec_compress_batch", (), (1, 7, at, 1 << 20, None)), ("enec_compress_per_block_batch", (), (1, 7, 16, at, 1 << 20, None)),
+                                ("enec_tune_batch", (), (1, 7, 1, prm, hist, at, 1 << 20, None)),
+                                ("enec_compress", (at, 10, 7, 0), (at, 1 << 20, None, at, 1 << 20, None))):
+        with pytest.raises(C.ArgumentError):
+            getattr(L, name)(*before, (DecompressItem * 1)(), *after)
