@@ -74,13 +74,19 @@ def test_a_workspace_with_room_for_the_look_back_words_only(gpu, oracle):
     assert rc == enec.E_CAPACITY
 
 
-def test_a_wait_given_up_shows_in_the_header(gpu, oracle, monkeypatch):
-    """With a bound of one poll every run ends with status 0 and the oracle's stream, or with ENEC_E_HIP and size 0."""
-    torch, enec = gpu.torch, gpu.enec
+def _test_library(enec):
+    """libenec_test.so, which reads ENEC_SPIN_LIMIT."""
     L = C.CDLL(os.path.join(os.path.dirname(enec.LIB_PATH), "libenec_test.so"))
     L.enec_compress_per_block.restype = C.c_int
     L.enec_compress_per_block.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.c_uint32, C.c_uint32, C.c_void_p, C.c_size_t, C.c_void_p,
                                           C.c_void_p, C.c_size_t, C.c_void_p]
+    return L
+
+
+def test_a_wait_given_up_shows_in_the_header(gpu, oracle, monkeypatch):
+    """With a bound of one poll every run ends with status 0 and the oracle's stream, or with ENEC_E_HIP and size 0."""
+    torch, enec = gpu.torch, gpu.enec
+    L = _test_library(enec)
     w = _tensor(1900 * B + 77, BF16, 5)
     s_o = oracle.compress_per_block(w, B, BF16, 16)[1]
     ref = torch.from_numpy(s_o).cuda()
@@ -106,3 +112,30 @@ def test_a_wait_given_up_shows_in_the_header(gpu, oracle, monkeypatch):
     assert enec.compress_per_block(src[:w.size], out, ws, block_size=B, out_bytes=size) == 0
     torch.cuda.synchronize()
     assert int(size.item()) == s_o.size and torch.equal(out[:s_o.size], ref)
+
+
+def test_a_dirty_workspace_ends_in_a_status_not_in_a_hang(gpu, oracle, monkeypatch):
+    """Accumulators that claim 100 blocks too many, as a call that died may leave them: no group of blocks ever completes, so every
+    block behind the first group gives up after 200 polls.  Each is then stored at a start that misses sizes, below its own."""
+    torch, enec = gpu.torch, gpu.enec
+    L = _test_library(enec)
+    w = _tensor(400 * B + 9, BF16, 6)
+    src = gpu.to_dev(w, BF16)
+    ws = enec.new_workspace(w.size)
+    state = 1024 + 16 * 2048                             # control records and histograms, then the state words
+    words = ws[state:state + (ws.numel() - state) // 8 * 8].view(torch.int64)
+    words[:words.numel() // 9] = 100 << 48
+    out = torch.zeros(enec.compress_bound_per_block(w.size), dtype=torch.uint8, device="cuda")
+    size = torch.full((1,), -1, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    monkeypatch.setenv("ENEC_SPIN_LIMIT", "200")
+    assert L.enec_compress_per_block(src.data_ptr(), w.size, 0, B, 16, out.data_ptr(), out.numel(), size.data_ptr(), ws.data_ptr(), ws.numel(), None) == 0
+    torch.cuda.synchronize()
+    monkeypatch.delenv("ENEC_SPIN_LIMIT")
+    info = enec.stream_info(out[:64].cpu().numpy())
+    assert info["status"] == enec.E_HIP and info["total_bytes"] == 0 and int(size.item()) == 0
+    enec.workspace_init(ws)
+    assert enec.compress_per_block(src[:w.size], out, ws, block_size=B, out_bytes=size) == 0
+    torch.cuda.synchronize()
+    s_o = oracle.compress_per_block(w, B, BF16, 16)[1]
+    assert int(size.item()) == s_o.size and np.array_equal(out[:s_o.size].cpu().numpy(), s_o)
