@@ -3,7 +3,9 @@
  *
  * C ABI.  Every entry point takes plain pointers and sizes; the doc of each argument
  * says whether it is a HOST or a DEVICE pointer.  The library allocates no device
- * memory: inputs, outputs and the workspace are the caller's.  All work is enqueued
+ * memory: inputs, outputs and the workspace are the caller's.  (The parameter search
+ * receives its counts in pinned host memory: a slot of 32 KB for each call that is
+ * running, of which four are kept until the process ends.)  All work is enqueued
  * on the HIP stream passed as `stream` (a hipStream_t handed over as void*, NULL =
  * the default stream).  Unless stated otherwise a call returns as soon as its work
  * is enqueued.
@@ -153,7 +155,9 @@ int enec_compress_static(const void *in, size_t n_elems, int dtype, uint32_t blo
 
 /* Compress several tensors with as few kernel launches as possible: tensors that share (m, n - m, L,
  * block size) go into one launch (up to 16 tensors each), whose workgroups walk the data blocks of all of them, so that
- * small tensors cost no launch of their own and the device never drains between tensors.
+ * small tensors cost no launch of their own and the device never drains between tensors.  Tensors of one data block that
+ * share these with no longer tensor of the call go into launches of their own kernel, up to 16 of one L each, whatever
+ * their tuples and block sizes.
  * Every field of an item means what the argument of the same name means for enec_compress
  * (params == NULL tunes that tensor first, which makes the call synchronous).  The workspace
  * must hold enec_workspace_bytes(sum of the items' n_elems, block size).  Items are independent:
@@ -193,8 +197,8 @@ int enec_decompress_with_header(const void *in, size_t in_bytes, const void *hos
                                 size_t n_elems, uint32_t *status, void *stream);
 
 /* Decompress several streams with one launch per (dtype, group length, block size) and sixteen streams, whatever
- * their tuples (streams of a few blocks join the launch of a larger block size); fields as the arguments of
- * enec_decompress_with_header.  Fully asynchronous. */
+ * their tuples; streams of at most sixteen blocks join the launch of a larger block size where that saves a launch.
+ * Fields as the arguments of enec_decompress_with_header.  Fully asynchronous. */
 typedef struct {
     const void *in;             /* DEVICE */
     size_t in_bytes;
@@ -260,12 +264,13 @@ int enec_pipeline_trace(enec_pipeline *pipeline, float *ms, size_t max_steps, si
  *   params     HOST, written before return
  *   histogram  NULL, or HOST array of 256 u64 that receives the exponent counts
  *   workspace  DEVICE, as for enec_compress (workspace_bytes: its size)
- * Synchronous: returns after the histogram has been copied back. */
+ * Synchronous: waits for the stream, and returns when the counts have arrived (in pinned memory, see the top).  On a stream that
+ * is being captured: ENEC_E_HIP, with nothing enqueued. */
 int enec_tune(const void *in, size_t n_elems, int dtype, enec_params *params,
               uint64_t *histogram, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Many tensors at once: the histograms of up to sixteen tensors are counted into sixteen slots of the
- * workspace, copied back together, and the stream is waited for once per sixteen tensors (tuning a
+ * workspace, handed over together, and the stream is waited for once per sixteen tensors (tuning a
  * layer's tensors one by one spends most of its time in those waits).
  *   items       HOST array; in = DEVICE, 16-byte aligned
  *   every       1 = all exponents, k = every k-th chunk of 4096 elements (see enec_tune_sampled)
@@ -307,7 +312,8 @@ int enec_compress_sampled(const void *in, size_t n_elems, int dtype, uint32_t bl
  *   the tuples, 4 bytes per block (b, n, m, 0), zero-padded to a multiple of 16, between the offset
  *   table and the fp32 region / the payloads.
  * enec_decompress, enec_decompress_with_header and enec_decompress_batch read such streams as any
- * other (in a batch they share a launch with one-tuple streams of their element format, group length and block size).  Arguments as for enec_compress, without params;
+ * other (in a batch they share launches with one-tuple streams, see enec_decompress_batch).  Arguments as for enec_compress,
+ * without params;
  * group_length = 8, 16, 32 or 0 (= 16) is the group length the blocks are coded with (ENEC_E_PARAMS if
  * the block size does not admit it; the search evaluates Eq. 4, 1/L + n + (m - n) p(m)^L, with that length);
  * out_capacity >= enec_compress_bound_per_block(n_elems, dtype, block_size) (0 for an invalid dtype

@@ -34,8 +34,9 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950",
 
 def _units():
     units = [("enec_api.o", [SOURCES[0]]), ("enec_api_test.o", ["-DENEC_TEST_HOOKS", SOURCES[0]]),
-             # (no constants kept in registers over a loop with sixteen packers: see enec_per_block.hpp)
-             ("enec_per_block.o", ["-mllvm", "-disable-machine-licm", SOURCES[2]]), 
+             # (no constants kept in registers over a loop with sixteen packers: compress_per_block_stream_kernel in
+             # enec_per_block.hpp, where both sides' figures stand; the unit's other kernel is the same either way)
+             ("enec_per_block.o", ["-mllvm", "-disable-machine-licm", SOURCES[2]]),
              ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]]),
              ("enec_single.o", [SOURCES[5]])]
     for lpg in (2, 1, 4):           # lanes per group: group lengths 16, 8, 32

@@ -1254,7 +1254,9 @@ __global__ void __launch_bounds__(HIST_THREADS) histogram_kernel(const Histogram
     constexpr uint32_t PER_VEC = DT == DT_FP32 ? 4u : 8u;        // elements in 16 bytes
     const uint64_t nvec = n_elems / PER_VEC;
     const uint64_t stride = (uint64_t)wgs * HIST_THREADS;
-    // the LDS counters cannot overflow: a workgroup counts at most 2^34 / 256 elements
+    // the LDS counters cannot overflow: the workgroups are shared out over the launch's tensors by size, a tensor gets at least
+    // half of its exact share of HIST_WORKGROUPS (rounded down, but not below one), so a workgroup counts at most twice the
+    // launch's sixteen times 2^34 elements / 256 = 2^31
     // the sample: chunks of SAMPLE_CHUNK elements whose number is a multiple of `every`
     constexpr uint32_t LOG_VPC = DT == DT_FP32 ? 10u : 9u;      // 16-byte vectors in a chunk
     const uint64_t chunks = (nvec + (1u << LOG_VPC) - 1u) >> LOG_VPC;

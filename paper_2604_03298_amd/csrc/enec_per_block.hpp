@@ -632,14 +632,19 @@ compress_per_block_kernel(const PbCompressArgs p)
 // next block travel while a block is worked on, and a block is stored an iteration after its size was published.  Three
 // workgroups per CU (50 KB of LDS: two images of the worst case and the waiting block's raw bytes).  An iteration takes 12 us: rows
 // and split 0.6, counting 1.9, sums and search 1.4, transform 0.7, packing 1.6, start of the waiting block 1.8, loads
-// and stores 3.0, rest 0.9.  us, against one workgroup per block with the former search in brackets:
-// (before the waves' priority) 67e6 elements of mixed blocks 60.3 (79.3), 34e6 Gaussian 34.8 (50.7), 134e6 119.8 (143.3), 405 MB layer 186 (216), fp16
-// 34e6 37.8 (52.5), fp32 56.8 (62.7), 1e6 10.5 (13.1).
-// Looking up the start during the search and storing then, by the other three waves, was slower than all of these (layer
-// 244, mixed blocks 76): the blocks before have not published by then, and the wait for them grows from 1.8 to 5 us.
+// and stores 3.0, rest 0.9.  us per call, one workgroup per block with the former search -> this kernel:
+//   before the waves' priority (below): 67e6 elements of mixed blocks 79.3 -> 60.3, 34e6 Gaussian 50.7 -> 34.8, 134e6
+//   143.3 -> 119.8, fp16 34e6 52.5 -> 37.8, fp32 62.7 -> 56.8, 1e6 13.1 -> 10.5
+//   a layer of Gaussian matrices, seven tensors of 405 MB: 210 -> 174, with the priority 154 (with two norm vectors, which take
+//   the other kernel: 220 -> 185 -> 165); one with a scale per row and outliers, nine tensors: 234 -> 205 -> 191
+// Looking up the start during the search and storing then, by the other three waves, was slower than all of these (mixed
+// blocks 76): the blocks before have not published by then, and the wait for them grows from 1.8 to 5 us.
 // The unit is compiled without the hoisting of constants out of loops: the sixteen packers' constants, kept in registers
-// over the whole loop, cost 4 to 12 spilled registers and 4 % (34e6 elements 40.0).  fp32 has twice the rows in flight
-// and runs two waves per SIMD.
+// over the whole loop, cost the 16-bit formats 12 to 15 spilled registers (34e6 elements: bf16 38.3 against 36.1 us with
+// groups of 16, 40.4 / 35.8 of 8, 41.8 / 39.1 of 32; fp16 41.4 / 38.9, 41.1 / 40.0, 43.9 / 41.7).  fp32 has twice the rows in
+// flight, runs two waves per SIMD and spills neither way; it loses by it (57.9 with the hoisting, 60.2 without, groups of 8
+// 57.3 / 61.6).  compress_per_block_kernel, which has no loop over blocks, is the same either way: equal registers and
+// times within 0.5 % in blocks of 2048 to 32768.
 // ---------------------------------------------------------------------------------
 #define PB_STREAM_WAVES (DT == DT_FP32 ? 2 : 3)
 
