@@ -675,13 +675,16 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
                 c.b = prm.b; c.n = prm.n; c.m = prm.m;
                 c.mode = subtract_mode(prm.b, prm.n, dtype);
                 largest = std::max(largest, prep[j].B);
-                lds = std::max(lds, (size_t)prep[j].B / (8 * prm.L) + (size_t)(prm.n + (dtype == ENEC_FP16 ? 3 : 0)) * prep[j].B / 8);
+                lds = std::max(lds, (size_t)single_lds_bytes(prep[j].B, prm.L, prm.n - prm.m));
                 done[j] = 1;
             }
             for (size_t j = count; j < (size_t)MAX_BATCH; ++j) sa.item[j] = sa.item[0];
             SingleFn fn = pick_compress_single(dtype, prep[i].prm.L);
             if (!fn) return ENEC_E_PARAMS;
-            hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(largest / 64 < 64 ? 64 : largest / 64), lds, s, sa);
+            const unsigned threads = std::min(largest / 8, SINGLE_THREADS);
+            // (a block of 32768 elements whose records hold whole exponents: more than 64 KB has to be asked for)
+            if (lds > 65536 && resident_workgroups((const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
+            hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);
             continue;
         }
         CompressArgs a;

@@ -100,6 +100,9 @@ struct SingleArgs {
     SingleItem item[MAX_BATCH];
 };
 
+constexpr uint32_t SINGLE_THREADS = 512;
+// its dynamic LDS: the transformed bytes in element order (y; fp16: with the three left-over mantissa bits in bits 5..7) | mask | high records
+constexpr uint32_t single_lds_bytes(uint32_t B, uint32_t L, uint32_t a) { return B + B / (8u * L) + a * B / 8u; }
 using SingleFn = void (*)(const SingleArgs);
 SingleFn pick_compress_single(int dtype, unsigned L);
 

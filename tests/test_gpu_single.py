@@ -73,6 +73,17 @@ def test_every_width_pair(gpu, oracle, n):
         _run(gpu, oracle, dtype, jobs)
 
 
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+def test_whole_exponents_as_records(gpu, oracle, dtype):
+    """m = 0: no low plane (fp16: three bits), records as long as they get; blocks of 32768 take more than 64 KB of LDS."""
+    rng = np.random.default_rng(dtype)
+    full = 5 if dtype == FP16 else 8
+    jobs = [(_tensor(rng, dtype, B - 3, 0, EXP[dtype], 1.0), (7, full, 0, L), B)
+            for B in (2048, 4096, 16384, 32768) for L in (8, 16, 32) if 128 * L <= B <= 2048 * L]
+    for j in jobs:
+        _run(gpu, oracle, dtype, [j])
+
+
 def test_beside_larger_tensors(gpu, oracle):
     """One-block tensors that share (m, n, L, block size) with a tensor of more blocks go through its launch, the others don't."""
     rng = np.random.default_rng(3)
