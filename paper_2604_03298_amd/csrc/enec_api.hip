@@ -200,13 +200,15 @@ void fill_compress_item(CompressArgs &a, size_t &acc, size_t &word, void *worksp
 template <class Fn>
 void launch_compress(Fn fn, CompressArgs &a, unsigned resident, unsigned threads, size_t lds, hipStream_t s)
 {
+    // (tensors of one block come on top of the grid, which may leave workgroups waiting until one of theirs ends: these draw
+    // their first block then)
     const unsigned grid = persistent_grid(a.total, resident);
     a.ncls = grid < 8 ? grid : 8;
     // The next ticket is drawn while the current block is worked on only if there are blocks for
     // two rounds: with fewer, an early workgroup would take the block of one that starts a moment later.
     a.lookahead = a.total >= 2 * grid ? 1u : 0u;
     a.spin_limit = spin_limit();
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), lds, s, a);
+    hipLaunchKernelGGL(fn, dim3(grid + a.n_single), dim3(threads), lds, s, a);
 }
 
 // Dynamic LDS of a decompression workgroup of a 16-bit format, so that a CU works on 65536 elements at a time (the
@@ -637,9 +639,11 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
     }
 
     // ---- one launch per group of tensors that share (m, n - m, L, block size) ----------------
-    // A tensor of one block goes with others of its kind, whatever their tuples, to a kernel without the machinery for
-    // the order of blocks (the layer of 405 MB with its two norm vectors 140.8 -> 138.4 us, one of hidden size 1024 29.6 ->
-    // 26, two fp16 vectors of 4096 elements 14.9 -> 11.0), unless the call has a launch that it can join.
+    // A tensor of one block whose (m, n - m, L, block size) no longer tensor has is coded without the machinery for the order
+    // of blocks (compress_one_block, whatever its tuple and block size): by the first workgroups of the first launch of the
+    // default block size and the same L, or, where the call has none or its LDS is too small for the tensor's records, with others
+    // of its kind in a launch of their own, after the others.  Its own launch behind that of a layer of 405 MB took 4 us for two
+    // norm vectors (139.6 -> 135.4 us with the kernel's own gain).
     auto kernel_of = [&](size_t j) {
         return prep[j].B << 16 | (uint32_t)prep[j].prm.n << 12 | (uint32_t)prep[j].prm.m << 8 | prep[j].prm.L;
     };
@@ -648,8 +652,22 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
         if (prep[i].nb > 1 && std::find(large.begin(), large.end(), kernel_of(i)) == large.end()) large.push_back(kernel_of(i));
     auto alone = [&](size_t j) { return prep[j].nb == 1 && std::find(large.begin(), large.end(), kernel_of(j)) == large.end(); };
     std::vector<char> done(n_items, 0);
+    auto take_single = [&](SingleItem &c, size_t j) {
+        const enec_params &prm = prep[j].prm;
+        c.in = static_cast<const uint16_t *>(items[j].in);
+        c.out = static_cast<uint8_t *>(items[j].out);
+        c.out_bytes = items[j].out_bytes;
+        c.n_elems = items[j].n_elems;
+        c.payload_base = (uint32_t)payload_base(items[j].n_elems, prep[j].B, dtype);
+        c.tail_base = (uint32_t)table_end(items[j].n_elems, prep[j].B);
+        c.logB = ilog2(prep[j].B);
+        c.b = prm.b; c.n = prm.n; c.m = prm.m;
+        c.mode = subtract_mode(prm.b, prm.n, dtype);
+        done[j] = 1;
+        return (size_t)single_lds_bytes(prep[j].B, prm.L, prm.n - prm.m);
+    };
     for (size_t i = 0; i < n_items; ++i) {
-        if (done[i]) continue;
+        if (done[i] || alone(i)) continue;
         if (prep[i].nb == 0) {
             compress_empty_kernel<<<1, 64, 0, s>>>(static_cast<uint8_t *>(items[i].out), items[i].out_bytes,
                                                    prep[i].B, prep[i].prm.b, prep[i].prm.n, prep[i].prm.m,
@@ -657,41 +675,11 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
             done[i] = 1;
             continue;
         }
-        if (alone(i)) {
-            SingleArgs sa;
-            size_t count = 0, lds = 0;
-            uint32_t largest = 0;
-            for (size_t j = i; j < n_items && count < (size_t)MAX_BATCH; ++j) {
-                if (done[j] || prep[j].prm.L != prep[i].prm.L || !alone(j)) continue;
-                const enec_params &prm = prep[j].prm;
-                SingleItem &c = sa.item[count++];
-                c.in = static_cast<const uint16_t *>(items[j].in);
-                c.out = static_cast<uint8_t *>(items[j].out);
-                c.out_bytes = items[j].out_bytes;
-                c.n_elems = items[j].n_elems;
-                c.payload_base = (uint32_t)payload_base(items[j].n_elems, prep[j].B, dtype);
-                c.tail_base = (uint32_t)table_end(items[j].n_elems, prep[j].B);
-                c.logB = ilog2(prep[j].B);
-                c.b = prm.b; c.n = prm.n; c.m = prm.m;
-                c.mode = subtract_mode(prm.b, prm.n, dtype);
-                largest = std::max(largest, prep[j].B);
-                lds = std::max(lds, (size_t)single_lds_bytes(prep[j].B, prm.L, prm.n - prm.m));
-                done[j] = 1;
-            }
-            for (size_t j = count; j < (size_t)MAX_BATCH; ++j) sa.item[j] = sa.item[0];
-            SingleFn fn = pick_compress_single(dtype, prep[i].prm.L);
-            if (!fn) return ENEC_E_PARAMS;
-            const unsigned threads = std::min(largest / 8, SINGLE_THREADS);
-            // (a block of 32768 elements whose records hold whole exponents: more than 64 KB has to be asked for)
-            if (lds > 65536 && resident_workgroups((const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
-            hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);
-            continue;
-        }
         CompressArgs a;
         a.ws_ctl = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_CTL);
         a.B = prep[i].B;
         a.logB = ilog2(a.B);
-        a.n_items = 0;
+        a.n_items = a.n_single = 0;
         a.total = 0;
         size_t word = acc_words, acc = 0;   // scan words handed out to this launch (tags make reuse between launches safe)
         for (size_t j = i; j < n_items && a.n_items < (uint32_t)MAX_BATCH; ++j) {
@@ -711,7 +699,30 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
                            (compress_sm_in_lds(dtype, a.B == 1u << DEFAULT_LOGB) ? a.B : 0);
         const unsigned resident = resident_workgroups((const void *)fn, threads, lds);
         if (resident == 0) return ENEC_E_HIP;
+        if (a.B == 1u << DEFAULT_LOGB)
+            for (size_t j = 0; j < n_items && a.n_single < (uint32_t)MAX_BATCH; ++j)
+                if (!done[j] && alone(j) && prep[j].prm.L == prep[i].prm.L &&
+                    single_lds_bytes(prep[j].B, prep[j].prm.L, prep[j].prm.n - prep[j].prm.m) <= lds)
+                    take_single(a.single[a.n_single++], j);
         launch_compress(fn, a, resident, threads, lds, s);
+    }
+    for (size_t i = 0; i < n_items; ++i) {
+        if (done[i]) continue;
+        SingleArgs sa;
+        size_t count = 0, lds = 0;
+        uint32_t largest = 0;
+        for (size_t j = i; j < n_items && count < (size_t)MAX_BATCH; ++j) {
+            if (done[j] || prep[j].prm.L != prep[i].prm.L) continue;
+            lds = std::max(lds, take_single(sa.item[count++], j));
+            largest = std::max(largest, prep[j].B);
+        }
+        for (size_t j = count; j < (size_t)MAX_BATCH; ++j) sa.item[j] = sa.item[0];
+        SingleFn fn = pick_compress_single(dtype, prep[i].prm.L);
+        if (!fn) return ENEC_E_PARAMS;
+        const unsigned threads = std::min(largest / 8, SINGLE_THREADS);
+        // (a block of 32768 elements whose records hold whole exponents: more than 64 KB has to be asked for)
+        if (lds > 65536 && resident_workgroups((const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
+        hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);
     }
     return hipGetLastError() == hipSuccess ? ENEC_OK : ENEC_E_HIP;
 }
@@ -848,7 +859,7 @@ int enec_compress_per_block_batch(const enec_per_block_item *items, size_t n_ite
             a.ws_ctl = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_CTL);
             a.B = ENEC_DEFAULT_BLOCK;
             a.logB = DEFAULT_LOGB;
-            a.n_items = a.total = 0;
+            a.n_items = a.n_single = a.total = 0;
             for (; i < n_items && a.n_items < (uint32_t)MAX_BATCH; ++i) {
                 if (!streamed(i)) continue;
                 fill_compress_item(a, acc, word, workspace, items[i].in, items[i].out, items[i].out_bytes, items[i].n_elems, dtype);

@@ -88,14 +88,6 @@ CompressFn pick_compress_per_block_stream(int dtype, unsigned L);
 
 // Compression of tensors of one data block each (enec_single.hpp, compiled in enec_single.hip), whatever their tuples and
 // block sizes: workgroup i takes tensor i.
-struct SingleItem {
-    const uint16_t *in;
-    uint8_t *out;
-    uint64_t *out_bytes;        // device-accessible or null
-    uint64_t n_elems;
-    uint32_t payload_base, tail_base;
-    uint32_t logB, b, n, m, mode;       // mode as in CompressItem
-};
 struct SingleArgs {
     SingleItem item[MAX_BATCH];
 };

@@ -93,3 +93,29 @@ def test_beside_larger_tensors(gpu, oracle):
         w = _tensor(rng, BF16, (B - 5, 3 * B + 1, 77, B, 9 * B)[i % 5], 100 + i % 3, 118, 0.02)
         jobs.append((w, (115, 5, 2 + i % 3, 16), B))
     _run(gpu, oracle, BF16, jobs)
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+@pytest.mark.parametrize("L", [8, 16, 32])
+def test_in_the_launch_of_a_larger_tensor(gpu, oracle, dtype, L):
+    """One-block tensors with tuples and block sizes of their own beside tensors of the default block size: the first sixteen of the
+    same group length ride along, unless their records need more LDS than the larger tensors' kernel has (the second call: a tuple of
+    one bit beside whole exponents as records), one of them with an exponent outside its window."""
+    rng = np.random.default_rng(30 + 3 * dtype + L)
+    full = 5 if dtype == FP16 else 8
+    lo, hi = (10, 17) if dtype == FP16 else (100, 118)
+    small = []
+    for i in range(19):
+        B = max((2048, 4096, 8192, 16384)[i % 4], 128 * L)
+        w = _tensor(rng, dtype, (1, 700, B - 1, B)[i // 4 % 4] if B < 16384 else B - 9 * i, lo, hi, 0.1)
+        b, n, m, _ = oracle.tune(w, dtype)
+        small.append((w, (b, n, m, L), B))
+    w = small[5][0].copy()
+    keep = WORD[dtype](~(EXP[dtype] << SHIFT[dtype]) & np.iinfo(WORD[dtype]).max)
+    w[w.size // 2] = (w[w.size // 2] & keep) | (WORD[dtype](EXP[dtype]) << WORD[dtype](SHIFT[dtype]))
+    small[5] = (w, small[5][1], small[5][2])
+    big = _tensor(rng, dtype, 5 * 16384 + 77, lo, hi, 0.05)
+    _run(gpu, oracle, dtype, small[:7] + [(big, oracle.tune(big, dtype)[:3] + (L,), 16384)] + small[7:] + [(small[0][0], small[0][1][:3] + (16,), 4096)])
+    flat = np.full(3 * 16384 - 5, WORD[dtype](lo) << WORD[dtype](SHIFT[dtype]), dtype=WORD[dtype])
+    wide = [(_tensor(rng, dtype, 16384 - i, 0, EXP[dtype], 1.0), (7, full, 0, L), 16384) for i in range(2)]
+    _run(gpu, oracle, dtype, wide + [(flat, (lo, 1, 1, L), 16384)] + small[:2])
