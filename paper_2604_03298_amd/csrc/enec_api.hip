@@ -4,6 +4,8 @@
 #include "enec_kernels.hpp"
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -45,10 +47,12 @@ __global__ void __launch_bounds__(256) copy_kernel(uint4 *__restrict__ dst, cons
     for (uint64_t v = (uint64_t)blockIdx.x * 256u + threadIdx.x; v < nvec; v += stride) dst[v] = src[v];
 }
 
-// the tuner's counts on their way to the host (pinned memory): one workgroup per histogram
-__global__ void __launch_bounds__(128) hand_over_counts_kernel(uint4 *host, const uint4 *hist)
+// for a workspace that is not in the state the last call left it in: the tuner's counts, one workgroup per histogram, and the
+// number of workgroups that have added theirs
+__global__ void __launch_bounds__(128) clear_counts_kernel(uint4 *hist, uint32_t *done)
 {
-    host[blockIdx.x * 128u + threadIdx.x] = hist[blockIdx.x * 128u + threadIdx.x];
+    hist[blockIdx.x * 128u + threadIdx.x] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0;
 }
 
 }  // namespace enec
@@ -59,7 +63,8 @@ using namespace enec;
 
 // workspace: [0, 1024) control records of the block classes | [1024, 33792) sixteen histograms |
 // group words | block words (the last two sized by the call's block count)
-constexpr size_t WS_CTL = 0, WS_HIST = 1024, WS_HIST_SLOTS = MAX_BATCH, WS_STATE = WS_HIST + WS_HIST_SLOTS * 256 * 8;
+// (the counting kernel's own counter lies in the last control record, whose first six words only are used otherwise)
+constexpr size_t WS_CTL = 0, WS_HIST_DONE = 1008, WS_HIST = 1024, WS_HIST_SLOTS = MAX_BATCH, WS_STATE = WS_HIST + WS_HIST_SLOTS * 256 * 8;
 inline size_t ws_groups(size_t nb) { return (nb + GROUP - 1) / GROUP; }
 // The state words behind WS_STATE: first the group accumulators, which every call leaves zero, in
 // a region whose length depends only on the size of the workspace (1/9 of the words), then the
@@ -224,8 +229,8 @@ constexpr bool holds_65536_elements(uint32_t B)
 static_assert(holds_65536_elements(4096) && holds_65536_elements(8192) && holds_65536_elements(16384) &&
                   holds_65536_elements(32768), "LDS of a decompression workgroup");
 
-// Pinned memory in which a call that tunes finds its counts: a kernel stores them there, which takes 1.3 to 2.5 us for one
-// tensor and 4.2 for nine, where a copy to pageable memory takes 14.  A call takes a slot for as long as it runs; up to four are kept for later calls, for
+// Pinned memory in which a call that tunes finds its counts: the counting kernel stores them there, where a copy to pageable
+// memory takes 14 us.  A call takes a slot for as long as it runs; up to four are kept for later calls, for
 // all threads, streams and devices, more are given back when their call ends, and these when the process does.
 class CountSlots {
     // Another thread may be capturing a graph: allocating or freeing would end its capture in any mode but this one.
@@ -235,7 +240,8 @@ class CountSlots {
         ~SparesCaptures() { if (swapped) { hipStreamCaptureMode back = mode; (void)hipThreadExchangeStreamCaptureMode(&back); } }
     };
 public:
-    static constexpr size_t BYTES = WS_HIST_SLOTS * 256 * 8, KEPT = 4;
+    // the counts of WS_HIST_SLOTS tensors, then the word that says that they have arrived
+    static constexpr size_t ARRIVED = WS_HIST_SLOTS * 256 * 8, BYTES = ARRIVED + 64, KEPT = 4;
     void *take()
     {
         {
@@ -268,6 +274,16 @@ private:
 };
 // made by the first call that tunes, after the runtime has started, so that it ends before the runtime does
 CountSlots &count_slots() { static CountSlots slots; return slots; }
+
+// elements that the parameter search looks at: those of every `every`-th chunk, the first one included
+uint64_t sampled_elements(uint64_t n, uint32_t every)
+{
+    const uint64_t chunks = (n + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
+    if (chunks == 0) return 0;
+    const uint64_t picked = (chunks + every - 1) / every;
+    const bool last = (chunks - 1) % every == 0;             // the last chunk, perhaps a short one, is among them
+    return picked * SAMPLE_CHUNK - (last ? chunks * SAMPLE_CHUNK - n : 0);
+}
 
 unsigned bit_length(unsigned v) { return v ? 32u - (unsigned)__builtin_clz(v) : 0u; }
 
@@ -490,7 +506,6 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
     // and the stream is waited for once
     for (size_t first = 0; first < n_items; first += WS_HIST_SLOTS) {
         const size_t count = n_items - first < WS_HIST_SLOTS ? n_items - first : WS_HIST_SLOTS;
-        fill_zero_kernel<<<(unsigned)count, 256, 0, s>>>(reinterpret_cast<uint4 *>(dhist), count * 256 * 8 / 16);
         // One launch for the sixteen: a workgroup per HIST_THREADS vectors of the sample, or HIST_WORKGROUPS shared out
         // by size, rounded down but at least one for each tensor (so up to fifteen more).
         HistogramArgs a;
@@ -514,23 +529,49 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
             d.count = (uint32_t)share;
             grid += d.count;
         }
+        volatile uint32_t *arrived = reinterpret_cast<volatile uint32_t *>(host + CountSlots::ARRIVED / 8);
+        *arrived = 0;
         if (grid) {
             for (uint32_t j = a.n_items; j < (uint32_t)MAX_BATCH; ++j) a.item[j] = a.item[0];
-            if (dtype == ENEC_FP32) histogram_kernel<DT_FP32><<<grid, HIST_THREADS, 0, s>>>(a);
-            else if (dtype == ENEC_FP16) histogram_kernel<DT_FP16><<<grid, HIST_THREADS, 0, s>>>(a);
-            else histogram_kernel<DT_BF16><<<grid, HIST_THREADS, 0, s>>>(a);
+            a.done = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_HIST_DONE);
+            a.counts = dhist;
+            a.host = reinterpret_cast<unsigned long long *>(host);
+            a.arrived = const_cast<uint32_t *>(arrived);
+            a.n_counts = (uint32_t)count * 256u;
+        } else {
+            std::memset(host, 0, count * 256 * 8);
         }
-        uint4 *to = reinterpret_cast<uint4 *>(host);
-        const uint4 *from = reinterpret_cast<const uint4 *>(dhist);
-        void *args[] = {&to, &from};
-        if (hipLaunchKernel((const void *)hand_over_counts_kernel, dim3((unsigned)count), dim3(128), args, 0, s) != hipSuccess) {
-            (void)hipGetLastError();
-            count_slots().give(host);
-            return ENEC_E_HIP;
-        }
-        if (hipStreamSynchronize(s) != hipSuccess) {
-            (void)hipGetLastError();
-            return ENEC_E_HIP;                 // (the slot is not given back: a kernel may still be about to write there)
+        const void *fn = dtype == ENEC_FP32 ? (const void *)histogram_kernel<DT_FP32>
+                       : dtype == ENEC_FP16 ? (const void *)histogram_kernel<DT_FP16> : (const void *)histogram_kernel<DT_BF16>;
+        // Every call leaves the counters zero.  A workspace in which they were not would show in the sums, or in a kernel that
+        // ends without handing over: it is cleared then, and counted once more.
+        for (int attempt = 0; attempt < 2; ++attempt) {
+            if (attempt) clear_counts_kernel<<<(unsigned)count, 128, 0, s>>>(reinterpret_cast<uint4 *>(dhist), a.done);
+            void *args[] = {&a};
+            if (grid && hipLaunchKernel(fn, dim3(grid), dim3(HIST_THREADS), args, 0, s) != hipSuccess) {
+                (void)hipGetLastError();
+                count_slots().give(host);
+                return ENEC_E_HIP;
+            }
+            // The counts are looked for in memory for a while: layer 86.5 -> 80.2 us together with the two kernels that are left
+            // out.  The runtime's wait takes over where the stream has more to do first, and finds out if something went wrong.
+            const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+            while (grid && !*arrived && std::chrono::steady_clock::now() < until)
+                for (int i = 0; i < 16 && !*arrived; ++i) __builtin_ia32_pause();
+            if (!*arrived && hipStreamSynchronize(s) != hipSuccess) {
+                (void)hipGetLastError();
+                return ENEC_E_HIP;             // (the slot is not given back: a kernel may still be about to write there)
+            }
+            bool sound = !grid || *arrived;
+            std::atomic_thread_fence(std::memory_order_acquire);
+            for (size_t j = 0; j < count && sound; ++j) {
+                uint64_t sum = 0;
+                for (unsigned x = 0; x < 256; ++x) sum += host[256 * j + x];
+                sound = sum == sampled_elements(items[first + j].n_elems, every);
+            }
+            if (sound) break;
+            if (hipStreamSynchronize(s) != hipSuccess) { (void)hipGetLastError(); return ENEC_E_HIP; }
+            *arrived = 0;
         }
         for (size_t j = 0; j < count; ++j) {
             enec_tune_histogram(host + 256 * j, dtype, &params[first + j]);          // (refuses nothing that can be here)

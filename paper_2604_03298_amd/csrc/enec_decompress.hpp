@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
                                                        : make_uint2(0, 0);
         }
     }
-    wait_loads();
+    wait_accesses();
     __syncthreads();
     // (a wave of fp32 stays whole, its lanes exchange what they have)
     if (DT == DT_FP32 ? MIXED && (tid & ~63u) >= nact : !active) return;

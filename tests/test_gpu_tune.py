@@ -57,3 +57,28 @@ def test_calls_from_many_threads(gpu, oracle):
         assert len(got[i]) == 5
         for _, hist in got[i]:
             assert np.array_equal(hist, want), i
+
+
+@pytest.mark.parametrize("every", [1, 3])
+@pytest.mark.parametrize("dirt", ["counts", "done", "both", "after an early last"])
+def test_a_workspace_whose_counters_are_not_zero(gpu, oracle, dirt, every):
+    """Every call leaves its counters zero for the next one.  Where something else lies there the counts are right all the same."""
+    torch, enec = gpu.torch, gpu.enec
+    rng = np.random.default_rng(3)
+    sizes = [5 * STEP + 3, 1, 4096, 40 * STEP + 4099]
+    data = [rng.integers(15000, 17000, n, dtype=np.uint16) for n in sizes]
+    dev = [torch.from_numpy(w.view(np.int16)).cuda() for w in data]
+    ws = enec.new_workspace(sum(sizes))
+    want = [oracle.histogram(w if every == 1 else oracle.sample(w, every, BF16), BF16) for w in data]
+    for _ in range(2):
+        if dirt in ("counts", "both"):
+            ws[1024:1024 + 4 * 2048] = 7
+        if dirt in ("done", "both"):
+            ws[1008:1012] = 255
+        if dirt == "after an early last":
+            ws[1008] = 40 if every == 1 else 12                   # (a workgroup that is not the last takes itself for it)
+        for _ in range(2):
+            _, hist = enec.tune_batch(dev, ws, every=every, dtype=BF16, want_histograms=True)
+            for h, w in zip(hist, want):
+                assert np.array_equal(h, w)
+    assert int(ws[1008:1012].sum()) == 0 and int(ws[1024:1024 + 4 * 2048].to(torch.int64).sum()) == 0
