@@ -77,6 +77,19 @@ __device__ __forceinline__ void exchange_in_wave()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Zero, known when all fields of the item are: has them loaded together.  Left to itself the compiler asks for each where it
+// is used, and the first workgroups of a launch, whose arguments are in no cache yet, wait for memory three times before they
+// know where their stream is.
+__device__ __forceinline__ uint32_t loaded(const DecompressItem &it)
+{
+    uint32_t zero, zero2;
+    asm("s_mov_b32 %0, 0" : "=s"(zero) : "s"(it.in), "s"(it.out), "s"(it.n_elems), "s"(it.tuples_at), "s"(it.tail_base), "s"(it.payload_base),
+        "s"(it.payload_bytes), "s"(it.status), "s"(it.tuple_stride), "s"(it.logB));
+    asm("s_mov_b32 %0, 0" : "=s"(zero2) : "s"(it.hdr[0]), "s"(it.hdr[1]), "s"(it.hdr[2]), "s"(it.hdr[3]), "s"(it.hdr[4]), "s"(it.hdr[5]),
+        "s"(it.hdr[6]), "s"(it.hdr[7]), "s"(it.hdr[8]), "s"(it.hdr[9]), "s"(it.hdr[10]));
+    return zero | zero2;
+}
+
 // fp32: three waves per SIMD, whose blocks are 115 KB of traffic and need the registers (45e6 elements: 66.8 us with
 // four, four registers spilled; 61.1 with three; 66.6 with two); the 16-bit formats: at least what their LDS allows
 #define DEC_WAVES_MIN (DT == DT_FP32 ? 3 : 4)
@@ -93,12 +106,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     // the stream this block belongs to (the blocks of the launch's streams are numbered through; `first` of
     // the entries that are not used is beyond every block)
-    uint32_t ti = 0;
+    DecompressItem it = p.item[0];
+    uint32_t zero = loaded(it), ti = 0, first = 0;
 #pragma unroll
     for (int i = 1; i < MAX_BATCH; ++i)
-        if (blockIdx.x >= p.first[i]) ti = i;
-    const DecompressItem &it = p.item[ti];
-    const uint32_t k = blockIdx.x - p.first[ti];
+        if (blockIdx.x + zero >= p.first[i]) { ti = i; first = p.first[i]; }
+    if (ti != 0) {
+        it = p.item[ti];
+        zero = loaded(it);
+    }
+    const uint32_t k = blockIdx.x - first + zero;
     const uint32_t logB = MIXED ? it.logB : p.logB, B = MIXED ? 1u << logB : p.B, logC = logB - 3u;
     const uint32_t nact = B >> 6, threads = MIXED ? blockDim.x : nact < 64u ? 64u : nact;     // those that unpack / that load
     const bool active = tid < nact;
