@@ -84,7 +84,7 @@ using PbCompressFn = void (*)(const PbCompressArgs);
 PbCompressFn pick_compress_per_block(int dtype, unsigned L);
 // the same for blocks of the default size, with deferred stores (its arguments are those of the one-tuple kernels)
 constexpr uint32_t pb_image_bytes(uint32_t L) { return (1u << DEFAULT_LOGB) / (8u * L) + (1u << DEFAULT_LOGB); }
-CompressFn pick_compress_per_block_stream(int dtype, unsigned L);
+CompressFn pick_compress_per_block_stream(int dtype, unsigned L), pick_compress_per_block_stream_fp32(unsigned L);
 
 // Compression of tensors of one data block each (enec_single.hpp, compiled in enec_single.hip), whatever their tuples and
 // block sizes: workgroup i takes tensor i.

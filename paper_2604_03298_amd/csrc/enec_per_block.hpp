@@ -642,8 +642,8 @@ compress_per_block_kernel(const PbCompressArgs p)
 // The unit is compiled without the hoisting of constants out of loops: the sixteen packers' constants, kept in registers
 // over the whole loop, cost the 16-bit formats 12 to 15 spilled registers (34e6 elements: bf16 38.3 against 36.1 us with
 // groups of 16, 40.4 / 35.8 of 8, 41.8 / 39.1 of 32; fp16 41.4 / 38.9, 41.1 / 40.0, 43.9 / 41.7).  fp32 has twice the rows in
-// flight, runs two waves per SIMD and spills neither way; it loses by it (57.9 with the hoisting, 60.2 without, groups of 8
-// 57.3 / 61.6).  compress_per_block_kernel, which has no loop over blocks, is the same either way: equal registers and
+// flight, runs two waves per SIMD, spills neither way and loses by it, so its instances are compiled with the hoisting (34e6
+// elements, without / with: groups of 16 57.5 / 55.1, of 8 59.4 / 54.8, of 32 61.7 / 56.8; 67e6 97.8 / 92.9).  compress_per_block_kernel, which has no loop over blocks, is the same either way: equal registers and
 // times within 0.5 % in blocks of 2048 to 32768.
 // ---------------------------------------------------------------------------------
 #define PB_STREAM_WAVES (DT == DT_FP32 ? 2 : 3)
