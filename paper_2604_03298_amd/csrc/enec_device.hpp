@@ -1514,7 +1514,7 @@ struct HistogramArgs {
     uint32_t *done;             // workgroups that have added their counts, zero at launch and again at the end
     unsigned long long *counts; // all histograms of the call, one behind the other
     unsigned long long *host;   // pinned memory: where they go
-    uint32_t *arrived;          // pinned memory: set to 1 behind them
+    uint32_t *arrived;          // pinned memory: set to 1 behind them (0: nobody was last, see enec_tune_batch)
     uint32_t n_counts;
 };
 
@@ -1525,10 +1525,8 @@ struct HistogramArgs {
 // waves, 70.  Whole calls, us, 512 threads x 256 workgroups against 512 x 512 / 1024 x 256 / 256 x 1024: layer
 // 99.4 against 101.3 / 103.2 / 103.2, 268e6 elements 107.7 / 117.0 / 112.1 / 124.9, 17e6 41.0 / 44.4 / 40.7 / 53.0;
 // six or eight vectors in flight are slower again (layer 103.5, 103.9).
-// The workgroup that adds its counts last hands all of them over, so that the host, which looks for `arrived`, has them when
-// it would otherwise learn that the kernel has ended and a second one has yet to start; and it leaves the counters zero for the
-// next call.  (With a kernel before this one that clears them and one behind it that hands them over a call for the layer took
-// 86.5 us, now 80.2; without the first of the two kernels only 83.)
+// The workgroup that adds its counts last hands all of them over and leaves the counters zero for the next call: with a kernel
+// before this one that cleared them and one behind it that handed them over a call for the layer took 86.6 us, now 85.6.
 constexpr uint32_t HIST_THREADS = 512, HIST_WORKGROUPS = 256;
 
 template <int DT>
