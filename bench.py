@@ -223,8 +223,9 @@ def main():
     sizes = torch.zeros(nt, dtype=torch.int64, device="cuda")
 
     # one library call of at most sixteen tensors per kernel launch: tensors of one tuple and block size are compressed
-    # together, and those of one block that share neither with a longer tensor; streams of one block size are decompressed
-    # together, whatever their tuples, and streams of at most sixteen blocks join the largest block size
+    # together, and those of one block that share neither with a longer tensor ride along in the first launch of the default
+    # block size and their group length, sixteen at most; streams of one block size are decompressed together, whatever their
+    # tuples, and streams of at most sixteen blocks join the largest block size
     def calls_by(key):
         found = {}
         for i in range(nt):
@@ -236,6 +237,12 @@ def main():
     longer = {(params[i][1:], blocks[i]) for i in range(nt) if nblocks[i] > 1}
     single = [(params[i][1:], blocks[i]) not in longer for i in range(nt)]
     ccalls = calls_by(lambda i: (params[i][3],) if single[i] else (params[i][1:], blocks[i]))
+    for g in [g for g in ccalls if single[g[0]]]:
+        for h in ccalls:
+            if not single[h[0]] and blocks[h[0]] == 16384 and params[h[0]][3] == params[g[0]][3]:
+                h += g
+                ccalls.remove(g)
+                break
     dcalls = calls_by(lambda i: (params[i][3], max(blocks) if nblocks[i] <= 16 else blocks[i]))
 
     def compress_all(ev=None):
