@@ -750,12 +750,20 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
             lds = std::max(lds, take_single(sa.item[count++], j));
             largest = std::max(largest, prep[j].B);
         }
-        SingleFn fn = pick_compress_single(dtype, prep[i].prm.L);
-        if (!fn) return ENEC_E_PARAMS;
+        const SingleFn fn = pick_compress_single(dtype, prep[i].prm.L);
+        const SingleFewFn few = pick_compress_single_few(dtype, prep[i].prm.L);
+        if (!fn || !few) return ENEC_E_PARAMS;
         const unsigned threads = std::min(largest / 8, SINGLE_THREADS);
         // (a block of 32768 elements whose records hold whole exponents: more than 64 KB has to be asked for)
-        if (lds > 65536 && resident_workgroups((const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
-        hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);
+        const bool is_few = count <= (size_t)SINGLE_FEW;
+        if (lds > 65536 && resident_workgroups(is_few ? (const void *)few : (const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
+        if (is_few) {
+            SingleFewArgs fa;
+            std::copy(sa.item, sa.item + SINGLE_FEW, fa.item);
+            hipLaunchKernelGGL(few, dim3((unsigned)count), dim3(threads), lds, s, fa);
+        } else {
+            hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);
+        }
     }
     return hipGetLastError() == hipSuccess ? ENEC_OK : ENEC_E_HIP;
 }

@@ -88,14 +88,22 @@ CompressFn pick_compress_per_block_stream(int dtype, unsigned L), pick_compress_
 
 // Compression of tensors of one data block each (enec_single.hpp, compiled in enec_single.hip), whatever their tuples and
 // block sizes: workgroup i takes tensor i.
+// A launch of few has arguments of its own: they lie in device memory, where the host writes them over the link (256 bytes
+// instead of 1 KB, 0.1 us of a call's 7).
+constexpr int SINGLE_FEW = 4;
 struct SingleArgs {
     SingleItem item[MAX_BATCH];
+};
+struct SingleFewArgs {
+    SingleItem item[SINGLE_FEW];
 };
 
 constexpr uint32_t SINGLE_THREADS = 512;
 // its dynamic LDS: the transformed bytes in element order (y; fp16: with the three left-over mantissa bits in bits 5..7) | mask | high records
 constexpr uint32_t single_lds_bytes(uint32_t B, uint32_t L, uint32_t a) { return B + B / (8u * L) + a * B / 8u; }
 using SingleFn = void (*)(const SingleArgs);
+using SingleFewFn = void (*)(const SingleFewArgs);
 SingleFn pick_compress_single(int dtype, unsigned L);
+SingleFewFn pick_compress_single_few(int dtype, unsigned L);
 
 }  // namespace enec
