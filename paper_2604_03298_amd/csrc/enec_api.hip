@@ -283,6 +283,17 @@ uint64_t sampled_elements(uint64_t n, uint32_t every)
     return picked * SAMPLE_CHUNK - (last ? chunks * SAMPLE_CHUNK - n : 0);
 }
 
+// each tensor's counts add up to the elements that were to be looked at
+bool counts_are_whole(const uint64_t *counts, const enec_tune_item *items, size_t n_items, uint32_t every)
+{
+    for (size_t j = 0; j < n_items; ++j) {
+        uint64_t sum = 0;
+        for (unsigned x = 0; x < 256; ++x) sum += counts[256 * j + x];
+        if (sum != sampled_elements(items[j].n_elems, every)) return false;
+    }
+    return true;
+}
+
 unsigned bit_length(unsigned v) { return v ? 32u - (unsigned)__builtin_clz(v) : 0u; }
 
 // ---- Sec. V-E phases 1-3 on a 256-bin exponent histogram -------------------------------------
@@ -542,13 +553,22 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
         const void *fn = dtype == ENEC_FP32 ? (const void *)histogram_kernel<DT_FP32>
                        : dtype == ENEC_FP16 ? (const void *)histogram_kernel<DT_FP16> : (const void *)histogram_kernel<DT_BF16>;
         // Every call leaves the counters zero.  A workspace in which they were not would show in the sums, or in a kernel that
-        // ends without handing over: it is cleared then, and counted once more.
+        // ends without handing over: it is cleared then, and counted once more.  Counts that are wrong even so (something writes
+        // to the workspace during the call) are not used.
         // (Looking for `arrived` instead of waiting for the stream takes 5 us less for the layer, and the runtime makes up for 2
         // of them in whatever is called next; hipStreamQuery or the wait after the search take more than the wait here.)
-        for (int attempt = 0; attempt < 2; ++attempt) {
-            if (attempt) clear_counts_kernel<<<(unsigned)count, 128, 0, s>>>(reinterpret_cast<uint4 *>(dhist), a.done);
+        bool sound = false;
+        for (int attempt = 0; attempt < 2 && !sound; ++attempt) {
+            bool launched = true;
+            if (attempt) {
+                *arrived = 0;
+                uint4 *counts = reinterpret_cast<uint4 *>(dhist);
+                void *args[] = {&counts, &a.done};
+                launched = hipLaunchKernel((const void *)clear_counts_kernel, dim3((unsigned)count), dim3(128), args, 0, s) == hipSuccess;
+            }
             void *args[] = {&a};
-            if (grid && hipLaunchKernel(fn, dim3(grid), dim3(HIST_THREADS), args, 0, s) != hipSuccess) {
+            if (launched && grid) launched = hipLaunchKernel(fn, dim3(grid), dim3(HIST_THREADS), args, 0, s) == hipSuccess;
+            if (!launched) {                   // (nothing that is still to run writes to the slot)
                 (void)hipGetLastError();
                 count_slots().give(host);
                 return ENEC_E_HIP;
@@ -557,14 +577,11 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
                 (void)hipGetLastError();
                 return ENEC_E_HIP;             // (the slot is not given back: a kernel may still be about to write there)
             }
-            bool sound = !grid || *arrived;
-            for (size_t j = 0; j < count && sound; ++j) {
-                uint64_t sum = 0;
-                for (unsigned x = 0; x < 256; ++x) sum += host[256 * j + x];
-                sound = sum == sampled_elements(items[first + j].n_elems, every);
-            }
-            if (sound) break;
-            *arrived = 0;
+            sound = (!grid || *arrived) && counts_are_whole(host, items + first, count, every);
+        }
+        if (!sound) {
+            count_slots().give(host);
+            return ENEC_E_HIP;
         }
         for (size_t j = 0; j < count; ++j) {
             enec_tune_histogram(host + 256 * j, dtype, &params[first + j]);          // (refuses nothing that can be here)

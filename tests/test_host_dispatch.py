@@ -19,6 +19,8 @@ typedef struct { uint32_t x, y, z; } dim3_;
 static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static pthread_cond_t moved = PTHREAD_COND_INITIALIZER;
 int slots_held, slots_most, frees_unguarded, mallocs_unguarded, launches;
+int counted = 100000, wrong_syncs;                   /* what a counting kernel hands over: so many elements, none in the first wrong_syncs waits */
+static struct { char *at; size_t bytes; } slot[16];  /* pinned memory: counts first, the word that says they are there 64 bytes before its end */
 int capturing, launch_fails, sync_fails, gather;     /* set by the test; gather: callers that meet in a wait */
 static int gathered;
 uint32_t grid[64], block[64], lds[64];
@@ -34,8 +36,9 @@ int hipHostMalloc(void **p, size_t n, unsigned flags)
     pthread_mutex_lock(&mu);
     if (mode != 2) ++mallocs_unguarded;
     if (++slots_held > slots_most) slots_most = slots_held;
-    pthread_mutex_unlock(&mu);
     *p = calloc(1, n);
+    for (int i = 0; i < 16; ++i) if (!slot[i].at) { slot[i].at = *p; slot[i].bytes = n; break; }
+    pthread_mutex_unlock(&mu);
     return 0;
 }
 int hipHostFree(void *p)
@@ -43,6 +46,7 @@ int hipHostFree(void *p)
     pthread_mutex_lock(&mu);
     if (mode != 2) ++frees_unguarded;
     --slots_held;
+    for (int i = 0; i < 16; ++i) if (slot[i].at == p) slot[i].at = 0;
     pthread_mutex_unlock(&mu);
     free(p);
     return 0;
@@ -55,6 +59,8 @@ int hipStreamSynchronize(void *s)
         pthread_cond_broadcast(&moved);
         while (gathered < gather) pthread_cond_wait(&moved, &mu);
     }
+    if (wrong_syncs > 0) --wrong_syncs;
+    else for (int i = 0; i < 16; ++i) if (slot[i].at) { *(uint64_t *)slot[i].at = (uint64_t)counted; *(uint32_t *)(slot[i].at + slot[i].bytes - 64) = 1; }
     pthread_mutex_unlock(&mu);
     return capturing ? 900 : sync_fails;
 }
@@ -127,6 +133,22 @@ rcs = {tune() for _ in range(50)}
 report(rcs=list(rcs), held=word("slots_held").value)
 """)
     assert got == dict(rcs=[8], held=1)
+
+
+def test_counts_that_are_wrong_twice_are_not_used(stand_in):
+    """A kernel that ends without handing over, or whose counts don't add up to the elements: cleared and counted once more, and
+    refused after that.  The slot is given back either way."""
+    got = stand_in("""
+word("wrong_syncs").value = 1
+once = tune(), word("launches").value
+word("wrong_syncs").value, word("launches").value = 2, 0
+twice = tune(), word("launches").value
+word("counted").value = 99999
+short = {tune() for _ in range(50)}
+word("counted").value = 100000
+report(once=once, twice=twice, short=list(short), after=tune(), held=word("slots_held").value)
+""")
+    assert got == dict(once=[0, 3], twice=[8, 3], short=[8], after=0, held=1)
 
 
 def test_slots_beyond_those_kept_are_freed_without_ending_a_capture_elsewhere(stand_in):
