@@ -370,6 +370,8 @@ struct SingleItem {
     uint32_t payload_base, tail_base;
     uint32_t logB, b, n, m, mode;       // mode as in CompressItem
 };
+// Arguments lie in device memory, where the host writes them over the link for every launch, so what few launches have must
+// not make them longer for all: a launch's tensors of one block lie behind its items, from the end of their array down.
 struct CompressArgs {
     uint32_t *ws_ctl;       // WS_CLASSES control records
     uint32_t B, logB;
@@ -379,8 +381,17 @@ struct CompressArgs {
     uint32_t n_items;
     uint32_t spin_limit;    // polls of the scan state after which a workgroup gives up (status ENEC_E_HIP)
     uint32_t n_single;      // tensors of one block that the launch takes along (default block size only): its first workgroups
-    CompressItem item[MAX_BATCH];
-    SingleItem single[MAX_BATCH];
+    static constexpr uint32_t SINGLES = MAX_BATCH * sizeof(CompressItem) / sizeof(SingleItem);
+    union {
+        CompressItem item[MAX_BATCH];
+        SingleItem behind[SINGLES];
+    };
+    __host__ __device__ SingleItem &single(uint32_t i) { return behind[SINGLES - 1u - i]; }
+    __host__ __device__ const SingleItem &single(uint32_t i) const { return behind[SINGLES - 1u - i]; }
+    bool takes_another_single() const
+    {
+        return n_single < (uint32_t)MAX_BATCH && n_items * sizeof(CompressItem) + (n_single + 1u) * sizeof(SingleItem) <= sizeof item;
+    }
 };
 
 // ---------------------------------------------------------------------------------
@@ -1036,7 +1047,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     const uint32_t n_single = LOGB ? p.n_single : 0u, wg = blockIdx.x - n_single;
     if constexpr (LOGB != 0)
         if (__builtin_expect(blockIdx.x < n_single, 0)) {
-            compress_one_block<DT, LPG>(p.single[blockIdx.x], smem, (1u << LOGB) / 64u);
+            compress_one_block<DT, LPG>(p.single(blockIdx.x), smem, (1u << LOGB) / 64u);
             return;
         }
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;

@@ -119,3 +119,14 @@ def test_in_the_launch_of_a_larger_tensor(gpu, oracle, dtype, L):
     flat = np.full(3 * 16384 - 5, WORD[dtype](lo) << WORD[dtype](SHIFT[dtype]), dtype=WORD[dtype])
     wide = [(_tensor(rng, dtype, 16384 - i, 0, EXP[dtype], 1.0), (7, full, 0, L), 16384) for i in range(2)]
     _run(gpu, oracle, dtype, wide + [(flat, (lo, 1, 1, L), 16384)] + small[:2])
+
+
+@pytest.mark.parametrize("larges", [11, 16, 17])
+def test_in_launches_with_little_room(gpu, oracle, larges):
+    """The more tensors a launch has, the fewer of one block it takes along: six, none, and sixteen with the seventeenth."""
+    rng = np.random.default_rng(larges)
+    jobs = [(_tensor(rng, BF16, 16384 + 999 * i + 1, 100, 118, 0.02), (115, 5, 3, 16), 16384) for i in range(larges)]
+    for i in range(18):
+        w = _tensor(rng, BF16, 4096 - 13 * i, 100, 118, 0.1)
+        jobs.insert(2 * i, (w, oracle.tune(w, BF16), 4096))
+    _run(gpu, oracle, BF16, jobs)

@@ -77,6 +77,9 @@ int __hipPushCallConfiguration(dim3_ g, dim3_ b, size_t shared, void *s) { pushe
 int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *shared, void **s) { *g = pushed_grid; *b = pushed_block; *shared = pushed_lds; *s = pushed_stream; return 0; }
 int hipGetLastError(void) { return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int threads, size_t dynamic) { *n = 3; return 0; }
+int hipDeviceGetAttribute(int *v, int what, int device) { *v = 256; return 0; }
+int hipFuncSetAttribute(const void *f, int what, int value) { return 0; }
 """
 
 PRELUDE = r"""
@@ -197,3 +200,24 @@ report(before=decompress([norm] * 20 + [matrix], d), after=decompress([matrix] +
                        many=[[16 * 256, 2 * 256 + 3], [256, 256]],
                        three=[[2 * 17, 15 * 256, 15], [512, 256, 64]],
                        long=[[17 + 16, 256], [64, 256]], rest=[[17 + 15, 256 + 2], [64, 256]], sizes=[[13, 13, 14], [128, 64, 64]], empty=[[1], [64]])
+
+
+def test_tensors_of_one_block_ride_along_where_there_is_room(stand_in):
+    """They come on top of the grid of the first launch of default blocks: sixteen at most, fewer where its items leave less room
+    among the arguments, none where it holds sixteen; the rest are launched together at the end."""
+    got = stand_in("""
+class Item(C.Structure): _fields_ = [("src", C.c_void_p), ("n", C.c_size_t), ("B", C.c_uint32), ("params", C.POINTER(P)), ("out", C.c_void_p), ("cap", C.c_size_t), ("out_bytes", C.c_void_p)]
+big, small = P(122, 6, 3, 16), P(122, 5, 3, 16)
+def compress(larges, smalls):
+    items = (Item * (larges + smalls))()
+    for i, it in enumerate(items):
+        it.src = it.out = FAKE
+        it.n, it.B, it.params = (32768, 16384, C.pointer(big)) if i < larges else (4096, 4096, C.pointer(small))
+        it.cap = 1 << 30
+    word("launches").value = 0
+    assert L.enec_compress_batch(items, C.c_size_t(larges + smalls), 0, C.c_void_p(FAKE), C.c_size_t(1 << 20), C.c_void_p(64)) == 0
+    return launches()
+report(layer=compress(7, 2), few=compress(1, 19), many=compress(12, 7), full=compress(16, 3), two=compress(17, 3), none=compress(0, 3))
+""")
+    assert got == dict(layer=[[16], [256]], few=[[2 + 16, 3], [256, 512]], many=[[24 + 5, 2], [256, 512]], full=[[32, 3], [256, 512]],
+                       two=[[32, 2 + 3], [256, 256]], none=[[3], [512]])
