@@ -691,10 +691,10 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
 
     // ---- one launch per group of tensors that share (m, n - m, L, block size) ----------------
     // A tensor of one block whose (m, n - m, L, block size) no longer tensor has is coded without the machinery for the order
-    // of blocks (compress_one_block, whatever its tuple and block size): by the first workgroups of the first launch of the
-    // default block size and the same L that has room for it among its arguments, or, where there is none or its LDS is too small for
-    // the tensor's records, with others of its kind in a launch of their own, after the others.  Its own launch behind that of a layer of 405 MB took 4 us for two
-    // norm vectors (139.6 -> 135.4 us with the kernel's own gain).
+    // of blocks (compress_one_block, whatever its tuple and block size): by the first workgroups of the first launch of the same L
+    // whose kernel takes such tensors along (takes_singles), has room for it among its arguments and LDS for its records, or,
+    // where there is none, with others of its kind in a launch of their own, after the others.  Its own launch behind that of a
+    // layer of 405 MB took 4 us for two norm vectors (139.6 -> 135.4 us with the kernel's own gain).
     auto kernel_of = [&](size_t j) {
         return prep[j].B << 16 | (uint32_t)prep[j].prm.n << 12 | (uint32_t)prep[j].prm.m << 8 | prep[j].prm.L;
     };
@@ -750,7 +750,7 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
                            (compress_sm_in_lds(dtype, a.B == 1u << DEFAULT_LOGB) ? a.B : 0);
         const unsigned resident = resident_workgroups((const void *)fn, threads, lds);
         if (resident == 0) return ENEC_E_HIP;
-        if (a.B == 1u << DEFAULT_LOGB)
+        if (takes_singles(prep[i].prm.m, prep[i].prm.n - prep[i].prm.m, a.logB))
             for (size_t j = 0; j < n_items && a.takes_another_single(); ++j)
                 if (!done[j] && alone(j) && prep[j].prm.L == prep[i].prm.L &&
                     single_lds_bytes(prep[j].B, prep[j].prm.L, prep[j].prm.n - prep[j].prm.m) <= lds)

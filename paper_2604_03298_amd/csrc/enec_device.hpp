@@ -731,7 +731,7 @@ __device__ __forceinline__ void load_block_rows(const Item &p, uint32_t B, uint3
 
 // ---------------------------------------------------------------------------------
 // compression of a tensor of one data block by one workgroup (of at most `most` threads): compress_single_kernel, and the
-// first workgroups of a compress_kernel launch that has such tensors beside it
+// first workgroups of a compress_kernel launch that has such tensors beside it.  Q: vectors of a thread whose loads travel together
 // ---------------------------------------------------------------------------------
 // Alg. 2's bit map for W-bit values (HHTable) by planes: the entries of plane q, unused ones zero.
 // Bits 0-2 row, 3-7 rotation to the right, 8-15 destination bits.
@@ -757,13 +757,12 @@ constexpr HHPlanes make_hh_planes()
 }
 static __device__ const HHPlanes hh_planes = make_hh_planes();
 
-template <int DT, int LPG>
+template <int DT, int LPG, int Q>
 __device__ __forceinline__ void compress_one_block(const SingleItem &it, uint8_t *smem, uint32_t most)
 {
     __shared__ uint32_t s_tab[128], s_err[8];
     constexpr uint32_t E = exponent_bits(DT);
     constexpr int LOG_LPG = LPG == 4 ? 2 : LPG - 1;
-    constexpr int Q = DT == DT_FP32 ? 2 : 4;             // vectors of a thread whose loads travel together
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t logB = it.logB, B = 1u << logB, logC = logB - 3u, nvec = B >> 3, threads = nvec < most ? nvec : most;
     if (tid >= threads) return;                          // whole waves that the launch's larger blocks need
@@ -1008,6 +1007,14 @@ __device__ __forceinline__ void compress_one_block(const SingleItem &it, uint8_t
 // compression: split, transform, group test, packing, inter-block scan, store
 // (Sec. V-A compression path; Sec. V-B; Sec. V-C; Fig. 4)
 // ---------------------------------------------------------------------------------
+// Which instances take tensors of one block along: those of the default block size (2^14) for the tuples that the search returns for
+// matrices (bf16 and fp32 n = 5 to 8, fp16 n = 4 and 5, m >= 2 and n - m = 1 to 3, for Gaussian, uniform and heavy-tailed
+// weights, with outliers, a scale per row or zeros among them).  compress_one_block does not depend on the widths, and a
+// process's first compression loads all instances of a unit: in each of the 44 of bf16, and with four vectors in flight, it made
+// their code 1.38 MB instead of 0.98 and that call 2.13 ms instead of 1.90, and it took fp32's instance for (m, n) = (5, 5) over
+// the step from three waves per SIMD to two; in these 15, and with one vector, 1.06 MB and 1.98 ms against 1.94.
+constexpr bool takes_singles(unsigned m, unsigned a, unsigned logb) { return logb == 14u && m >= 2u && a >= 1u && a <= 3u; }
+
 // LOGB: log2 of the block size where it is a constant, 0 = it is p.B.  The default block size has instances of its
 // own: with run-time sizes 50 scalar registers of shifts and offsets are spilled into vector lanes and read back in
 // every block; as constants they cost nothing (layer of 405 MB 151.2 -> 147.7 us, 470 MB matrices 312.7 -> 301.6,
@@ -1044,10 +1051,11 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     __shared__ uint32_t s_status;              // header status found by the scan for that block
     __shared__ uint32_t s_err[2];              // range error in the block of image 0 / 1
 
-    const uint32_t n_single = LOGB ? p.n_single : 0u, wg = blockIdx.x - n_single;
-    if constexpr (LOGB != 0)
+    constexpr bool TAKES_SINGLES = takes_singles(M, A, LOGB);
+    const uint32_t n_single = TAKES_SINGLES ? p.n_single : 0u, wg = blockIdx.x - n_single;
+    if constexpr (TAKES_SINGLES)
         if (__builtin_expect(blockIdx.x < n_single, 0)) {
-            compress_one_block<DT, LPG>(p.single(blockIdx.x), smem, (1u << LOGB) / 64u);
+            compress_one_block<DT, LPG, 1>(p.single(blockIdx.x), smem, (1u << LOGB) / 64u);
             return;
         }
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;

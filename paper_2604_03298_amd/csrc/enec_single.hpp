@@ -22,7 +22,7 @@ template <int DT, int LPG, class Args>
 __global__ void __launch_bounds__(SINGLE_THREADS) compress_single_kernel(const Args p)
 {
     extern __shared__ __align__(16) uint8_t smem[];
-    compress_one_block<DT, LPG>(p.item[blockIdx.x], smem, SINGLE_THREADS);
+    compress_one_block<DT, LPG, DT == DT_FP32 ? 2 : 4>(p.item[blockIdx.x], smem, SINGLE_THREADS);
 }
 
 }  // namespace enec

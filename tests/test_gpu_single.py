@@ -130,3 +130,21 @@ def test_in_launches_with_little_room(gpu, oracle, larges):
         w = _tensor(rng, BF16, 4096 - 13 * i, 100, 118, 0.1)
         jobs.insert(2 * i, (w, oracle.tune(w, BF16), 4096))
     _run(gpu, oracle, BF16, jobs)
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+@pytest.mark.parametrize("L", [8, 16, 32])
+def test_in_the_launches_that_take_them(gpu, oracle, dtype, L):
+    """Beside each tuple whose instance takes tensors of one block along, from the lengths at which a vector, a thread's turn and a
+    block end; records of whole exponents, which the kernel's LDS may be too small for."""
+    rng = np.random.default_rng(60 + 3 * dtype + L)
+    full = 5 if dtype == FP16 else 8
+    lo, hi = (10, 17) if dtype == FP16 else (100, 118)
+    for a in (1, 2, 3):
+        for m in range(2, full - a + 1):
+            big = _tensor(rng, dtype, 2 * 16384 + 5, lo, lo + 1, 0.0)
+            jobs = [(big, (lo, m + a, m, L), 16384), (_tensor(rng, dtype, 16384 - a, 0, EXP[dtype], 1.0), (7, full, 0, L), 16384)]
+            for n in (1, 2047, 2049, 4096 - m):
+                w = _tensor(rng, dtype, n, lo, hi, 0.1)
+                jobs.append((w, oracle.tune(w, dtype)[:3] + (L,), 4096 if n > 2048 or L == 32 else 2048))
+            _run(gpu, oracle, dtype, jobs)

@@ -204,11 +204,11 @@ report(before=decompress([norm] * 20 + [matrix], d), after=decompress([matrix] +
 
 def test_tensors_of_one_block_ride_along_where_there_is_room(stand_in):
     """They come on top of the grid of the first launch of default blocks: sixteen at most, fewer where its items leave less room
-    among the arguments, none where it holds sixteen; the rest are launched together at the end."""
+    among the arguments, none where it holds sixteen or its instance has not the code; the rest are launched together at the end."""
     got = stand_in("""
 class Item(C.Structure): _fields_ = [("src", C.c_void_p), ("n", C.c_size_t), ("B", C.c_uint32), ("params", C.POINTER(P)), ("out", C.c_void_p), ("cap", C.c_size_t), ("out_bytes", C.c_void_p)]
 big, small = P(122, 6, 3, 16), P(122, 5, 3, 16)
-def compress(larges, smalls):
+def compress(larges, smalls, big=big):
     items = (Item * (larges + smalls))()
     for i, it in enumerate(items):
         it.src = it.out = FAKE
@@ -217,7 +217,10 @@ def compress(larges, smalls):
     word("launches").value = 0
     assert L.enec_compress_batch(items, C.c_size_t(larges + smalls), 0, C.c_void_p(FAKE), C.c_size_t(1 << 20), C.c_void_p(64)) == 0
     return launches()
-report(layer=compress(7, 2), few=compress(1, 19), many=compress(12, 7), full=compress(16, 3), two=compress(17, 3), none=compress(0, 3))
+report(layer=compress(7, 2), few=compress(1, 19), many=compress(12, 7), full=compress(16, 3), two=compress(17, 3), none=compress(0, 3),
+       tuples=[compress(2, 2, P(100, n, m, 16))[0] for n, m in ((8, 7), (2, 1), (3, 2), (5, 5), (8, 4), (8, 5))],
+       lengths=compress(2, 2, P(100, 6, 3, 8))[0])
 """)
     assert got == dict(layer=[[16], [256]], few=[[2 + 16, 3], [256, 512]], many=[[24 + 5, 2], [256, 512]], full=[[32, 3], [256, 512]],
-                       two=[[32, 2 + 3], [256, 256]], none=[[3], [512]])
+                       two=[[32, 2 + 3], [256, 256]], none=[[3], [512]],
+                       tuples=[[4 + 2], [4, 2], [4 + 2], [4, 2], [4, 2], [4 + 2]], lengths=[4, 2])
