@@ -206,6 +206,7 @@ void launch_compress(Fn fn, CompressArgs &a, unsigned resident, unsigned threads
     // (tensors of one block come on top of the grid, which may leave workgroups waiting until one of theirs ends: these draw
     // their first block then)
     const unsigned grid = persistent_grid(a.total, resident);
+    a.wgs = grid;
     a.ncls = grid < 8 ? grid : 8;
     // The next ticket is drawn while the current block is worked on only if there are blocks for
     // two rounds: with fewer, an early workgroup would take the block of one that starts a moment later.

@@ -376,11 +376,13 @@ struct CompressArgs {
     uint32_t *ws_ctl;       // WS_CLASSES control records
     uint32_t B, logB;
     uint32_t total;         // data blocks of all items
-    uint32_t ncls;          // number of block classes = min(8, gridDim.x)
-    uint32_t lookahead;     // draw the next ticket while working on the current block
+    uint32_t wgs;           // workgroups that code them: the grid without n_single.  (Asked of the runtime, gridDim.x lies behind
+                            // all arguments: 256 bytes more of them, and a trip to memory of its own for the first workgroups)
+    uint32_t ncls;          // number of block classes = min(8, wgs)
     uint32_t n_items;
     uint32_t spin_limit;    // polls of the scan state after which a workgroup gives up (status ENEC_E_HIP)
-    uint32_t n_single;      // tensors of one block that the launch takes along (default block size only): its first workgroups
+    uint16_t lookahead;     // draw the next ticket while working on the current block
+    uint16_t n_single;      // tensors of one block that the launch takes along (takes_singles): its first workgroups
     static constexpr uint32_t SINGLES = MAX_BATCH * sizeof(CompressItem) / sizeof(SingleItem);
     union {
         CompressItem item[MAX_BATCH];
@@ -1054,7 +1056,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     constexpr bool TAKES_SINGLES = takes_singles(M, A, LOGB);
     const uint32_t n_single = TAKES_SINGLES ? p.n_single : 0u, wg = blockIdx.x - n_single;
     if constexpr (TAKES_SINGLES)
-        if (__builtin_expect(blockIdx.x < n_single, 0)) {
+        if (__builtin_expect((int32_t)wg < 0, 0)) {
             compress_one_block<DT, LPG, 1>(p.single(blockIdx.x), smem, (1u << LOGB) / 64u);
             return;
         }
@@ -1071,7 +1073,7 @@ __global__ void __launch_bounds__(LOGB ? (1 << LOGB) / 64 : 512) ENEC_COMPRESS_O
     const uint32_t home = wg % p.ncls;
     uint32_t *ctl = p.ws_ctl + WS_STRIDE * home;
     const uint32_t class_blocks = home < p.total ? (p.total - home + p.ncls - 1u) / p.ncls : 0u;
-    const uint32_t class_wgs = (gridDim.x - n_single - home + p.ncls - 1u) / p.ncls;
+    const uint32_t class_wgs = (p.wgs - home + p.ncls - 1u) / p.ncls;
     uint32_t ticket_base = 0, zero = 0;
     uint64_t tag0 = 0;
     bool drawing = true;

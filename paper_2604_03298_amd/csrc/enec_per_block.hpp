@@ -670,7 +670,7 @@ compress_per_block_stream_kernel(const CompressArgs p)
     const uint32_t home = blockIdx.x % p.ncls;
     uint32_t *ctl = p.ws_ctl + WS_STRIDE * home;
     const uint32_t class_blocks = home < p.total ? (p.total - home + p.ncls - 1u) / p.ncls : 0u;
-    const uint32_t class_wgs = (gridDim.x - home + p.ncls - 1u) / p.ncls;
+    const uint32_t class_wgs = (p.wgs - home + p.ncls - 1u) / p.ncls;
     uint32_t ticket_base = 0, zero = 0;
     uint64_t tag0 = 0;
     bool drawing = true;

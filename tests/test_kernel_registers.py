@@ -20,8 +20,10 @@ def test_no_kernel_spills_its_registers():
 
 
 def test_the_arguments_of_compression_launches_stay_short():
-    """Arguments are written over the link for every launch: sixteen tensors' fit in 1704 bytes (the runtime's own among them), and
-    the tensors of one block that a launch takes along have to fit in with them (1 KB more cost small calls 1 to 2 %)."""
+    """Arguments are written over the link for every launch: sixteen tensors' fit in 1448 bytes, 1704 with the runtime's own, which
+    the kernel for one tuple per tensor does without (its grid is an argument among the others).  Tensors of one block that a
+    launch takes along have to fit in with them (1 KB more, and a branch on their number before the grid was known, cost small
+    calls 1 to 2 %)."""
     from paper_2604_03298_amd import enec
     with open(enec.LIB_PATH, "rb") as f:
         data = f.read()
@@ -29,7 +31,7 @@ def test_the_arguments_of_compression_launches_stay_short():
                  re.findall(rb"\.kernarg_segment_size\xcd(..).{0,400}?\.symbol.{1,3}?(_ZN4enec\w+)\.kd", data, re.S))
     takes = {name: size for name, size in found.items() if "CompressArgs" in name and "PbCompressArgs" not in name}
     assert len(takes) == 648 + 9
-    assert {name: size for name, size in takes.items() if size > 1704} == {}
+    assert {name: size for name, size in takes.items() if size > (1448 if "15compress_kernel" in name else 1704)} == {}
 
 
 def test_few_instances_hold_the_code_for_tensors_of_one_block():
