@@ -284,17 +284,6 @@ uint64_t sampled_elements(uint64_t n, uint32_t every)
     return picked * SAMPLE_CHUNK - (last ? chunks * SAMPLE_CHUNK - n : 0);
 }
 
-// each tensor's counts add up to the elements that were to be looked at
-bool counts_are_whole(const uint64_t *counts, const enec_tune_item *items, size_t n_items, uint32_t every)
-{
-    for (size_t j = 0; j < n_items; ++j) {
-        uint64_t sum = 0;
-        for (unsigned x = 0; x < 256; ++x) sum += counts[256 * j + x];
-        if (sum != sampled_elements(items[j].n_elems, every)) return false;
-    }
-    return true;
-}
-
 unsigned bit_length(unsigned v) { return v ? 32u - (unsigned)__builtin_clz(v) : 0u; }
 
 // ---- Sec. V-E phases 1-3 on a 256-bin exponent histogram -------------------------------------
@@ -375,6 +364,20 @@ void threshold_and_length(Search &r, uint32_t lengths)
             }
         }
     }
+}
+
+// the tuple for a histogram; the number of elements in it
+uint64_t search(const uint64_t *hist, int dtype, uint32_t lengths, enec_params *params)
+{
+    Search r;
+    const bool any = centre_and_width(hist, exp_bits(dtype), r);
+    if (!any) {                                                 // no elements at all: (b, n) = (0, 1) and p = 1
+        r.b = 0; r.n = 1; r.total = 1;
+        r.at_most[0] = r.at_most[1] = 1;
+    }
+    threshold_and_length(r, lengths);
+    *params = enec_params{(uint8_t)r.b, (uint8_t)r.n, (uint8_t)r.m, (uint8_t)r.L};
+    return any ? r.total : 0;
 }
 
 struct Header {
@@ -483,13 +486,7 @@ int enec_tune_histogram_groups(const uint64_t *hist, int dtype, uint32_t group_l
     for (unsigned L = 8; L <= 32; L *= 2)
         if ((group_lengths & L) && group_fits_block(L, B)) lengths |= L;
     if (!lengths) lengths = 16u;
-    Search r;
-    if (!centre_and_width(hist, exp_bits(dtype), r)) {          // no elements at all: (b, n) = (0, 1) and p = 1
-        r.b = 0; r.n = 1; r.total = 1;
-        r.at_most[0] = r.at_most[1] = 1;
-    }
-    threshold_and_length(r, lengths);
-    *params = enec_params{(uint8_t)r.b, (uint8_t)r.n, (uint8_t)r.m, (uint8_t)r.L};
+    search(hist, dtype, lengths, params);
     return ENEC_OK;
 }
 
@@ -548,6 +545,7 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
             a.host = reinterpret_cast<unsigned long long *>(host);
             a.arrived = const_cast<uint32_t *>(arrived);
             a.n_counts = (uint32_t)count * 256u;
+            a.wgs = grid;
         } else {
             std::memset(host, 0, count * 256 * 8);
         }
@@ -559,6 +557,7 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
         // (Looking for `arrived` instead of waiting for the stream takes 5 us less for the layer, and the runtime makes up for 2
         // of them in whatever is called next; hipStreamQuery or the wait after the search take more than the wait here.)
         bool sound = false;
+        enec_params found[WS_HIST_SLOTS];
         for (int attempt = 0; attempt < 2 && !sound; ++attempt) {
             bool launched = true;
             if (attempt) {
@@ -578,16 +577,16 @@ int enec_tune_batch(const enec_tune_item *items, size_t n_items, int dtype, uint
                 (void)hipGetLastError();
                 return ENEC_E_HIP;             // (the slot is not given back: a kernel may still be about to write there)
             }
-            sound = (!grid || *arrived) && counts_are_whole(host, items + first, count, every);
+            sound = !grid || *arrived;
+            for (size_t j = 0; j < count && sound; ++j)
+                sound = search(host + 256 * j, dtype, 16u, &found[j]) == sampled_elements(items[first + j].n_elems, every);
         }
         if (!sound) {
             count_slots().give(host);
             return ENEC_E_HIP;
         }
-        for (size_t j = 0; j < count; ++j) {
-            enec_tune_histogram(host + 256 * j, dtype, &params[first + j]);          // (refuses nothing that can be here)
-            if (histograms) std::memcpy(histograms + 256 * (first + j), host + 256 * j, 256 * 8);
-        }
+        std::copy(found, found + count, params + first);
+        if (histograms) std::memcpy(histograms + 256 * first, host, count * 256 * 8);
     }
     count_slots().give(host);
     return ENEC_OK;

@@ -1535,8 +1535,8 @@ struct HistogramArgs {
     uint32_t *done;             // workgroups that have added their counts, zero at launch and again at the end
     unsigned long long *counts; // all histograms of the call, one behind the other
     unsigned long long *host;   // pinned memory: where they go
-    uint32_t *arrived;          // pinned memory: set to 1 behind them (0: nobody was last, see enec_tune_batch)
-    uint32_t n_counts;
+    uint32_t *arrived;          // pinned memory: set to 1 (0 when the kernel has ended: nobody was last, see enec_tune_batch)
+    uint32_t n_counts, wgs;     // wgs: the grid
 };
 
 // Bound: HBM, with the LDS atomics (7.2 lanes per clock and CU: 46 us for a layer of 202e6 elements) not far behind.
@@ -1546,8 +1546,10 @@ struct HistogramArgs {
 // waves, 70.  Whole calls, us, 512 threads x 256 workgroups against 512 x 512 / 1024 x 256 / 256 x 1024: layer
 // 99.4 against 101.3 / 103.2 / 103.2, 268e6 elements 107.7 / 117.0 / 112.1 / 124.9, 17e6 41.0 / 44.4 / 40.7 / 53.0;
 // six or eight vectors in flight are slower again (layer 103.5, 103.9).
-// The workgroup that adds its counts last hands all of them over and leaves the counters zero for the next call: with a kernel
-// before this one that cleared them and one behind it that handed them over a call for the layer took 86.6 us, now 85.6.
+// The workgroup that adds its counts last hands all of them over and leaves the counters zero for the next call.  With a kernel
+// before this one that cleared them and one behind it that handed them over a call took, for the layer / twenty tensors of
+// 262144 elements / one of 1e6, 85.4 / 56.6 / 25.6 us, now 83.3 / 53.9 / 22.7; with one count of a thread after the other, each
+// waited for, and sums on the host beside the search 84.3 / 57.8 / 23.3.
 constexpr uint32_t HIST_THREADS = 512, HIST_WORKGROUPS = 256;
 
 template <int DT>
@@ -1637,22 +1639,34 @@ __global__ void __launch_bounds__(HIST_THREADS) histogram_kernel(const Histogram
         for (uint32_t i = 0; i < COPIES; ++i) c += s_h[i * STRIDE + tid];
     }
     if (c) atomicAdd(&hist[tid], (unsigned long long)c);
-    // Everything that passes from one workgroup to another or to the host is an atomic of that scope, which no cache keeps back,
-    // so waiting for this wave's own accesses is enough; a release would write the L2 back, 40 us of a layer's 86.
+    // What passes from one workgroup to another is an atomic of the device's scope, which no cache keeps back, so waiting for this
+    // wave's own accesses is enough; a release would write the L2 back, 40 us of a layer's 86.
     wait_accesses();
     __syncthreads();
     if (tid == 0) s_h[0] = __hip_atomic_fetch_add(p.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (s_h[0] != gridDim.x - 1u) return;
-    for (uint32_t i = tid; i < p.n_counts; i += HIST_THREADS)
-        __hip_atomic_store(p.host + i, __hip_atomic_load(p.counts + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-    for (uint32_t i = tid; i < p.n_counts; i += HIST_THREADS)
-        __hip_atomic_store(p.counts + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0) __hip_atomic_store(p.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    wait_accesses();
-    __syncthreads();
-    if (tid == 0) __hip_atomic_store(p.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (s_h[0] != p.wgs - 1u) return;
+    // (all counts of a thread travel together.  The host reads when the kernel has ended, so nothing here waits for anything else.)
+    constexpr uint32_t R = MAX_BATCH * 256u / 2u / HIST_THREADS;
+    unsigned long long lo[R], hi[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = 2u * (r * HIST_THREADS + tid);
+        if (i >= p.n_counts) break;
+        lo[r] = __hip_atomic_load(p.counts + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        hi[r] = __hip_atomic_load(p.counts + i + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = 2u * (r * HIST_THREADS + tid);
+        if (i >= p.n_counts) break;
+        *reinterpret_cast<uint4 *>(p.host + i) = make_uint4((uint32_t)lo[r], (uint32_t)(lo[r] >> 32), (uint32_t)hi[r], (uint32_t)(hi[r] >> 32));
+        *reinterpret_cast<uint4 *>(p.counts + i) = make_uint4(0, 0, 0, 0);
+    }
+    if (tid == 0) {
+        *p.done = 0;
+        *p.arrived = 1;
+    }
 }
 
 }  // namespace enec

@@ -82,3 +82,18 @@ def test_a_workspace_whose_counters_are_not_zero(gpu, oracle, dirt, every):
             for h, w in zip(hist, want):
                 assert np.array_equal(h, w)
     assert int(ws[1008:1012].sum()) == 0 and int(ws[1024:1024 + 4 * 2048].to(torch.int64).sum()) == 0
+
+
+@pytest.mark.parametrize("count", [1, 2, 15, 16, 17])
+def test_as_many_histograms_as_a_launch_hands_over(gpu, oracle, count):
+    """Two counters at a time for every thread of the last workgroup, up to sixteen tensors' of them; empty tensors among these."""
+    torch, enec = gpu.torch, gpu.enec
+    rng = np.random.default_rng(count)
+    data = [rng.integers(0, 65536, (0 if i % 5 == 3 else 700 * i + 1), dtype=np.uint16) for i in range(count)]
+    dev = [torch.from_numpy(w.view(np.int16)).cuda() for w in data]
+    ws = enec.new_workspace(sum(w.size for w in data) + 1)
+    for _ in range(2):
+        prm, hist = enec.tune_batch(dev, ws, dtype=BF16, want_histograms=True)
+        for w, p, h in zip(data, prm, hist):
+            want = oracle.histogram(w, BF16)
+            assert np.array_equal(h, want) and tuple(p) == oracle.tune_hist(want)[0], w.size
