@@ -759,7 +759,7 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
     }
     for (size_t i = 0; i < n_items; ++i) {
         if (done[i]) continue;
-        SingleArgs sa;
+        SingleArgs sa{};
         size_t count = 0, lds = 0;
         uint32_t largest = 0;
         for (size_t j = i; j < n_items && count < (size_t)MAX_BATCH; ++j) {
@@ -775,8 +775,8 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
         const bool is_few = count <= (size_t)SINGLE_FEW;
         if (lds > 65536 && resident_workgroups(is_few ? (const void *)few : (const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
         if (is_few) {
-            SingleFewArgs fa;
-            std::copy(sa.item, sa.item + SINGLE_FEW, fa.item);
+            SingleFewArgs fa{};
+            std::copy_n(sa.item, count, fa.item);
             hipLaunchKernelGGL(few, dim3((unsigned)count), dim3(threads), lds, s, fa);
         } else {
             hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);

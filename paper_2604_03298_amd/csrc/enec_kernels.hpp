@@ -89,7 +89,7 @@ CompressFn pick_compress_per_block_stream(int dtype, unsigned L), pick_compress_
 // Compression of tensors of one data block each (enec_single.hpp, compiled in enec_single.hip), whatever their tuples and
 // block sizes: workgroup i takes tensor i.
 // A launch of few has arguments of its own: they lie in device memory, where the host writes them over the link (256 bytes
-// instead of 1 KB, 0.1 us of a call's 7).
+// instead of 1 KB: one, two and four vectors of 4096 elements 6.15, 7.25 and 8.54 us with the long ones, 5.95, 7.04 and 8.35 with these).
 constexpr int SINGLE_FEW = 4;
 struct SingleArgs {
     SingleItem item[MAX_BATCH];

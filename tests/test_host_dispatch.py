@@ -24,6 +24,8 @@ static struct { char *at; size_t bytes; } slot[16];  /* pinned memory: counts fi
 int capturing, launch_fails, sync_fails, gather;     /* set by the test; gather: callers that meet in a wait */
 static int gathered;
 uint32_t grid[64], block[64], lds[64];
+int keep_bytes;                                      /* of the next launches' first argument, the last launch's are kept */
+uint8_t kept[2048];
 static _Thread_local int mode;                       /* 0 = global, 2 = relaxed */
 static _Thread_local dim3_ pushed_grid, pushed_block;
 static _Thread_local size_t pushed_lds;
@@ -69,6 +71,7 @@ int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t shared,
     pthread_mutex_lock(&mu);
     if (launches < 64) { grid[launches] = g.x; block[launches] = b.x; lds[launches] = (uint32_t)shared; }
     ++launches;
+    for (int i = 0; i < keep_bytes; ++i) kept[i] = ((uint8_t *)args[0])[i];
     pthread_mutex_unlock(&mu);
     return launch_fails;
 }
@@ -202,10 +205,7 @@ report(before=decompress([norm] * 20 + [matrix], d), after=decompress([matrix] +
                        long=[[17 + 16, 256], [64, 256]], rest=[[17 + 15, 256 + 2], [64, 256]], sizes=[[13, 13, 14], [128, 64, 64]], empty=[[1], [64]])
 
 
-def test_tensors_of_one_block_ride_along_where_there_is_room(stand_in):
-    """They come on top of the grid of the first launch of default blocks: sixteen at most, fewer where its items leave less room
-    among the arguments, none where it holds sixteen or its instance has not the code; the rest are launched together at the end."""
-    got = stand_in("""
+COMPRESS = """
 class Item(C.Structure): _fields_ = [("src", C.c_void_p), ("n", C.c_size_t), ("B", C.c_uint32), ("params", C.POINTER(P)), ("out", C.c_void_p), ("cap", C.c_size_t), ("out_bytes", C.c_void_p)]
 big, small = P(122, 6, 3, 16), P(122, 5, 3, 16)
 def compress(larges, smalls, big=big):
@@ -217,6 +217,13 @@ def compress(larges, smalls, big=big):
     word("launches").value = 0
     assert L.enec_compress_batch(items, C.c_size_t(larges + smalls), 0, C.c_void_p(FAKE), C.c_size_t(1 << 20), C.c_void_p(64)) == 0
     return launches()
+"""
+
+
+def test_tensors_of_one_block_ride_along_where_there_is_room(stand_in):
+    """They come on top of the grid of the first launch of default blocks: sixteen at most, fewer where its items leave less room
+    among the arguments, none where it holds sixteen or its instance has not the code; the rest are launched together at the end."""
+    got = stand_in(COMPRESS + """
 report(layer=compress(7, 2), few=compress(1, 19), many=compress(12, 7), full=compress(16, 3), two=compress(17, 3), none=compress(0, 3),
        tuples=[compress(2, 2, P(100, n, m, 16))[0] for n, m in ((8, 7), (2, 1), (3, 2), (5, 5), (8, 4), (8, 5))],
        lengths=compress(2, 2, P(100, 6, 3, 8))[0])
@@ -224,3 +231,16 @@ report(layer=compress(7, 2), few=compress(1, 19), many=compress(12, 7), full=com
     assert got == dict(layer=[[16], [256]], few=[[2 + 16, 3], [256, 512]], many=[[24 + 5, 2], [256, 512]], full=[[32, 3], [256, 512]],
                        two=[[32, 2 + 3], [256, 256]], none=[[3], [512]],
                        tuples=[[4 + 2], [4, 2], [4 + 2], [4, 2], [4, 2], [4 + 2]], lengths=[4, 2])
+
+
+@pytest.mark.parametrize("count, slots", [(1, 4), (3, 4), (5, 16)])
+def test_a_launch_for_tensors_of_one_block_passes_nothing_but_these(stand_in, count, slots):
+    """The slots behind them are zero, whatever lay on the stack (an earlier call's tensors)."""
+    got = stand_in(COMPRESS + f"""
+compress(0, 4), compress(0, 16)
+word("keep_bytes").value = {64 * slots}
+grid = compress(0, {count})[0]
+args = bytes((C.c_uint8 * 2048).in_dll(rt, "kept"))
+report(grid=grid, used=[args[64 * i:64 * i + 64] != bytes(64) for i in range({slots})])
+""")
+    assert got == dict(grid=[count], used=[True] * count + [False] * (slots - count))
