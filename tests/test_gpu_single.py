@@ -84,6 +84,17 @@ def test_whole_exponents_as_records(gpu, oracle, dtype):
         _run(gpu, oracle, dtype, [j])
 
 
+@pytest.mark.parametrize("dtype", [BF16, FP32])
+@pytest.mark.parametrize("L", [16, 32])
+def test_whole_exponents_as_records_of_many_tensors(gpu, oracle, dtype, L):
+    """The same where a launch has more than four tensors: more than 64 KB of LDS for the kernel with the long arguments, smaller
+    blocks among its workgroups."""
+    rng = np.random.default_rng(40 + dtype + L)
+    jobs = [(_tensor(rng, dtype, B - i, 0, EXP[dtype], 1.0), (7, 8, 0, L), B)
+            for i, B in enumerate((32768, 4096, 32768, 16384, 8192, 32768, 4096))]
+    _run(gpu, oracle, dtype, jobs)
+
+
 def test_beside_larger_tensors(gpu, oracle):
     """One-block tensors that share (m, n, L, block size) with a tensor of more blocks go through its launch, the others don't."""
     rng = np.random.default_rng(3)

@@ -70,13 +70,14 @@ def test_a_workspace_whose_counters_are_not_zero(gpu, oracle, dirt, every):
     dev = [torch.from_numpy(w.view(np.int16)).cuda() for w in data]
     ws = enec.new_workspace(sum(sizes))
     want = [oracle.histogram(w if every == 1 else oracle.sample(w, every, BF16), BF16) for w in data]
+    wgs = sum(max(1, -(-(n // 8 // every) // 512)) for n in sizes)     # of the launch: one for every 512 vectors of a tensor's sample
     for _ in range(2):
         if dirt in ("counts", "both"):
             ws[1024:1024 + 4 * 2048] = 7
         if dirt in ("done", "both"):
             ws[1008:1012] = 255
         if dirt == "after an early last":
-            ws[1008] = 40 if every == 1 else 12                   # (a workgroup that is not the last takes itself for it)
+            ws[1008] = wgs - 6                                    # (the sixth workgroup takes itself for the last)
         for _ in range(2):
             _, hist = enec.tune_batch(dev, ws, every=every, dtype=BF16, want_histograms=True)
             for h, w in zip(hist, want):
