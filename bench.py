@@ -45,6 +45,32 @@ MEASURED_TRAFFIC = {
 }
 
 
+def compression_calls(params, blocks, nblocks):
+    """The tensors (by number) of each compression call that makes one launch: those of one tuple and block size together, sixteen at
+    most.  One-block tensors that share neither with a longer tensor ride along in a launch of default blocks of their group length
+    whose instance has their code (m >= 2, n - m = 1 to 3), as far as its arguments (88 bytes a tensor, 64 for one that rides, 16 x 88
+    in all) and its LDS go; the rest of them have calls of their own.  (bf16.)"""
+    longer = {(p[1:], b) for p, b, nb in zip(params, blocks, nblocks) if nb > 1}
+    alone = [(p[1:], b) not in longer for p, b in zip(params, blocks)]
+    groups, waiting = {}, {}
+    for i, p in enumerate(params):
+        if alone[i]:
+            waiting.setdefault(p[3], []).append(i)
+        else:
+            groups.setdefault((p[1:], blocks[i]), []).append(i)
+    calls = [g[c:c + 16] for g in groups.values() for c in range(0, len(g), 16)]
+    for g in calls:
+        (_, n, m, L), B = params[g[0]], blocks[g[0]]
+        if B != 16384 or m < 2 or not 1 <= n - m <= 3:
+            continue
+        lds, room = 2 * (B // (8 * L) + n * B // 8) + B, min(16, (16 * 88 - 88 * len(g)) // 64)
+        ride = [j for j in waiting.get(L, [])
+                if blocks[j] + blocks[j] // (8 * L) + (params[j][1] - params[j][2]) * blocks[j] // 8 <= lds][:room]
+        g += ride
+        waiting[L] = [j for j in waiting.get(L, []) if j not in ride]
+    return calls + [g[c:c + 16] for g in waiting.values() for c in range(0, len(g), 16)]
+
+
 def kernel_sources_sha256():
     """Hash of the library's sources with // comments, blank lines and indentation taken out (no string literal of these
     files holds "//"), so that a reworded comment does not retire a measurement."""
@@ -222,10 +248,8 @@ def main():
     backs = [torch.zeros_like(s) for s in srcs]
     sizes = torch.zeros(nt, dtype=torch.int64, device="cuda")
 
-    # one library call of at most sixteen tensors per kernel launch: tensors of one tuple and block size are compressed
-    # together, and those of one block that share neither with a longer tensor ride along in the first launch of the default
-    # block size and their group length, sixteen at most; streams of one block size are decompressed together, whatever their
-    # tuples, and streams of at most sixteen blocks join the largest block size
+    # one library call per kernel launch: compression_calls; streams of one block size are decompressed together, at most
+    # sixteen and whatever their tuples, and streams of at most sixteen blocks join the largest block size
     def calls_by(key):
         found = {}
         for i in range(nt):
@@ -234,15 +258,7 @@ def main():
 
     blocks = [enec.default_block_size(n) for n in n_el]
     nblocks = [-(-n // b) for n, b in zip(n_el, blocks)]
-    longer = {(params[i][1:], blocks[i]) for i in range(nt) if nblocks[i] > 1}
-    single = [(params[i][1:], blocks[i]) not in longer for i in range(nt)]
-    ccalls = calls_by(lambda i: (params[i][3],) if single[i] else (params[i][1:], blocks[i]))
-    for g in [g for g in ccalls if single[g[0]]]:
-        for h in ccalls:
-            if not single[h[0]] and blocks[h[0]] == 16384 and params[h[0]][3] == params[g[0]][3]:
-                h += g
-                ccalls.remove(g)
-                break
+    ccalls = compression_calls(params, blocks, nblocks)
     dcalls = calls_by(lambda i: (params[i][3], max(blocks) if nblocks[i] <= 16 else blocks[i]))
 
     def compress_all(ev=None):
@@ -311,13 +327,13 @@ def main():
     # the whole stream (sign/mantissa plane, mask, packed planes, offset table, header), each read
     # or written once
     # compress_kernel<m, n - m, element format, lanes per group, log2 of a constant block size or 0>,
-    # compress_single_kernel<element format, lanes per group>, decompress_kernel<element format, lanes per group, several block
-    # sizes>; launches without blocks of the default size are kept apart
+    # compress_single_kernel<element format, lanes per group, arguments>, decompress_kernel<element format, lanes per group,
+    # several block sizes>; launches without blocks of the default size are kept apart
     def compress_name(g):
         i = g[0]
         _, n, m, L = params[i]
-        if single[i]:
-            return f"enec::compress_single_kernel<{enec.BF16}, {L // 8}>"
+        if all(nblocks[j] == 1 for j in g):
+            return f"enec::compress_single_kernel<{enec.BF16}, {L // 8}, enec::Single{'Few' if len(g) <= 4 else ''}Args>"
         return f"enec::compress_kernel<{m}, {n - m}, {enec.BF16}, {L // 8}, {14 if blocks[i] == 16384 else 0}u>"
 
     def decompress_name(g):

@@ -233,6 +233,38 @@ report(layer=compress(7, 2), few=compress(1, 19), many=compress(12, 7), full=com
                        tuples=[[4 + 2], [4, 2], [4 + 2], [4, 2], [4, 2], [4 + 2]], lengths=[4, 2])
 
 
+def test_the_benchmark_knows_what_makes_one_launch(stand_in):
+    """bench.py's compression calls make one launch each, as many of them as one call for all tensors makes, and no tensor is lost."""
+    import random
+    import bench
+    from paper_2604_03298_amd import enec
+    rng, cases, want = random.Random(5), [], []
+    for k in range(60):
+        tensors = []
+        for _ in range(rng.choice([1, 3, 9, 20, 45])):
+            n = rng.choice([100, 2048, 4096, 9000, 16384, 16385, 40000, 70000])
+            width, m = rng.choice([(6, 3), (6, 4), (2, 1), (2, 2), (8, 0), (8, 7), (3, 2)])
+            tensors.append((n, enec.default_block_size(n), (7, width, m, rng.choice([8, 16]))))
+        blocks, nblocks = [b for _, b, _ in tensors], [-(-n // b) for n, b, _ in tensors]
+        calls = bench.compression_calls([p for _, _, p in tensors], blocks, nblocks)
+        assert sorted(i for g in calls for i in g) == list(range(len(tensors)))
+        cases.append([tensors] + [[tensors[i] for i in g] for g in calls])
+        want.append([1] * len(calls))
+    got = stand_in(COMPRESS + f"""
+def launches_of(tensors):
+    items = (Item * len(tensors))()
+    for it, (n, B, p) in zip(items, tensors):
+        it.src = it.out = FAKE
+        it.n, it.B, it.params, it.cap = n, B, C.pointer(P(*p)), 1 << 30
+    word("launches").value = 0
+    assert L.enec_compress_batch(items, C.c_size_t(len(tensors)), 0, C.c_void_p(FAKE), C.c_size_t(1 << 20), C.c_void_p(64)) == 0
+    return word("launches").value
+report(of=[[launches_of(t) for t in case] for case in {cases!r}])
+""")["of"]
+    assert [c[1:] for c in got] == want
+    assert [c[0] for c in got] == [len(w) for w in want]
+
+
 @pytest.mark.parametrize("count, slots", [(1, 4), (3, 4), (5, 16)])
 def test_a_launch_for_tensors_of_one_block_passes_nothing_but_these(stand_in, count, slots):
     """The slots behind them are zero, whatever lay on the stack (an earlier call's tensors)."""
