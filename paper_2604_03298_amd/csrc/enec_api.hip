@@ -726,12 +726,10 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
             done[i] = 1;
             continue;
         }
-        CompressArgs a;
+        CompressArgs a{};
         a.ws_ctl = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_CTL);
         a.B = prep[i].B;
         a.logB = ilog2(a.B);
-        a.n_items = a.n_single = 0;
-        a.total = 0;
         size_t word = acc_words, acc = 0;   // scan words handed out to this launch (tags make reuse between launches safe)
         for (size_t j = i; j < n_items && a.n_items < (uint32_t)MAX_BATCH; ++j) {
             if (done[j] || prep[j].nb == 0 || kernel_of(j) != kernel_of(i)) continue;
@@ -908,16 +906,15 @@ int enec_compress_per_block_batch(const enec_per_block_item *items, size_t n_ite
     if (state_words < first + need_all) return ENEC_E_CAPACITY;
     std::vector<char> done(n_items, 0);
     if (use_stream) {
-        CompressArgs a;
         const size_t lds = 2 * (size_t)pb_image_bytes(L) + ENEC_DEFAULT_BLOCK;
         for (size_t i = 0; i < n_items;) {
             for (; i < n_items && !streamed(i); ++i) {}
             if (i == n_items) break;
+            CompressArgs a{};
             size_t word = acc_words, acc = 0;
             a.ws_ctl = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(workspace) + WS_CTL);
             a.B = ENEC_DEFAULT_BLOCK;
             a.logB = DEFAULT_LOGB;
-            a.n_items = a.n_single = a.total = 0;
             for (; i < n_items && a.n_items < (uint32_t)MAX_BATCH; ++i) {
                 if (!streamed(i)) continue;
                 fill_compress_item(a, acc, word, workspace, items[i].in, items[i].out, items[i].out_bytes, items[i].n_elems, dtype);

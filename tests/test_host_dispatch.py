@@ -276,3 +276,23 @@ args = bytes((C.c_uint8 * 2048).in_dll(rt, "kept"))
 report(grid=grid, used=[args[64 * i:64 * i + 64] != bytes(64) for i in range({slots})])
 """)
     assert got == dict(grid=[count], used=[True] * count + [False] * (slots - count))
+
+
+@pytest.mark.parametrize("per_block", [False, True])
+def test_a_launch_passes_no_items_of_earlier_ones(stand_in, per_block):
+    """Between a launch's items (88 bytes each, behind 40) and the tensors of one block at the end of the same 1408 bytes lie zeros."""
+    got = stand_in(COMPRESS + f"""
+class Tensor(C.Structure): _fields_ = [("src", C.c_void_p), ("n", C.c_size_t), ("B", C.c_uint32), ("out", C.c_void_p), ("cap", C.c_size_t), ("out_bytes", C.c_void_p)]
+compress(16, 0)
+word("keep_bytes").value = 1448
+if {per_block}:
+    items = (Tensor * 17)()
+    for it in items: it.src, it.n, it.B, it.out, it.cap = FAKE, 32768, 16384, FAKE, 1 << 30
+    assert L.enec_compress_per_block_batch(items, C.c_size_t(17), 0, 16, C.c_void_p(FAKE), C.c_size_t(1 << 20), C.c_void_p(64)) == 0
+else:
+    compress(1, 2)
+args = bytes((C.c_uint8 * 2048).in_dll(rt, "kept"))
+end = 1448 - (0 if {per_block} else 2 * 64)
+report(first=args[40:48] != bytes(8), between=args[128:end] == bytes(end - 128), rest=args[end:end + 8] != bytes(8))
+""")
+    assert got == dict(first=True, between=True, rest=not per_block)
