@@ -757,7 +757,7 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
     }
     for (size_t i = 0; i < n_items; ++i) {
         if (done[i]) continue;
-        SingleArgs sa{};
+        SingleArgs sa;
         size_t count = 0, lds = 0;
         uint32_t largest = 0;
         for (size_t j = i; j < n_items && count < (size_t)MAX_BATCH; ++j) {
@@ -772,9 +772,10 @@ int enec_compress_batch(const enec_compress_item *items, size_t n_items, int dty
         // (a block of 32768 elements whose records hold whole exponents: more than 64 KB has to be asked for)
         const bool is_few = count <= (size_t)SINGLE_FEW;
         if (lds > 65536 && resident_workgroups(is_few ? (const void *)few : (const void *)fn, threads, lds) == 0) return ENEC_E_HIP;
+        for (size_t j = count; j < (size_t)(is_few ? SINGLE_FEW : MAX_BATCH); ++j) sa.item[j] = SingleItem{};
         if (is_few) {
-            SingleFewArgs fa{};
-            std::copy_n(sa.item, count, fa.item);
+            SingleFewArgs fa;
+            std::copy_n(sa.item, SINGLE_FEW, fa.item);
             hipLaunchKernelGGL(few, dim3((unsigned)count), dim3(threads), lds, s, fa);
         } else {
             hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(threads), lds, s, sa);
