@@ -40,7 +40,7 @@ WORKLOADS = ["config1", "config2", "config3", "config3b", "config4", "config5"]
 MEASURED_TRAFFIC = {
     "kernel_sources_sha256": "eacb38dab1e08341157c5ddc902994c28b0c23a1287c4bdab0f03290ba6d6052",
     "bytes_per_launch": {
-        "config2": {"enec::compress_kernel<4, 2, 0, 2, 14u>": 714510293, "enec::decompress_kernel<0, 2, true>": 716905719},
+        "config2": {"enec::compress_kernel<4, 2, 0, 2, 14u>": 714510293, "enec::decompress_kernel<0, 2, true, false>": 716905719},
     },
 }
 
@@ -328,7 +328,7 @@ def main():
     # or written once
     # compress_kernel<m, n - m, element format, lanes per group, log2 of a constant block size or 0>,
     # compress_single_kernel<element format, lanes per group, arguments>, decompress_kernel<element format, lanes per group,
-    # several block sizes>; launches without blocks of the default size are kept apart
+    # several block sizes, one stream>; launches without blocks of the default size are kept apart
     def compress_name(g):
         i = g[0]
         _, n, m, L = params[i]
@@ -338,7 +338,7 @@ def main():
 
     def decompress_name(g):
         mixed = "true" if len({blocks[i] for i in g}) > 1 else "false"
-        return f"enec::decompress_kernel<{enec.BF16}, {params[g[0]][3] // 8}, {mixed}>"
+        return f"enec::decompress_kernel<{enec.BF16}, {params[g[0]][3] // 8}, {mixed}, {'true' if len(g) == 1 else 'false'}>"
 
     kern = {}
     for name, calls, dur in ((compress_name, ccalls, dur_c), (decompress_name, dcalls, dur_d)):

@@ -98,7 +98,9 @@ __device__ __forceinline__ uint32_t loaded(const DecompressItem &it)
 
 // MIXED: the streams' block sizes differ.  (In the instances for one block size it stays an argument: looked up with the
 // stream, it cost fp32 1 to 2 % and the 16-bit formats the eighth wave per SIMD, 12 % in blocks of 2048.)
-template <int DT, int LPG, bool MIXED>
+// ONE: the launch has one stream, so a block need not look for its own, nor wait for fields that only launches of several need
+// (us, without / with: 4e6 elements 5.98 / 5.81, 45e6 in fp32 58.4 / 58.1, 67e6 in blocks of 4096 40.3 / 40.2).
+template <int DT, int LPG, bool MIXED, bool ONE>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WAVES_MIN, DEC_WAVES_MAX))) decompress_kernel(const DecompressArgs p)
 {
     constexpr uint32_t E = exponent_bits(DT);
@@ -108,20 +110,24 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DEC_WA
     // the stream this block belongs to (the blocks of the launch's streams are numbered through; `first` of
     // the entries that are not used is beyond every block)
     DecompressItem it = p.item[0];
-    // The next streams' fields are on their way by then: two words bring the next 256 bytes.  (Without them a launch of two
-    // streams waits for the first one's fields and then as long again for the second's: 128 blocks of two streams 5.50 us against
-    // 5.39 where no field is loaded early, 5.29 like this.  Bringing all sixteen streams' costs every launch 4 to 6 %, and finding
-    // the stream before any field is asked for takes back what launches of one stream and long ones gain, 1 to 2 %, though
-    // 7 to 20 streams of up to 1e6 elements are 1 to 3 % faster with it.)
-    uint32_t next;
-    asm("s_mov_b32 %0, 0" : "=s"(next) : "s"(p.item[1].status), "s"(p.item[2].tuple_stride));
-    uint32_t zero = loaded(it) | next, ti = 0, first = 0;
-#pragma unroll
-    for (int i = 1; i < MAX_BATCH; ++i)
-        if (blockIdx.x + zero >= p.first[i]) { ti = i; first = p.first[i]; }
-    if (ti != 0) {
-        it = p.item[ti];
+    uint32_t zero, ti = 0, first = 0;
+    if constexpr (ONE) {
         zero = loaded(it);
+    } else {
+        // The next streams' fields are on their way by then: two words bring the next 256 bytes.  (Without them a launch of two
+        // streams waits for the first one's fields and then as long again for the second's: 128 blocks of two streams 5.50 us against
+        // 5.39 where no field is loaded early, 5.29 like this.  Bringing all sixteen streams' costs every launch 4 to 6 %.  Finding
+        // the stream before any field is asked for makes seven streams of 1e6 elements 1 to 2 % faster, sixteen of 4e6 1.4 % slower.)
+        uint32_t next;
+        asm("s_mov_b32 %0, 0" : "=s"(next) : "s"(p.item[1].status), "s"(p.item[2].tuple_stride));
+        zero = loaded(it) | next;
+#pragma unroll
+        for (int i = 1; i < MAX_BATCH; ++i)
+            if (blockIdx.x + zero >= p.first[i]) { ti = i; first = p.first[i]; }
+        if (ti != 0) {
+            it = p.item[ti];
+            zero = loaded(it);
+        }
     }
     const uint32_t k = blockIdx.x - first + zero;
     const uint32_t logB = MIXED ? it.logB : p.logB, B = MIXED ? 1u << logB : p.B, logC = logB - 3u;

@@ -54,6 +54,31 @@ def test_one_launch_for_streams_with_different_tuples(gpu, oracle, dtype, L, B):
         assert int(st.item()) == 0
 
 
+@pytest.mark.parametrize("L,B", [(8, 2048), (16, 2048), (16, 16384), (32, 4096), (8, 16384), (32, 32768)])
+@pytest.mark.parametrize("dtype", [BF16, FP16, FP32])
+def test_launches_of_one_two_and_three_streams(gpu, oracle, dtype, L, B):
+    """A stream alone has an instance of its own; the second and the third stream of a launch are found by their fields, which come
+    with the first one's."""
+    torch, enec = gpu.torch, gpu.enec
+    made = _streams(oracle, dtype, L, B, [1, 9, 257, B - 1, B, B + 1, 2 * B, 3 * B - 4, 5 * B + 3])
+    wide = torch.int32 if dtype == FP32 else torch.int16
+    poison = 0x5A5A5A5A if dtype == FP32 else 0x5A5A
+    bufs = [torch.from_numpy(np.ascontiguousarray(s)).cuda() for _, s, _ in made]
+    for count in (1, 2, 3):
+        for i in range(0, len(made), count):
+            part = made[i:i + count]
+            backs = [torch.full((w.size + 16,), poison, dtype=wide, device="cuda") for w, _, _ in part]
+            status = [torch.zeros(1, dtype=torch.int32, device="cuda") for _ in part]
+            items, keep = enec.make_decompress_items(bufs[i:i + count], [s[:64].tobytes() for _, s, _ in part],
+                                                     [b[:w.size] for b, (w, _, _) in zip(backs, part)], status)
+            assert enec.decompress_batch(bufs[i:i + count], None, backs, items=items) == enec.OK
+            torch.cuda.synchronize()
+            for (w, _, per_block), back, st in zip(part, backs, status):
+                got = back.cpu().numpy().view(WORD[dtype])
+                assert np.array_equal(got[:w.size], w) and (got[w.size:] == poison).all(), (w.size, per_block, count)
+                assert int(st.item()) == 0
+
+
 @pytest.mark.parametrize("per_block", [False, True])
 def test_a_misaligned_offset_is_skipped_and_reported(gpu, oracle, per_block):
     """Both ends of block 1 moved by 8 bytes: its size still fits, its start is no multiple of 16."""

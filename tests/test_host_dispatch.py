@@ -24,6 +24,7 @@ static struct { char *at; size_t bytes; } slot[16];  /* pinned memory: counts fi
 int capturing, launch_fails, sync_fails, gather;     /* set by the test; gather: callers that meet in a wait */
 static int gathered;
 uint32_t grid[64], block[64], lds[64];
+uint64_t fn[64];
 int keep_bytes;                                      /* of the next launches' first argument, the last launch's are kept */
 uint8_t kept[2048];
 static _Thread_local int mode;                       /* 0 = global, 2 = relaxed */
@@ -69,7 +70,7 @@ int hipStreamSynchronize(void *s)
 int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t shared, void *s)
 {
     pthread_mutex_lock(&mu);
-    if (launches < 64) { grid[launches] = g.x; block[launches] = b.x; lds[launches] = (uint32_t)shared; }
+    if (launches < 64) { grid[launches] = g.x; block[launches] = b.x; lds[launches] = (uint32_t)shared; fn[launches] = (uint64_t)f; }
     ++launches;
     for (int i = 0; i < keep_bytes; ++i) kept[i] = ((uint8_t *)args[0])[i];
     pthread_mutex_unlock(&mu);
@@ -203,6 +204,24 @@ report(before=decompress([norm] * 20 + [matrix], d), after=decompress([matrix] +
                        many=[[16 * 256, 2 * 256 + 3], [256, 256]],
                        three=[[2 * 17, 15 * 256, 15], [512, 256, 64]],
                        long=[[17 + 16, 256], [64, 256]], rest=[[17 + 15, 256 + 2], [64, 256]], sizes=[[13, 13, 14], [128, 64, 64]], empty=[[1], [64]])
+
+
+@pytest.mark.parametrize("dtype", [0, 1, 2])
+def test_a_stream_alone_has_its_own_decompression_kernel(stand_in, dtype):
+    """One for a launch of one stream, whatever its blocks, one for several of one block size, one for several block sizes."""
+    got = stand_in(DECOMPRESS + f"""
+def kernels(streams): return [(C.c_uint64 * 64).in_dll(rt, "fn")[i] for i in range(len(decompress(streams, {dtype})[0]))]
+norm, matrix, wide = (4096, 4096), (4 << 20, 16384), (17 << 15, 32768)
+one = [kernels([s]) for s in (norm, matrix, wide)]
+same = [kernels([s] * n) for s in (norm, matrix) for n in (2, 3, 16)]
+mixed = [kernels(s) for s in ([norm, matrix], [matrix, norm, norm])]
+left = kernels([matrix] * 17)
+report(one=one, same=same, mixed=mixed, left=left)
+""")
+    one, same, mixed = got["one"][0][0], got["same"][0][0], got["mixed"][0][0]
+    assert len({one, same, mixed}) == 3
+    assert got["one"] == [[one]] * 3 and got["same"] == [[same]] * 6 and got["left"] == [same, one]
+    assert got["mixed"] == [[mixed]] * 2
 
 
 COMPRESS = """
