@@ -4,9 +4,10 @@ libenec_test.so is the same library with ENEC_TEST_HOOKS defined for the host co
 variable ENEC_SPIN_LIMIT lowers the bound of the scan's waits, which the tests of that bound need.
 
 The host code (csrc/enec_api.hip, csrc/enec_pipeline.hip), the compression kernels for one tuple per data block
-(csrc/enec_per_block.hip, its fp32 kernels with deferred stores apart) and for tensors of one block (csrc/enec_single.hip), the decompression kernels (csrc/enec_decompress.hip) and the eighteen tables of
-compression kernels (csrc/enec_kernels.hip, once per element format, group length and kind of block size) are compiled
-side by side into _build/*.o and linked into libenec.so.
+(csrc/enec_per_block.hip, its fp32 kernels with deferred stores apart) and for tensors of one block (csrc/enec_single.hip), the
+decompression kernels (csrc/enec_decompress.hip, those for one stream apart) and the eighteen tables of compression kernels
+(csrc/enec_kernels.hip, once per element format, group length and kind of block size) are compiled side by side into
+_build/*.o and linked into libenec.so.
 """
 from __future__ import annotations
 
@@ -38,8 +39,8 @@ def _units():
              # enec_per_block.hpp, where both sides' figures stand: fp32 is faster with them; the unit's other kernel is the same either way)
              ("enec_per_block.o", ["-DENEC_FP32=0", "-mllvm", "-disable-machine-licm", SOURCES[2]]),
              ("enec_per_block_fp32.o", ["-DENEC_FP32=1", SOURCES[2]]),
-             ("enec_pipeline.o", [SOURCES[3]]), ("enec_decompress.o", [SOURCES[4]]),
-             ("enec_single.o", [SOURCES[5]])]
+             ("enec_pipeline.o", [SOURCES[3]]), ("enec_single.o", [SOURCES[5]]),
+             ("enec_decompress.o", ["-DENEC_ONE=0", SOURCES[4]]), ("enec_decompress_one.o", ["-DENEC_ONE=1", SOURCES[4]])]
     for lpg in (2, 1, 4):           # lanes per group: group lengths 16, 8, 32
         for dt in (0, 2, 1):
             for logb in (14, 0):    # block size: the default one as a constant, any as an argument

@@ -1108,7 +1108,7 @@ int enec_decompress_batch(const enec_decompress_item *items, size_t n_items, voi
             a.first[j] = 0xFFFFFFFFu;
             a.item[j] = a.item[0];
         }
-        DecompressFn fn = pick_decompress(h0.dtype, h0.prm.L, mixed, items_in == 1);
+        DecompressFn fn = items_in == 1 && !mixed ? pick_decompress_one(h0.dtype, h0.prm.L) : pick_decompress(h0.dtype, h0.prm.L, mixed);
         if (!fn) return ENEC_E_FORMAT;
         size_t lds = packed + (h0.dtype == ENEC_FP32 ? 16 * threads : 0);
         if (h0.dtype != ENEC_FP32 && lds < decompress_lds_floor(B)) lds = decompress_lds_floor(B);

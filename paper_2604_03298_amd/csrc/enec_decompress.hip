@@ -1,29 +1,37 @@
-// The decompression kernels (see enec_decompress.hpp): per element format and group length one instance for one stream, one for
-// several of one block size and one for several block sizes.
+// The decompression kernels (see enec_decompress.hpp), per element format and group length.  Compiled twice: with -DENEC_ONE=1 the
+// instances for one stream, with -DENEC_ONE=0 those for several, of one block size and of several block sizes.  (A process's first
+// decompression loads all instances of a unit: 1.55 ms for all 27, 1.13 for the 18 for several streams, 0.64 for the nine for one.)
 #include "enec_decompress.hpp"
+
+#ifndef ENEC_ONE
+#error "compile with -DENEC_ONE=0|1"
+#endif
 
 namespace enec {
 
-template <int DT, bool MIXED, bool ONE>
+template <int DT, bool MIXED>
 static DecompressFn decompress_for(unsigned L)
 {
-    if (L == 8) return &decompress_kernel<DT, 1, MIXED, ONE>;
-    if (L == 32) return &decompress_kernel<DT, 4, MIXED, ONE>;
-    return L == 16 ? &decompress_kernel<DT, 2, MIXED, ONE> : nullptr;
+    if (L == 8) return &decompress_kernel<DT, 1, MIXED, ENEC_ONE>;
+    if (L == 32) return &decompress_kernel<DT, 4, MIXED, ENEC_ONE>;
+    return L == 16 ? &decompress_kernel<DT, 2, MIXED, ENEC_ONE> : nullptr;
 }
 
-template <int DT>
-static DecompressFn decompress_of(unsigned L, bool mixed_block_sizes, bool one_stream)
+#if ENEC_ONE
+DecompressFn pick_decompress_one(int dtype, unsigned L)
 {
-    if (mixed_block_sizes) return decompress_for<DT, true, false>(L);
-    return one_stream ? decompress_for<DT, false, true>(L) : decompress_for<DT, false, false>(L);
+    if (dtype == DT_FP16) return decompress_for<DT_FP16, false>(L);
+    if (dtype == DT_FP32) return decompress_for<DT_FP32, false>(L);
+    return dtype == DT_BF16 ? decompress_for<DT_BF16, false>(L) : nullptr;
 }
-
-DecompressFn pick_decompress(int dtype, unsigned L, bool mixed_block_sizes, bool one_stream)
+#else
+DecompressFn pick_decompress(int dtype, unsigned L, bool mixed_block_sizes)
 {
-    if (dtype == DT_FP16) return decompress_of<DT_FP16>(L, mixed_block_sizes, one_stream);
-    if (dtype == DT_FP32) return decompress_of<DT_FP32>(L, mixed_block_sizes, one_stream);
-    return dtype == DT_BF16 ? decompress_of<DT_BF16>(L, mixed_block_sizes, one_stream) : nullptr;
+    if (dtype == DT_FP16) return mixed_block_sizes ? decompress_for<DT_FP16, true>(L) : decompress_for<DT_FP16, false>(L);
+    if (dtype == DT_FP32) return mixed_block_sizes ? decompress_for<DT_FP32, true>(L) : decompress_for<DT_FP32, false>(L);
+    if (dtype != DT_BF16) return nullptr;
+    return mixed_block_sizes ? decompress_for<DT_BF16, true>(L) : decompress_for<DT_BF16, false>(L);
 }
+#endif
 
 }  // namespace enec

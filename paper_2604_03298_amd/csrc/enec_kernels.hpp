@@ -46,7 +46,7 @@ struct DecompressArgs {
 };
 
 using DecompressFn = void (*)(const DecompressArgs);
-DecompressFn pick_decompress(int dtype, unsigned L, bool mixed_block_sizes, bool one_stream);
+DecompressFn pick_decompress(int dtype, unsigned L, bool mixed_block_sizes), pick_decompress_one(int dtype, unsigned L);
 
 // Compression with one tuple per data block (enec_per_block.hpp, compiled in enec_per_block.hip).
 // LDS copies of the block histogram in the compress kernel, and their distance in words
