@@ -734,6 +734,19 @@ __device__ __forceinline__ void load_block_rows(const Item &p, uint32_t B, uint3
 // ---------------------------------------------------------------------------------
 // compression of a tensor of one data block by one workgroup (of at most `most` threads): compress_single_kernel, and the
 // first workgroups of a compress_kernel launch that has such tensors beside it.  Q: vectors of a thread whose loads travel together
+//
+// Bound: the latency of a launch.  Such a tensor has no earlier block to wait for and nobody waits for it, so none of what
+// compress_kernel does for the order of blocks is needed here: control record, ticket, scan words and the look at them are
+// four trips to memory one after the other, and its stores wait for them.  The raw bytes are stored as soon as they are split.
+// The widths and the block size are run-time values, looked up with the tensor, so that tensors share a launch whatever their
+// tuples and lengths.
+//
+// A thread takes eight adjacent elements at a time, not the eight rows of eight columns of the other kernels: a block of
+// 4096 elements has eight waves' worth of such vectors and one wave's worth of columns.  The transformed bytes meet in LDS,
+// in element order, and Alg. 2's bit map is a table that is read at run time: each byte of a plane is the OR of up to eight
+// rotated and masked bytes.  So the code is short, which matters to a kernel that runs each instruction once or twice.
+// Two norm vectors of 4096 elements in a launch of their own, with columns / vectors: kernel 4.8 / 3.5 us (the call takes 6.9
+// either way, which is the host's time).
 // ---------------------------------------------------------------------------------
 // Alg. 2's bit map for W-bit values (HHTable) by planes: the entries of plane q, unused ones zero.
 // Bits 0-2 row, 3-7 rotation to the right, 8-15 destination bits.
