@@ -265,7 +265,8 @@ int enec_pipeline_trace(enec_pipeline *pipeline, float *ms, size_t max_steps, si
  *   histogram  NULL, or HOST array of 256 u64 that receives the exponent counts
  *   workspace  DEVICE, as for enec_compress (workspace_bytes: its size)
  * Synchronous: waits for the stream, and returns when the counts have arrived (in pinned memory, see the top).  On a stream that
- * is being captured: ENEC_E_HIP, with nothing enqueued. */
+ * is being captured: ENEC_E_HIP, with nothing enqueued.  ENEC_E_HIP also where the counts do not add up to the elements that were
+ * looked at, twice in a row: something else writes to the workspace meanwhile. */
 int enec_tune(const void *in, size_t n_elems, int dtype, enec_params *params,
               uint64_t *histogram, void *workspace, size_t workspace_bytes, void *stream);
 
